@@ -390,7 +390,7 @@ PassCfg pick_cfg(const DevLayout &L, int vk, int B = 1)
     c.vec = (vk == VK_F32) ? 4 : 8;
     if (B > 1) {
         c.mode = 0;
-        c.lpr = 8;
+        c.lpr = mm_lanes(B, 1);
         const int64_t rpb = kBlock / c.lpr;
         c.grid = (int)std::max<int64_t>(1, std::min<int64_t>((L.rows + rpb - 1) / rpb, kMaxPassGrid));
         return c;
@@ -1510,7 +1510,7 @@ int create_problem(smx_operator *op, const smx_problem_desc *d, hipStream_t s, s
     const bool tiles_on = tiles_env && std::strcmp(tiles_env, "1") == 0;
     const bool use_tiles = op->has_tiles() && tiles_fit(op->t_max_rows, B) && !tiles_off;
     const bool start_tiles = use_tiles && (B == 1 || tiles_on);
-    if (B == 1 && op->has_f32) { // one slice: the float32 passes read 16-bit indices where the range allows
+    if (op->has_f32) { // the float32 passes read 16-bit indices where the range allows
         if (op->csr.idx16.p) p->fmt1[VK_F32] = VK_F32U16;
         if (op->csc.idx16.p) p->fmt2[VK_F32] = VK_F32U16;
     }
@@ -1526,7 +1526,7 @@ int create_problem(smx_operator *op, const smx_problem_desc *d, hipStream_t s, s
         }
         if (start_tiles) {
             p->cfg2[vk].mode = 2;
-            p->cfg2[vk].lpr = 4;
+            p->cfg2[vk].lpr = B == 1 ? 4 : mm_lanes(B, 1);
             p->cfg2[vk].vec = 4;
             p->cfg2[vk].grid = std::max(1, std::min(op->t_ntiles, kMaxPassGrid));
         }
@@ -1623,11 +1623,13 @@ std::vector<PassCfg> pass_candidates(const DevLayout &L, int vk, int B)
             add(c);
         }
     }
-    const std::vector<int> lprs = (B == 1) ? std::vector<int>{2, 4, 8, 16, 32} : std::vector<int>{4, 8, 16};
+    const std::vector<int> lprs = (B == 1) ? std::vector<int>{2, 4, 8, 16, 32}
+                                           : std::vector<int>{mm_lanes(B, 0), mm_lanes(B, 1), mm_lanes(B, 2)};
     const std::vector<int> vecs = (B == 1) ? std::vector<int>{4, 8} : std::vector<int>{(vk == VK_F32) ? 4 : 8};
     for (int lpr : lprs)
         for (int vec : vecs)
-            for (int g : {1024, 2048, 4096}) {
+            for (int g : {512, 1024, 2048, 4096}) {
+                if (g == 512 && B == 1) continue;
                 PassCfg c;
                 c.mode = 0;
                 c.lpr = lpr;
@@ -1752,7 +1754,8 @@ int autotune_impl(smx_problem *p, int reps)
                         cands2.push_back(c);
                     }
             if (p->tiles_ok)
-                for (int lpr : {2, 4, 8, 16})
+                for (int lpr : p->B == 1 ? std::vector<int>{2, 4, 8, 16}
+                                         : std::vector<int>{mm_lanes(p->B, 0), mm_lanes(p->B, 1), mm_lanes(p->B, 2)})
                     for (int vec : {4, 8})
                         for (int g : {1024, 2048, 4096}) {
                             PassCfg c;

@@ -1621,53 +1621,134 @@ __global__ __launch_bounds__(kBlock) void k_step_apply(int n, int B, const doubl
 
 // ---------------------------------------------------------------------------
 // Multi-slice passes (B right-hand sides sharing A, slice-interleaved
-// vectors).  A is read once for all slices; each lane keeps one float64
-// accumulator per slice and reads the B values of the gathered vector at an
-// index as B/4 vector loads.  The summation order of a slice does not depend
-// on the other slices, so a slice's result is the same whichever slices run
+// vectors).  A is read once for all slices; the B values of the gathered
+// vector at an entry's index are one contiguous stretch of 4B bytes.  The
+// lanes of a row group are split into LS = B/4 lanes over the slices (four
+// slices each, one 16-byte load) times EG = LPR/LS lanes over the row's
+// entries, so one load instruction of a wave fetches whole stretches (B = 32:
+// eight entries, 128 bytes each).  (With all B slices in every lane, as these
+// kernels were first written, each instruction touched 64 different cache
+// lines for 16 bytes of each, and the vector memory path's address rate
+// bound the pass: 256 x 256 CT, 15.0M entries, B = 32, bf16 297 us pass 1 and
+// 254 us pass 2 against 112 and 101 now, 1.9 GB of gathered lines at 17 and
+// 19 TB/s out of L2; 128 x 128, B = 8, float32 26 and 29 us against 16 and
+// 19.)  The summation order of a slice does not depend on
+// the other slices, so a slice's result is the same whichever slices run
 // beside it.  A slice that is not live is neither read back nor written.
 // ---------------------------------------------------------------------------
 
 template <int B>
-__device__ inline void load_slices(const float *__restrict__ v, int idx, float (&out)[B])
+struct SliceLanes {
+    static constexpr int LS = B >= 4 ? B / 4 : 1; // lanes over the slices
+    static constexpr int NS = B / LS;             // slices a lane holds
+};
+
+template <int N>
+__device__ inline void load_floats(const float *__restrict__ v, float (&out)[N])
 {
-    if constexpr (B % 4 == 0) {
-        const float4 *q = reinterpret_cast<const float4 *>(v + (long long)idx * B);
-#pragma unroll
-        for (int h = 0; h < B / 4; ++h) {
-            const float4 a = q[h];
-            out[4 * h + 0] = a.x; out[4 * h + 1] = a.y; out[4 * h + 2] = a.z; out[4 * h + 3] = a.w;
-        }
-    } else if constexpr (B == 2) {
-        const float2 a = *reinterpret_cast<const float2 *>(v + (long long)idx * 2);
-        out[0] = a.x; out[1] = a.y;
+    static_assert(N == 2 || N == 4, "slices of a lane");
+    if constexpr (N == 4) {
+        const float4 a = *reinterpret_cast<const float4 *>(v);
+        out[0] = a.x; out[1] = a.y; out[2] = a.z; out[3] = a.w;
     } else {
-#pragma unroll
-        for (int s = 0; s < B; ++s) out[s] = v[(long long)idx * B + s];
+        const float2 a = *reinterpret_cast<const float2 *>(v);
+        out[0] = a.x; out[1] = a.y;
     }
 }
 
+// v[k] into out[k] where on[k] (one vector store when every one is on).
+template <int N>
+__device__ inline void store_floats(float *__restrict__ out, const float (&v)[N], const bool (&on)[N])
+{
+    bool all = true;
+#pragma unroll
+    for (int k = 0; k < N; ++k) all = all && on[k];
+    if (all) {
+        if constexpr (N == 4) *reinterpret_cast<float4 *>(out) = make_float4(v[0], v[1], v[2], v[3]);
+        else *reinterpret_cast<float2 *>(out) = make_float2(v[0], v[1]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < N; ++k)
+            if (on[k]) out[k] = v[k];
+    }
+}
+
+// Dot products of one row with a lane's NS slices of v, by lane `lane` of an
+// LPR-lane group; every lane of the group returns the sums of its slices.  Two
+// chunks of VEC entries are gathered at a time (2 * VEC loads of the vector
+// in flight per lane), the next two chunks' entries already requested.
 template <int LPR, int VEC, typename VT, int B>
 __device__ inline void row_dot_mm(const SpView &A, int beg, int end, int lane, const float *__restrict__ v,
-                                  double (&acc)[B])
+                                  double (&acc)[SliceLanes<B>::NS])
 {
+    constexpr int LS = SliceLanes<B>::LS, NS = SliceLanes<B>::NS, EG = LPR / LS, STEP = EG * VEC, U = 2;
+    static_assert(EG >= 1 && EG * LS == LPR, "lanes per row");
+    const float *vs = v + (lane & (LS - 1)) * NS;
 #pragma unroll
-    for (int s = 0; s < B; ++s) acc[s] = 0.0;
-    for (int p = beg + lane * VEC; p < end; p += LPR * VEC) {
-        float val[VEC];
-        int id[VEC];
-        Entries<VT, VEC>::load(A, p, val, id);
+    for (int s = 0; s < NS; ++s) acc[s] = 0.0;
+    int p = beg + (lane / LS) * VEC;
+    EntryRaw<VT, VEC> raw[U];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-            float xs[B];
-            load_slices<B>(v, id[e], xs);
-            const double a = (double)val[e];
+    for (int u = 0; u < U; ++u) {
+        raw[u].zero();
+        if (p + u * STEP < end) raw[u].load(A, p + u * STEP);
+    }
+    while (p < end) {
+        float val[U][VEC];
+        int id[U][VEC];
+        bool ok[U];
 #pragma unroll
-            for (int s = 0; s < B; ++s) acc[s] = fma(a, (double)xs[s], acc[s]);
+        for (int u = 0; u < U; ++u) {
+            ok[u] = p + u * STEP < end;
+            raw[u].decode(val[u], id[u]);
         }
+        p += U * STEP;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            raw[u].zero();
+            if (p + u * STEP < end) raw[u].load(A, p + u * STEP);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (ok[u]) {
+                float xs[VEC][NS];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) load_floats<NS>(vs + (long long)id[u][e] * B, xs[e]);
+#pragma unroll
+                for (int e = 0; e < VEC; ++e)
+#pragma unroll
+                    for (int s = 0; s < NS; ++s) acc[s] = fma((double)val[u][e], (double)xs[e][s], acc[s]);
+            }
     }
 #pragma unroll
-    for (int s = 0; s < B; ++s) acc[s] = group_sum<LPR>(acc[s]);
+    for (int off = LS; off < LPR; off <<= 1)
+#pragma unroll
+        for (int s = 0; s < NS; ++s) acc[s] += __shfl_xor(acc[s], off, LPR);
+}
+
+// Workgroup sums per slice of v (lane l of a wave holds slices (l mod LS) NS
+// ..), written by thread s < B to out[s * gridDim.x + blockIdx.x].
+template <int B>
+__device__ inline void slice_partials(double (&v)[SliceLanes<B>::NS], double *__restrict__ out)
+{
+    constexpr int LS = SliceLanes<B>::LS, NS = SliceLanes<B>::NS;
+    __shared__ double red[kBlock / 64][B];
+#pragma unroll
+    for (int off = LS; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < NS; ++k) v[k] += __shfl_xor(v[k], off, 64);
+    const int wid = threadIdx.x >> 6, wl = threadIdx.x & 63;
+    if (wl < LS) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) red[wid][wl * NS + k] = v[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < B) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) t += red[w][threadIdx.x];
+        out[(long long)threadIdx.x * gridDim.x + blockIdx.x] = t;
+    }
 }
 
 template <int LPR, int VEC, typename VT, int B>
@@ -1677,36 +1758,70 @@ __global__ __launch_bounds__(kBlock) void k_pass1_mm(SpView A, const float *__re
                                                      const SliceState *__restrict__ st, int query,
                                                      double *__restrict__ partials)
 {
-    __shared__ double lds[4 * B];
-    __shared__ int live[B];
-    constexpr int RPB = kBlock / LPR;
-    if (threadIdx.x < B) live[threadIdx.x] = query ? 1 : st[threadIdx.x].live;
-    __syncthreads();
+    constexpr int RPB = kBlock / LPR, LS = SliceLanes<B>::LS, NS = SliceLanes<B>::NS;
     const int lane = threadIdx.x & (LPR - 1);
     const int grp = threadIdx.x / LPR;
-    double pacc[B];
+    const int s0 = (lane & (LS - 1)) * NS; // this lane's first slice
+    bool live[NS];
+    double pacc[NS];
 #pragma unroll
-    for (int s = 0; s < B; ++s) pacc[s] = 0.0;
+    for (int k = 0; k < NS; ++k) {
+        live[k] = query ? true : st[s0 + k].live != 0;
+        pacc[k] = 0.0;
+    }
     const long long stride = (long long)gridDim.x * RPB;
-    for (long long row = (long long)blockIdx.x * RPB + grp; row < A.rows; row += stride) {
-        const int beg = A.ptr[row], end = A.ptr[row + 1];
-        double acc[B];
-        row_dot_mm<LPR, VEC, VT, B>(A, beg, end, lane, x, acc);
-        if (lane == 0) {
-            const float d = w.D[row], sw = w.S[row];
-#pragma unroll
-            for (int s = 0; s < B; ++s) {
-                if (!live[s]) continue;
-                pacc[s] += epi1(w, acc[s] * (double)A.vscale_inv, lower[row * B + s], upper[row * B + s], d, sw,
-                                c + row * B + s, row, s, B);
-            }
+    long long row = (long long)blockIdx.x * RPB + grp;
+    int beg = 0, end = 0;
+    if (row < A.rows) {
+        beg = A.ptr[row];
+        end = A.ptr[row + 1];
+    }
+    for (; row < A.rows; row += stride) {
+        int nbeg = 0, nend = 0; // the next row's offsets, in flight meanwhile
+        if (row + stride < A.rows) {
+            nbeg = A.ptr[row + stride];
+            nend = A.ptr[row + stride + 1];
         }
-    }
-    block_sum<B>(pacc, lds);
-    if (threadIdx.x == 0) {
+        float lo[NS], up[NS], cv[NS]; // epilogue operands, fetched while the row streams
+        load_floats<NS>(lower + row * B + s0, lo);
+        load_floats<NS>(upper + row * B + s0, up);
+        const float d = w.D[row], sw = w.S[row];
+        double acc[NS];
+        row_dot_mm<LPR, VEC, VT, B>(A, beg, end, lane, x, acc);
+        if (lane < LS) {
 #pragma unroll
-        for (int s = 0; s < B; ++s) partials[(long long)s * gridDim.x + blockIdx.x] = pacc[s];
+            for (int k = 0; k < NS; ++k) {
+                cv[k] = 0.f;
+                if (live[k]) pacc[k] += epi1(w, acc[k] * (double)A.vscale_inv, lo[k], up[k], d, sw, &cv[k], row, s0 + k, B);
+            }
+            const bool dose_row = w.dose && row >= w.dose_lo && row < w.dose_hi;
+            if (!w.qform && !dose_row) store_floats<NS>(c + row * B + s0, cv, live);
+        }
+        beg = nbeg;
+        end = nend;
     }
+    slice_partials<B>(pacc, partials);
+}
+
+// Column step of a lane's NS slices of one column (x and ybuf index e .. e +
+// NS - 1, live slices only); adds y^2 to yacc in the deferred mode.
+template <int NS>
+__device__ inline void epi2_slices(const ColStep &cs, long long col, long long e, const double (&y)[NS],
+                                   const float (&xo)[NS], float l, float u, const bool (&live)[NS],
+                                   float *__restrict__ x, double (&yacc)[NS])
+{
+    if (cs.defer) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k)
+            if (live[k]) yacc[k] += epi2(cs, col, e + k, y[k], xo[k], l, u, x);
+        return;
+    }
+    const double f = cs.zcol ? (double)cs.zcol[col] : 1.0;
+    float xn[NS];
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
+        xn[k] = (float)fmin(fmax(fma((double)cs.lambda, y[k] * f, (double)xo[k]), (double)l), (double)u);
+    store_floats<NS>(x + e, xn, live);
 }
 
 template <int LPR, int VEC, typename VT, int B>
@@ -1715,45 +1830,52 @@ __global__ __launch_bounds__(kBlock) void k_pass2_mm(SpView At, const float *__r
                                                      SliceState *__restrict__ st_out,
                                                      const double *__restrict__ part1, int nparts1, Hist h)
 {
-    __shared__ double lds[4 * B];
-    __shared__ int live[B];
-    constexpr int RPB = kBlock / LPR;
-    if (threadIdx.x < B) live[threadIdx.x] = st_in[threadIdx.x].live;
-    __syncthreads();
+    __shared__ double lds[4];
+    constexpr int RPB = kBlock / LPR, LS = SliceLanes<B>::LS, NS = SliceLanes<B>::NS;
     const int lane = threadIdx.x & (LPR - 1);
     const int grp = threadIdx.x / LPR;
-    double yacc[B];
+    const int s0 = (lane & (LS - 1)) * NS;
+    bool live[NS];
+    double yacc[NS];
 #pragma unroll
-    for (int s = 0; s < B; ++s) yacc[s] = 0.0;
+    for (int k = 0; k < NS; ++k) {
+        live[k] = st_in[s0 + k].live != 0;
+        yacc[k] = 0.0;
+    }
     const long long stride = (long long)gridDim.x * RPB;
-    for (long long col = (long long)blockIdx.x * RPB + grp; col < At.rows; col += stride) {
-        const int beg = At.ptr[col], end = At.ptr[col + 1];
-        double acc[B];
+    long long col = (long long)blockIdx.x * RPB + grp;
+    int beg = 0, end = 0;
+    if (col < At.rows) {
+        beg = At.ptr[col];
+        end = At.ptr[col + 1];
+    }
+    for (; col < At.rows; col += stride) {
+        int nbeg = 0, nend = 0; // the next column's offsets, in flight meanwhile
+        if (col + stride < At.rows) {
+            nbeg = At.ptr[col + stride];
+            nend = At.ptr[col + stride + 1];
+        }
+        float xo[NS];
+        load_floats<NS>(x + col * B + s0, xo);
+        const float l = cs.lo[col], u = cs.hi[col];
+        double acc[NS];
         row_dot_mm<LPR, VEC, VT, B>(At, beg, end, lane, c, acc);
-        if (lane == 0) {
-            const float l = cs.lo[col], u = cs.hi[col];
+        if (lane < LS) {
 #pragma unroll
-            for (int s = 0; s < B; ++s) {
-                if (!live[s]) continue;
-                yacc[s] += epi2(cs, col, col * B + s, acc[s] * (double)At.vscale_inv, x[col * B + s], l, u, x);
-            }
+            for (int k = 0; k < NS; ++k) acc[k] *= (double)At.vscale_inv;
+            epi2_slices<NS>(cs, col, col * B + s0, acc, xo, l, u, live, x, yacc);
         }
+        beg = nbeg;
+        end = nend;
     }
-    if (cs.defer) {
-        block_sum<B>(yacc, lds);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int s = 0; s < B; ++s) cs.ypart[(long long)s * gridDim.x + blockIdx.x] = yacc[s];
-        }
-    } else if (blockIdx.x == 0) {
-        finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
-    }
+    if (cs.defer) slice_partials<B>(yacc, cs.ypart);
+    else if (blockIdx.x == 0) finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
 }
 
 // Pass 2 over the image-tile column layout for B slices: the tile's rows of
 // c (B values each, slice-interleaved as in memory) are staged in LDS, and
 // every entry of a column reads its B values from there, as k_pass2_tile does
-// for one slice.  Each slice's sums follow the same order as in k_pass2_tile.
+// for one slice.
 template <int LPR, int VEC, typename VT, int B>
 __global__ __launch_bounds__(kBlock) void k_pass2_tile_mm(TileView T, const float *__restrict__ c,
                                                           float *__restrict__ x, ColStep cs,
@@ -1763,20 +1885,24 @@ __global__ __launch_bounds__(kBlock) void k_pass2_tile_mm(TileView T, const floa
 {
     extern __shared__ float4 cl4[]; // 16-byte aligned: rows of B floats
     float *cl = reinterpret_cast<float *>(cl4);
-    __shared__ double lds[4 * B];
-    __shared__ int live[B];
-    constexpr int RPB = kBlock / LPR;
-    if (threadIdx.x < B) live[threadIdx.x] = st_in[threadIdx.x].live;
+    __shared__ double lds[4];
+    __shared__ int any_live;
+    constexpr int RPB = kBlock / LPR, LS = SliceLanes<B>::LS, NS = SliceLanes<B>::NS;
+    if (threadIdx.x == 0) any_live = 0;
     __syncthreads();
-    bool any = false;
-#pragma unroll
-    for (int s = 0; s < B; ++s) any = any || live[s];
+    if (threadIdx.x < B && st_in[threadIdx.x].live) any_live = 1; // every writer stores 1
+    __syncthreads();
     const int lane = threadIdx.x & (LPR - 1);
     const int grp = threadIdx.x / LPR;
-    double yacc[B];
+    const int s0 = (lane & (LS - 1)) * NS;
+    bool live[NS];
+    double yacc[NS];
 #pragma unroll
-    for (int s = 0; s < B; ++s) yacc[s] = 0.0;
-    if (any) {
+    for (int k = 0; k < NS; ++k) {
+        live[k] = st_in[s0 + k].live != 0;
+        yacc[k] = 0.0;
+    }
+    if (any_live) {
         for (int t = blockIdx.x; t < T.ntiles; t += gridDim.x) {
             const int r0 = T.rptr[t], nr = T.rptr[t + 1] - r0;
             __syncthreads(); // the previous tile's readers are done with cl
@@ -1786,29 +1912,22 @@ __global__ __launch_bounds__(kBlock) void k_pass2_tile_mm(TileView T, const floa
             for (int q = grp; q < np; q += RPB) {
                 const int col = T.tcol[p0 + q];
                 const int beg = T.A.ptr[p0 + q], end = T.A.ptr[p0 + q + 1];
-                double acc[B];
+                const long long e = (long long)col * B + s0;
+                float xo[NS];
+                load_floats<NS>(x + e, xo);
+                const float l = cs.lo[col], u = cs.hi[col];
+                double acc[NS];
                 row_dot_mm<LPR, VEC, VT, B>(T.A, beg, end, lane, cl, acc);
-                if (lane == 0) {
-                    const float l = cs.lo[col], u = cs.hi[col];
+                if (lane < LS) {
 #pragma unroll
-                    for (int s = 0; s < B; ++s) {
-                        if (!live[s]) continue;
-                        yacc[s] += epi2(cs, col, (long long)col * B + s, acc[s] * (double)T.A.vscale_inv,
-                                        x[(long long)col * B + s], l, u, x);
-                    }
+                    for (int k = 0; k < NS; ++k) acc[k] *= (double)T.A.vscale_inv;
+                    epi2_slices<NS>(cs, col, e, acc, xo, l, u, live, x, yacc);
                 }
             }
         }
     }
-    if (cs.defer) {
-        block_sum<B>(yacc, lds);
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int s = 0; s < B; ++s) cs.ypart[(long long)s * gridDim.x + blockIdx.x] = yacc[s];
-        }
-    } else if (blockIdx.x == 0) {
-        finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
-    }
+    if (cs.defer) slice_partials<B>(yacc, cs.ypart);
+    else if (blockIdx.x == 0) finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
 }
 
 // Query: the proximity at the current x from pass 1's partials (query mode).
@@ -2874,10 +2993,11 @@ static hipError_t pass1_mm(const PassCfg &cfg, const SpView &A, const float *x, 
                            double *partials, hipStream_t s)
 {
     const dim3 grid(cfg.grid), block(kBlock);
+    constexpr int L0 = mm_lanes(B, 0), L1 = mm_lanes(B, 1), L2 = mm_lanes(B, 2);
     switch (cfg.lpr) {
-    case 4: hipLaunchKernelGGL((k_pass1_mm<4, VEC, VT, B>), grid, block, 0, s, A, x, lower, upper, w, c, st, query, partials); break;
-    case 8: hipLaunchKernelGGL((k_pass1_mm<8, VEC, VT, B>), grid, block, 0, s, A, x, lower, upper, w, c, st, query, partials); break;
-    case 16: hipLaunchKernelGGL((k_pass1_mm<16, VEC, VT, B>), grid, block, 0, s, A, x, lower, upper, w, c, st, query, partials); break;
+    case L0: hipLaunchKernelGGL((k_pass1_mm<L0, VEC, VT, B>), grid, block, 0, s, A, x, lower, upper, w, c, st, query, partials); break;
+    case L1: hipLaunchKernelGGL((k_pass1_mm<L1, VEC, VT, B>), grid, block, 0, s, A, x, lower, upper, w, c, st, query, partials); break;
+    case L2: hipLaunchKernelGGL((k_pass1_mm<L2, VEC, VT, B>), grid, block, 0, s, A, x, lower, upper, w, c, st, query, partials); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -3106,7 +3226,7 @@ hipError_t launch_pass1(const PassCfg &cfg, const SpView &A, const RowBlocks &RB
         return pass1_lds_kind(cfg, vk, A, x, lower, upper, w, c, st, query, partials, 0, s);
     }
     if (B > 1) {
-        if (vk == VK_F32U16) return hipErrorInvalidValue;
+        if (vk == VK_F32U16) return pass1_mm_b<F32U16Tag, 4>(cfg, A, x, lower, upper, w, c, st, B, query, partials, s);
         if (vk == VK_F32) return pass1_mm_b<float, 4>(cfg, A, x, lower, upper, w, c, st, B, query, partials, s);
         if (vk == VK_BF16) return pass1_mm_b<Bf16Tag, 8>(cfg, A, x, lower, upper, w, c, st, B, query, partials, s);
         if (vk == VK_BF16P) return pass1_mm_b<Bf16PTag, 4>(cfg, A, x, lower, upper, w, c, st, B, query, partials, s);
@@ -3188,10 +3308,11 @@ static hipError_t pass2_mm(const PassCfg &cfg, const SpView &At, const float *c,
 {
     const dim3 grid(cfg.grid), block(kBlock);
 #define SMX_P2MM(L) hipLaunchKernelGGL((k_pass2_mm<L, VEC, VT, B>), grid, block, 0, s, At, c, x, cs, st_in, st_out, part1, nparts1, h)
+    constexpr int L0 = mm_lanes(B, 0), L1 = mm_lanes(B, 1), L2 = mm_lanes(B, 2);
     switch (cfg.lpr) {
-    case 4: SMX_P2MM(4); break;
-    case 8: SMX_P2MM(8); break;
-    case 16: SMX_P2MM(16); break;
+    case L0: SMX_P2MM(L0); break;
+    case L1: SMX_P2MM(L1); break;
+    case L2: SMX_P2MM(L2); break;
     default: return hipErrorInvalidValue;
     }
 #undef SMX_P2MM
@@ -3221,11 +3342,11 @@ static hipError_t pass2_tiles_mm(const PassCfg &cfg, const TileView &T, const fl
     const dim3 grid(cfg.grid), block(kBlock);
     const size_t shm = sizeof(float) * B * size_t(T.max_rows > 0 ? T.max_rows : 1);
 #define SMX_P2TM(L) hipLaunchKernelGGL((k_pass2_tile_mm<L, VEC, VT, B>), grid, block, shm, s, T, c, x, cs, st_in, st_out, part1, nparts1, h)
+    constexpr int L0 = mm_lanes(B, 0), L1 = mm_lanes(B, 1), L2 = mm_lanes(B, 2);
     switch (cfg.lpr) {
-    case 2: SMX_P2TM(2); break;
-    case 4: SMX_P2TM(4); break;
-    case 8: SMX_P2TM(8); break;
-    case 16: SMX_P2TM(16); break;
+    case L0: SMX_P2TM(L0); break;
+    case L1: SMX_P2TM(L1); break;
+    case L2: SMX_P2TM(L2); break;
     default: return hipErrorInvalidValue;
     }
 #undef SMX_P2TM
@@ -3301,7 +3422,7 @@ hipError_t launch_pass2(const PassCfg &cfg, const SpView &At, const RowBlocks &R
         return pass2_lds_kind(cfg, vk, At, c, x, cs, st_in, st_out, part1, nparts1, h, 0, s);
     }
     if (B > 1) {
-        if (vk == VK_F32U16) return hipErrorInvalidValue;
+        if (vk == VK_F32U16) return pass2_mm_b<F32U16Tag, 4>(cfg, At, c, x, cs, st_in, st_out, B, part1, nparts1, h, s);
         if (vk == VK_F32) return pass2_mm_b<float, 4>(cfg, At, c, x, cs, st_in, st_out, B, part1, nparts1, h, s);
         if (vk == VK_BF16) return pass2_mm_b<Bf16Tag, 8>(cfg, At, c, x, cs, st_in, st_out, B, part1, nparts1, h, s);
         if (vk == VK_BF16P) return pass2_mm_b<Bf16PTag, 4>(cfg, At, c, x, cs, st_in, st_out, B, part1, nparts1, h, s);

@@ -26,7 +26,7 @@ constexpr int kApplyBlock = 1024;  // threads of the fused pass's apply kernel (
 // entry: the 16-bit value in the low half, a 16-bit index in the high half
 // (used when the layout's index range fits in 16 bits).
 // VK_F32U16: float32 values beside a uint16 index array (a layout whose
-// index range fits in 16 bits, one-slice passes).
+// index range fits in 16 bits).
 enum ValKind : int { VK_F32 = 0, VK_BF16 = 1, VK_F16 = 2, VK_BF16P = 3, VK_F16P = 4, VK_F32U16 = 5 };
 enum ObjKind : int { OBJ_NONE = 0, OBJ_SQNORM = 1, OBJ_TV2D = 2, OBJ_LINEAR = 3, OBJ_L1 = 4 };
 
@@ -263,6 +263,13 @@ hipError_t launch_get_column(float *dst, const float *src, int64_t rows, int B, 
 hipError_t launch_check_bands(const float *lo, const float *up, int64_t m, unsigned *flag, hipStream_t s);
 hipError_t launch_reset_slot(SliceState *st, int slot, int64_t budget, hipStream_t s);
 hipError_t launch_disable_slot(SliceState *st, int slot, hipStream_t s);
+
+// lanes per row of the multi-slice passes for B slices, choice i of 3: the
+// lanes over the slices (four slices a lane) times 1, 2 or 4 lanes over the
+// entries (B = 32), 2, 4 or 8 (B = 8, 16), 4, 8 or 16 (B = 2, 4)
+// (256 x 256 CT, B = 32, bf16: pass 1 112 us with 16 lanes, 119 / 125 with 8
+// / 32 at 1,024 workgroups; pass 2 101 / 116 / 103)
+constexpr int mm_lanes(int B, int i) { return (B >= 16 ? 8 : 4) << i; }
 
 constexpr int kMaxPassGrid = 4096; // workgroups of a pass kernel (one proximity partial each)
 

@@ -38,6 +38,33 @@ def test_batched_random_sparse(smx, obj):
     check_parity(smx, w, w.K, perturb=obj != W.OBJ_NONE)
 
 
+@pytest.mark.parametrize("B,storage,n", [(2, "f32", 90), (4, "f16", 90), (16, "bf16", 90), (32, "f16", 90),
+                                         (32, "f32", 90), (16, "f32", 66000), (8, "bf16", 66000)])
+def test_batched_lanes_over_slices(smx, B, storage, n):
+    """Each split of a row's lanes over slices and entries, with empty, short
+    (one chunk) and full-length rows, 16-bit and 32-bit column indices, and
+    every stored format: one feasibility step from x0 against the oracle's.  The
+    device rounds D_i, c_i and the result to float32 and nothing else, so an
+    entry may be off by 2 u sum_i |c_i a_ij| + u |x_j| (u = 2^-24)."""
+    w = W.random_sparse(260, n, 9, seed=70 + B, B=B, empty_frac=0.2, long_rows=2, long_len=1500, obj=W.OBJ_NONE, K=1)
+    p = smx.problem_from_workload(w, storage=storage, refine_iters=0)
+    p.run(1, perturb=False)
+    x = p.get_x().cpu().numpy().astype(np.float64)
+    p.close()
+    u = 2.0 ** -24
+    rows = np.repeat(np.arange(w.m), np.diff(w.row_ptr))
+    for s in range(B):
+        P = oracle.from_workload(w, s, value_round=None if storage == "f32" else storage)
+        x0 = w.x0[:, s].astype(np.float64)
+        xo, _ = P.step(x0)
+        r, q = P.matvec(x0), P.row_sqnorms()
+        c = np.where(q > 0, P.w / np.where(q > 0, q, 1.0), 0.0) * (np.clip(r, P.lower, P.upper) - r)
+        terms = np.zeros(w.n)
+        np.add.at(terms, w.col_idx, np.abs(c[rows] * P.val))
+        bound = 1.01 * (2 * u * terms + u * np.abs(xo)) + 1e-13
+        assert np.all(np.abs(x[:, s] - xo) <= bound), (s, float(np.max(np.abs(x[:, s] - xo) / bound)))
+
+
 @pytest.mark.parametrize("storage,B", [("f32", 2), ("f32", 4), ("bf16", 4), ("f32", 8)])
 def test_batched_image_tiles(smx, storage, B, monkeypatch):
     """Several slices of an image operator take pass 2 over the tile layout (a
