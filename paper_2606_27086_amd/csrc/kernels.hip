@@ -1984,11 +1984,22 @@ __device__ inline int trial_width(const SliceState &S, const PertParams &pp)
     return min(w, left);
 }
 
+// Rows of a TV tile: kTile for one slice; for several, halved (down to 2)
+// while the image has under 256 tiles.
+static inline int tv_tile_rows(const PertParams &pp)
+{
+    int th = kTile;
+    if (pp.B > 1)
+        while (th > 2 && ((pp.tv_rows + th - 1) / th) * ((pp.tv_cols + kTile - 1) / kTile) < 256) th /= 2;
+    return th;
+}
+
 // Grid of the phase kernels: blockIdx.y is the slice, blockIdx.x a tile (TV)
 // or a chunk of the vector.
 int phase_grid(const PertParams &pp)
 {
-    if (pp.obj == OBJ_TV2D) return ((pp.tv_rows + kTile - 1) / kTile) * ((pp.tv_cols + kTile - 1) / kTile);
+    if (pp.obj == OBJ_TV2D)
+        return ((pp.tv_rows + tv_tile_rows(pp) - 1) / tv_tile_rows(pp)) * ((pp.tv_cols + kTile - 1) / kTile);
     long long g = (pp.n + kBlock * 4 - 1) / (kBlock * 4);
     return (int)(g < 1 ? 1 : (g > 512 ? 512 : g));
 }
@@ -2401,6 +2412,245 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x,
             for (int k = 0; k < 4; ++k)
                 if (t0 + k < ntr) part_out[(long long)(t0 + k) * nslots + slot] = acc[k];
         }
+    }
+}
+
+// -- TV2D for several slices: one workgroup takes a tile's pixels of every
+//    slice, thread t slice t mod B of pixel t / B, then of the pixel
+//    blockDim / B further on, ...  The layout is slice-interleaved, so a
+//    wave's loads are whole cache lines; with a workgroup per (tile, slice),
+//    as for one slice, each read 4 bytes of a line that B workgroups fetch
+//    (B = 32 at 256 x 256: 124 us a trial launch, 25 us the gradient).
+
+//    The tiles are kTile wide and tv_tile_rows(pp) high: 16 rows on large
+//    images, fewer while that leaves the device with under 256 workgroups (a
+//    128 x 128 image of 8 slices in 64 tiles of 16 rows: 6.5 us the gradient,
+//    10 us the trials).
+
+// Threads of such a workgroup: 256 for small tiles, whose barriers and
+// reductions over 16 waves would outweigh the pixels.
+constexpr int kTrialSmallBlock = 256;
+static inline bool tv_small_block(const PertParams &pp) { return tv_tile_rows(pp) * kTile * pp.B < 2048; }
+
+// Sums per slice over a workgroup of BS threads (thread t holds slice t mod
+// B): the total of value v and slice s is returned to thread v * B + s.
+// red holds (BS/64) * NV * B doubles; barriers inside.
+template <int NV, int B, int BS>
+__device__ inline double block_sum_slices(double (&v)[NV], double *red)
+{
+    static_assert(NV * B <= BS, "one total a thread");
+#pragma unroll
+    for (int off = B; off < 64; off <<= 1)
+#pragma unroll
+        for (int k = 0; k < NV; ++k) v[k] += __shfl_xor(v[k], off, 64);
+    const int wid = threadIdx.x >> 6, wl = threadIdx.x & 63;
+    __syncthreads(); // the previous use of red is over
+    if (wl < B) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) red[(wid * NV + k) * B + wl] = v[k];
+    }
+    __syncthreads();
+    double t = 0.0;
+    if (threadIdx.x < NV * B) {
+        for (int w = 0; w < BS / 64; ++w) t += red[w * NV * B + threadIdx.x];
+    }
+    return t;
+}
+
+template <int B, int BS>
+__global__ __launch_bounds__(BS) void k_phase_tv_mm(const float *__restrict__ x, float *__restrict__ g,
+                                                    const SliceState *__restrict__ st, PertParams pp, int th,
+                                                    int eval_only, double *__restrict__ partials)
+{
+    constexpr int PX = BS / B;
+    __shared__ double red[BS / 64 * 2 * B];
+    const int s = threadIdx.x & (B - 1);
+    const int R = pp.tv_rows, C = pp.tv_cols;
+    const int tiles_x = (C + kTile - 1) / kTile;
+    const int i0 = (blockIdx.x / tiles_x) * th, j0 = (blockIdx.x % tiles_x) * kTile;
+    double v[2] = {0.0, 0.0}; // sum g^2, f
+    if (eval_only || st[s].live != 0) {
+        for (int pl = threadIdx.x / B; pl < th * kTile; pl += PX) {
+            const int i = i0 + pl / kTile, j = j0 + pl % kTile;
+            if (i >= R || j >= C) continue;
+            const long long e = ((long long)i * C + j) * B + s, up = (long long)C * B;
+            const bool here = i <= R - 2 && j <= C - 2, above = i >= 1 && j <= C - 2, left = j >= 1 && i <= R - 2;
+            const double x00 = (double)x[e];
+            double x10 = 0.0, x01 = 0.0, xm0 = 0.0, xm1 = 0.0, x0m = 0.0, x1m = 0.0;
+            if (i <= R - 2) x10 = (double)x[e + up];
+            if (j <= C - 2) x01 = (double)x[e + B];
+            if (above) {
+                xm0 = (double)x[e - up];
+                xm1 = (double)x[e - up + B];
+            }
+            if (left) {
+                x0m = (double)x[e - B];
+                x1m = (double)x[e + up - B];
+            }
+            double gv = 0.0;
+            if (here) {
+                const double tau = tv_tau(x00, x10, x01, pp.tv_eps2);
+                v[1] += tau;
+                if (tau > 0.0) gv -= ((x10 - x00) + (x01 - x00)) / tau;
+            }
+            if (above) { // term (i-1, j): this pixel is its +1 row neighbour
+                const double tau = tv_tau(xm0, x00, xm1, pp.tv_eps2);
+                if (tau > 0.0) gv += (x00 - xm0) / tau;
+            }
+            if (left) { // term (i, j-1): this pixel is its +1 column neighbour
+                const double tau = tv_tau(x0m, x1m, x00, pp.tv_eps2);
+                if (tau > 0.0) gv += (x00 - x0m) / tau;
+            }
+            if (!eval_only) {
+                const float gf = (float)gv;
+                g[e] = gf;
+                v[0] += (double)gf * (double)gf;
+            }
+        }
+    }
+    const double t = block_sum_slices<2, B, BS>(v, red);
+    if (threadIdx.x < 2 * B) // value-major partials, slot (slice, tile)
+        partials[(long long)threadIdx.x * gridDim.x + blockIdx.x] = t;
+}
+
+// Totals over the nt tiles of rows (value v0 + r / B, slice r mod B), r < nv *
+// B, into tot[r] (LDS): row by row within a wave, lane l adding tiles l, l +
+// 64, ... in order and wave_sum the lanes.  Every thread must call it.
+template <int B, int BS>
+__device__ inline void slice_totals(const double *__restrict__ part, int nt, int v0, int nv, double *tot)
+{
+    constexpr int W = BS / 64, Q = 4; // rows a wave sums at a time
+    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63, rows = nv * B;
+    const double *p = part + (long long)v0 * B * nt;
+    for (int r0 = wid; r0 < rows; r0 += W * Q) { // the same in every lane
+        double a[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) a[q] = 0.0;
+        for (int b = lane; b < nt; b += 64) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q) a[q] += p[(long long)min(r0 + q * W, rows - 1) * nt + b];
+        }
+        wave_sum<Q>(a);
+        if (lane == 0) {
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+                if (r0 + q * W < rows) tot[r0 + q * W] = a[q];
+        }
+    }
+    __syncthreads();
+}
+
+// Trial launch for TV with several slices: k_trial_tv's decisions for every
+// slice (thread s < B holds slice s's), then each slice either evaluates its
+// next batch of trials or gets its accepted step, whichever its state asks
+// for.  The totals a decision needs are read one trial first (usually
+// accepted), the rest of the batch only while a slice is undecided.  With
+// evaluate = 0 this is the phase's closing launch.
+template <int B, int BS>
+__global__ __launch_bounds__(BS) void k_trial_tv_mm(float *__restrict__ x, const float *__restrict__ g,
+                                                    const SliceState *__restrict__ st_in,
+                                                    SliceState *__restrict__ st_out, PertParams pp, int th,
+                                                    int first, int evaluate, const double *__restrict__ part_prev,
+                                                    double *__restrict__ part_out)
+{
+    constexpr int PX = BS / B, T = 8; // trials evaluated at a time
+    static_assert(sizeof(SliceState) % 8 == 0, "copied by words");
+    static_assert(T * B <= BS, "one trial and slice a thread");
+    __shared__ SliceState sS[B];
+    __shared__ double tot[T * B];
+    __shared__ double coef[T * B];
+    __shared__ double red[BS / 64 * T * B];
+    __shared__ int most; // trials the widest slice evaluates
+    const int s = threadIdx.x & (B - 1), nt = gridDim.x;
+    const int R = pp.tv_rows, C = pp.tv_cols;
+    const int tiles_x = (C + kTile - 1) / kTile;
+    const int i0 = (blockIdx.x / tiles_x) * th, j0 = (blockIdx.x % tiles_x) * kTile;
+    {
+        const unsigned long long *src = reinterpret_cast<const unsigned long long *>(st_in);
+        unsigned long long *dst = reinterpret_cast<unsigned long long *>(sS);
+        for (int k = threadIdx.x; k < (int)(B * sizeof(SliceState) / 8); k += BS) dst[k] = src[k];
+    }
+    if (threadIdx.x == 0) most = 0;
+    if (first) {
+        slice_totals<B, BS>(part_prev, nt, 0, 2, tot); // its barrier also publishes sS
+        if (threadIdx.x < B) open_phase_state(sS[threadIdx.x], pp, tot[threadIdx.x], tot[B + threadIdx.x]);
+        __syncthreads();
+    } else {
+        __syncthreads();
+        int ntr = 0, acc_t = -1;
+        double acc_f = 0.0;
+        bool need = false;
+        if (threadIdx.x < B) {
+            ntr = trial_width(sS[threadIdx.x], pp);
+            need = ntr > 0;
+        }
+        for (int t0 = 0, nv = 1; __syncthreads_or(need); t0 += nv, nv = T) { // ends: t0 passes every ntr
+            slice_totals<B, BS>(part_prev, nt, t0, min(nv, pp.max_trials - t0), tot);
+            if (need) {
+                for (int w = 0; w < nv && t0 + w < ntr; ++w)
+                    if (tot[w * B + threadIdx.x] <= sS[threadIdx.x].f_cur) {
+                        acc_t = t0 + w;
+                        acc_f = tot[w * B + threadIdx.x];
+                        break;
+                    }
+                need = acc_t < 0 && t0 + nv < ntr;
+            }
+        }
+        if (threadIdx.x < B && ntr > 0) record_decision(sS[threadIdx.x], pp, ntr, acc_t, acc_f);
+        __syncthreads();
+    }
+    const SliceState &S = sS[s];
+    const bool apply = must_apply(S);
+    const int ntr = (evaluate && !apply) ? trial_width(S, pp) : 0;
+    if (threadIdx.x < B && ntr > 0) atomicMax(&most, ntr);
+    if (blockIdx.x == 0 && threadIdx.x < B) {
+        SliceState o = S;
+        if (apply) o.applied = 1;
+        st_out[threadIdx.x] = o;
+    }
+    const double inv_gn = 1.0 / S.gn, s_acc = S.s_acc;
+    if (apply) { // x and g of this tile and slice: no other workgroup reads or writes them in this launch
+        for (int pl = threadIdx.x / B; pl < th * kTile; pl += PX) {
+            const int i = i0 + pl / kTile, j = j0 + pl % kTile;
+            if (i < R && j < C) {
+                const long long e = ((long long)i * C + j) * B + s;
+                x[e] = (float)((double)x[e] + s_acc * (-(double)g[e] * inv_gn));
+            }
+        }
+    }
+    __syncthreads();
+    const long long nslots = (long long)B * nt;
+    for (int t0 = 0; t0 < most; t0 += T) {
+        if (threadIdx.x < T * B) { // trial t0 + k of slice s
+            const int k = threadIdx.x / B;
+            coef[threadIdx.x] = t0 + k < ntr ? s_acc + trial_beta(pp, S, S.ell + t0 + k) : 0.0;
+        }
+        __syncthreads();
+        double cf[T], acc[T];
+#pragma unroll
+        for (int k = 0; k < T; ++k) {
+            cf[k] = coef[k * B + s];
+            acc[k] = 0.0;
+        }
+        const int nk = ntr - t0;
+        if (nk > 0) {
+            for (int pl = threadIdx.x / B; pl < th * kTile; pl += PX) {
+                const int i = i0 + pl / kTile, j = j0 + pl % kTile;
+                if (i > R - 2 || j > C - 2) continue;
+                const long long e = ((long long)i * C + j) * B + s, up = (long long)C * B;
+                const double x00 = (double)x[e], x10 = (double)x[e + up], x01 = (double)x[e + B];
+                const double v00 = -(double)g[e] * inv_gn, v10 = -(double)g[e + up] * inv_gn,
+                             v01 = -(double)g[e + B] * inv_gn;
+#pragma unroll
+                for (int k = 0; k < T; ++k)
+                    if (k < nk)
+                        acc[k] += tv_tau(x00 + cf[k] * v00, x10 + cf[k] * v10, x01 + cf[k] * v01, pp.tv_eps2);
+            }
+        }
+        const double t = block_sum_slices<T, B, BS>(acc, red); // its barriers also end this chunk's use of coef
+        const int k = threadIdx.x / B;
+        if (threadIdx.x < T * B && t0 + k < ntr)
+            part_out[(long long)(t0 + k) * nslots + (long long)s * nt + blockIdx.x] = t;
     }
 }
 
@@ -4134,7 +4384,26 @@ hipError_t launch_phase(const PertParams &pp, const float *x, float *g, const fl
                         int eval_only, double *partials, hipStream_t s)
 {
     const dim3 grid(phase_grid(pp), pp.B), block(kBlock);
-    if (pp.obj == OBJ_TV2D)
+    if (pp.obj == OBJ_TV2D && pp.B > 1) {
+#define SMX_PTV(NB)                                                                                                    \
+    case NB:                                                                                                           \
+        if (tv_small_block(pp))                                                                                        \
+            hipLaunchKernelGGL((k_phase_tv_mm<NB, kTrialSmallBlock>), dim3(grid.x), dim3(kTrialSmallBlock), 0, s, x,   \
+                               g, st, pp, tv_tile_rows(pp), eval_only, partials);                                      \
+        else                                                                                                           \
+            hipLaunchKernelGGL((k_phase_tv_mm<NB, kTrialBlock>), dim3(grid.x), dim3(kTrialBlock), 0, s, x, g, st, pp,  \
+                               tv_tile_rows(pp), eval_only, partials);                                                 \
+        break
+        switch (pp.B) {
+            SMX_PTV(2);
+            SMX_PTV(4);
+            SMX_PTV(8);
+            SMX_PTV(16);
+            SMX_PTV(32);
+        default: return hipErrorInvalidValue;
+        }
+#undef SMX_PTV
+    } else if (pp.obj == OBJ_TV2D)
         hipLaunchKernelGGL(k_phase_tv, grid, block, 0, s, x, g, st, pp, eval_only, partials);
     else
         hipLaunchKernelGGL(k_phase_flat, grid, block, 0, s, x, g, lin_c, st, pp, eval_only, partials);
@@ -4277,10 +4546,36 @@ hipError_t launch_trial_linear(const PertParams &pp, float *x, const float *c, c
     return hipGetLastError();
 }
 
+static hipError_t trial_tv_mm(const PertParams &pp, float *x, const float *g, const SliceState *st_in,
+                              SliceState *st_out, int first, int evaluate, const double *part_prev, double *part_out,
+                              hipStream_t s)
+{
+#define SMX_TTV(NB)                                                                                                    \
+    case NB:                                                                                                           \
+        if (tv_small_block(pp))                                                                                        \
+            hipLaunchKernelGGL((k_trial_tv_mm<NB, kTrialSmallBlock>), dim3(phase_grid(pp)), dim3(kTrialSmallBlock), 0, \
+                               s, x, g, st_in, st_out, pp, tv_tile_rows(pp), first, evaluate, part_prev, part_out);    \
+        else                                                                                                           \
+            hipLaunchKernelGGL((k_trial_tv_mm<NB, kTrialBlock>), dim3(phase_grid(pp)), dim3(kTrialBlock), 0, s, x, g,  \
+                               st_in, st_out, pp, tv_tile_rows(pp), first, evaluate, part_prev, part_out);             \
+        break
+    switch (pp.B) {
+        SMX_TTV(2);
+        SMX_TTV(4);
+        SMX_TTV(8);
+        SMX_TTV(16);
+        SMX_TTV(32);
+    default: return hipErrorInvalidValue;
+    }
+#undef SMX_TTV
+    return hipGetLastError();
+}
+
 hipError_t launch_trial_close(const PertParams &pp, float *x, const float *g, const SliceState *st_in,
                               SliceState *st_out, const double *part_prev, hipStream_t s)
 {
     if (pp.max_trials < 1 || pp.max_trials > 1024) return hipErrorInvalidValue;
+    if (pp.obj == OBJ_TV2D && pp.B > 1) return trial_tv_mm(pp, x, g, st_in, st_out, 0, 0, part_prev, nullptr, s);
     const long long g_need = (pp.n + kTrialBlock - 1) / kTrialBlock; // one unknown a thread, at most 256 workgroups
     const unsigned grid = (unsigned)std::max(1LL, std::min(g_need, 256LL));
     hipLaunchKernelGGL(k_trial_close, dim3(grid, pp.B), dim3(kTrialBlock), 0, s, x, g, st_in, st_out, pp,
@@ -4292,6 +4587,8 @@ hipError_t launch_trial(const PertParams &pp, float *x, const float *g, const Sl
                         int first, int evaluate, const double *part_prev, double *part_out, hipStream_t s)
 {
     if (pp.max_trials < 1 || pp.max_trials > 1024) return hipErrorInvalidValue;
+    if (pp.obj == OBJ_TV2D && pp.B > 1)
+        return trial_tv_mm(pp, x, g, st_in, st_out, first, evaluate, part_prev, part_out, s);
     const dim3 grid(phase_grid(pp), pp.B), block(kBlock);
     if (pp.obj == OBJ_TV2D)
         hipLaunchKernelGGL(k_trial_tv, grid, dim3(kTrialBlock), 0, s, x, g, st_in, st_out, pp, first, evaluate,

@@ -65,6 +65,42 @@ def test_batched_lanes_over_slices(smx, B, storage, n):
         assert np.all(np.abs(x[:, s] - xo) <= bound), (s, float(np.max(np.abs(x[:, s] - xo) / bound)))
 
 
+@pytest.mark.parametrize("R,C,B", [(1, 37, 2), (19, 3, 4), (5, 70, 8), (33, 17, 16), (16, 16, 32), (18, 31, 32)])
+def test_batched_tv_ragged_images(smx, R, C, B):
+    """The total-variation phase of several slices at tile edges: images of
+    one row, narrower than a tile, exactly one tile, and with ragged last
+    tiles; two reduction steps with rejected trials (gamma = 20).  One
+    iteration from x0 against the oracle's, with the oracle's trial count.
+    Beyond the step's own rounding (2 u sum_i |c_i a_ij| + u |x_j|, u = 2^-24)
+    the device rounds g and z to float32: dz = 2 u (|z| + |z - x0|), which
+    the step passes on as at most dz + |A|^T D |A| dz."""
+    w = W.random_sparse(2 * R * C, R * C, 5, seed=60 + B, B=B, obj=W.OBJ_TV2D, K=1, tv_shape=(R, C))
+    w = w.with_params(gamma=20.0, alpha=0.8)
+    p = smx.problem_from_workload(w)
+    p.run(1)
+    x = p.get_x().cpu().numpy().astype(np.float64)
+    st, _ = p.get_state()
+    p.close()
+    u = 2.0 ** -24
+    rows = np.repeat(np.arange(w.m), np.diff(w.row_ptr))
+    for s in range(B):
+        P = oracle.from_workload(w, s)
+        x0 = w.x0[:, s].astype(np.float64)
+        z, so = P.perturb(x0)
+        assert st[s]["ell"] == so.ell, (s, st[s]["ell"], so.ell)
+        xo, _ = P.step(z)
+        r, q = P.matvec(z), P.row_sqnorms()
+        D = np.where(q > 0, P.w / np.where(q > 0, q, 1.0), 0.0)
+        c = D * (np.clip(r, P.lower, P.upper) - r)
+        dz = 2 * u * (np.abs(z) + np.abs(z - x0))
+        dr = np.zeros(w.m)
+        np.add.at(dr, rows, np.abs(P.val) * dz[w.col_idx])
+        terms = np.zeros(w.n)
+        np.add.at(terms, w.col_idx, np.abs(P.val) * (2 * u * np.abs(c[rows]) + D[rows] * dr[rows]))
+        bound = 1.01 * (terms + dz + u * np.abs(xo)) + 1e-13
+        assert np.all(np.abs(x[:, s] - xo) <= bound), (s, float(np.max(np.abs(x[:, s] - xo) / bound)))
+
+
 @pytest.mark.parametrize("storage,B", [("f32", 2), ("f32", 4), ("bf16", 4), ("f32", 8)])
 def test_batched_image_tiles(smx, storage, B, monkeypatch):
     """Several slices of an image operator take pass 2 over the tile layout (a
