@@ -86,7 +86,7 @@ extern "C" {
 #define SMX_STEP_ADAPTIVE 1
 
 /* launch form of the perturbation phase (smx_set_phase_form) */
-#define SMX_PHASE_AUTO 0       /* one launch for short flat problems, else one launch per trial batch */
+#define SMX_PHASE_AUTO 0       /* chosen by objective and size, see smx_set_phase_form */
 #define SMX_PHASE_ONE_LAUNCH 1 /* one launch per phase (squared norm, L1, linear; n <= 20,000) */
 #define SMX_PHASE_BATCHES 2    /* a direction launch, trial launches, a closing launch */
 #define SMX_PHASE_CLOSED_FORM 3 /* linear objective: a direction launch, then the trials in closed form */
@@ -501,10 +501,14 @@ int smx_set_fused(smx_problem *p, int32_t mode);
  *     n = 8,192 (there the chain of launches, not the arithmetic, sets the
  *     phase's time; one workgroup reads x at one compute unit's rate, so on
  *     longer vectors it is no faster than the chain), else CLOSED_FORM for
- *     the linear objective, else BATCHES.
+ *     the linear objective, else, for the squared norm and for L1 up to n =
+ *     131,072, a direction launch and one launch that takes each trial's
+ *     value from f along the line x + t v (the squared norm in closed form;
+ *     L1 in closed form while no entry changes sign, by summation beyond),
+ *     else BATCHES.
  * Every form accepts the same trial (the first acceptable one in order) and
  * keeps the same state; they differ in the order of the float64 sums of f
- * (and CLOSED_FORM in taking a trial's value from the identity), so a
+ * (and those in closed form in taking a trial's value from the identity), so a
  * decision taken within rounding of the acceptance threshold can differ
  * between them.  Errors: SMX_EINVAL for another form, SMX_ESTATE for
  * ONE_LAUNCH on an objective or size it does not take or CLOSED_FORM on

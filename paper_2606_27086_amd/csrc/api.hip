@@ -820,14 +820,17 @@ void enqueue_extrapolated_step(smx_problem *p, int vk, const RowW &rw, int npart
               "extrapolated step");
 }
 
-enum PhaseKind { PHASE_CHAIN, PHASE_SMALL, PHASE_LINEAR };
+enum PhaseKind { PHASE_CHAIN, PHASE_SMALL, PHASE_LINEAR, PHASE_LINE };
 
 // How the problem's perturbation phase runs: as asked, or by default in one
 // launch for flat objectives on vectors up to kSmallPhaseAutoN (one
 // workgroup streams x at one CU's rate, about 15 GB/s from memory, so its
 // time grows with n: ~6 us at n = 324, ~28 us at n = 19,881, where the
 // launch chain takes ~22-25 us whatever n), the linear objective beyond that
-// with its trials in closed form, anything else as the chain of launches.
+// with its trials in closed form, the squared norm and L1 (up to kLineMaxN,
+// past which summing the trials in every workgroup would cost more than the
+// chain's launches) with theirs valued along the line in one launch, anything
+// else as the chain of launches.
 PhaseKind phase_kind(const smx_problem *p)
 {
     switch (p->phase_form) {
@@ -836,7 +839,8 @@ PhaseKind phase_kind(const smx_problem *p)
     case SMX_PHASE_CLOSED_FORM: return PHASE_LINEAR; // likewise
     default:
         if (phase_in_one_launch(p->pp) && p->n <= kSmallPhaseAutoN) return PHASE_SMALL;
-        return p->pp.obj == OBJ_LINEAR ? PHASE_LINEAR : PHASE_CHAIN;
+        if (p->pp.obj == OBJ_LINEAR) return PHASE_LINEAR;
+        return phase_on_line(p->pp) ? PHASE_LINE : PHASE_CHAIN;
     }
 }
 
@@ -880,6 +884,7 @@ int phase_launch_count(const smx_problem *p)
             if (lin_from_apply(p, vk)) return 1;
         }
         return 2;
+    case PHASE_LINE: return 2;
     default: return chain_trial_launches(p) + 2;
     }
 }
@@ -911,6 +916,15 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
                                           p->state(cur ^ 1), p->part_phase.as<double>(), s),
                       "linear phase");
         }
+        cur ^= 1;
+    } else if (perturb && p->pp.obj != OBJ_NONE && pk == PHASE_LINE) {
+        double *least = p->part_trial[0].as<double>(); // free: this form has no trial launches
+        hip_check(launch_phase(p->pp, p->x.as<float>(), p->g.as<float>(), nullptr, p->state(cur), 0,
+                               p->part_phase.as<double>(), s, least),
+                  "phase");
+        hip_check(launch_trial_line(p->pp, p->x.as<float>(), p->g.as<float>(), p->state(cur), p->state(cur ^ 1),
+                                    p->part_phase.as<double>(), least, s),
+                  "phase on the line");
         cur ^= 1;
     } else if (perturb && p->pp.obj != OBJ_NONE) {
         hip_check(launch_phase(p->pp, p->x.as<float>(), p->g.as<float>(), p->lin_c.as<float>(), p->state(cur), 0,

@@ -20,6 +20,7 @@ constexpr int kSmallPhaseBlock = 1024; // threads of the one-launch perturbation
 constexpr int kSmallPhaseMaxN = 20000; // longest x it takes (x and the direction in LDS, 8 bytes an entry)
 constexpr int kSmallPhaseAutoN = 8192; // longest x it is the default for
 constexpr int kSmallTrials = 8;        // trials per batch there
+constexpr int kLineMaxN = 131072;      // longest x the L1 norm's phase sums in every workgroup alike
 constexpr int kApplyBlock = 1024;  // threads of the fused pass's apply kernel (16 waves share a column's partials)
 
 // Stored formats of A's entries.  The packed kinds hold one 32-bit word per
@@ -379,8 +380,15 @@ hipError_t launch_query_prox(SliceState *st, int B, const double *partials, int 
 
 int phase_grid(const PertParams &pp);
 // gradient and per-tile partials [2][B*tiles] of ||g||^2 and f(x) (eval_only: no gradient)
+// (part_min, squared norm and L1: g gets a copy of x, part_min B*tiles minima of the nonzero |x_j|)
 hipError_t launch_phase(const PertParams &pp, const float *x, float *g, const float *lin_c, const SliceState *st,
-                        int eval_only, double *partials, hipStream_t s);
+                        int eval_only, double *partials, hipStream_t s, double *part_min = nullptr);
+// Whether the phase's trials can be valued along the line (squared norm, L1 up
+// to kLineMaxN), and that phase after launch_phase with part_min (xc: its copy
+// of x): decisions and the accepted step in one launch.
+bool phase_on_line(const PertParams &pp);
+hipError_t launch_trial_line(const PertParams &pp, float *x, const float *xc, const SliceState *st_in,
+                             SliceState *st_out, const double *part_phase, const double *part_min, hipStream_t s);
 // f(x) per slice from eval_only phase partials into out[B]
 hipError_t launch_eval_objective(SliceState *st, const PertParams &pp, const double *partials, double *out,
                                  hipStream_t s);

@@ -1,0 +1,84 @@
+"""Perturbation phases one iteration at a time, against the FP64 oracle's.
+
+From the same x0 the device must try and accept the same steps (the trial
+exponent ell), and its next iterate may differ by its own roundings only: g
+and z to float32 (dz = 2 u (|z| + |z - x0|), which the step passes on as at
+most dz + |A|^T D |A| dz), D_i, c_i and the result (2 u sum_i |c_i a_ij| +
+u |x_j|), u = 2^-24.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def smx():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2606_27086_amd as smx
+
+    smx.lib()
+    return smx
+
+
+def check_iteration(smx, w, expect_launches=None):
+    p = smx.problem_from_workload(w)
+    if expect_launches is not None:
+        assert p.describe()["phase_launches"] == expect_launches
+    p.run(1)
+    x = p.get_x().cpu().numpy().astype(np.float64)
+    st, _ = p.get_state()
+    p.close()
+    u = 2.0 ** -24
+    rows = np.repeat(np.arange(w.m), np.diff(w.row_ptr))
+    for s in range(w.B):
+        P = oracle.from_workload(w, s)
+        x0 = w.x0[:, s].astype(np.float64)
+        z, so = P.perturb(x0)
+        assert st[s]["ell"] == so.ell, (s, st[s]["ell"], so.ell)
+        xo, _ = P.step(z)
+        r, q = P.matvec(z), P.row_sqnorms()
+        D = np.where(q > 0, P.w / np.where(q > 0, q, 1.0), 0.0)
+        c = D * (np.clip(r, P.lower, P.upper) - r)
+        dz = 2 * u * (np.abs(z) + np.abs(z - x0))
+        dr, terms = np.zeros(w.m), np.zeros(w.n)
+        np.add.at(dr, rows, np.abs(P.val) * dz[w.col_idx])
+        np.add.at(terms, w.col_idx, np.abs(P.val) * (2 * u * np.abs(c[rows]) + D[rows] * dr[rows]))
+        bound = 1.01 * (terms + dz + u * np.abs(xo)) + 1e-13
+        assert np.all(np.abs(x[:, s] - xo) <= bound), (s, float(np.max(np.abs(x[:, s] - xo) / bound)))
+    return st
+
+
+@pytest.mark.parametrize("obj,n,B,gamma,n_red", [
+    (W.OBJ_SQNORM, 8200, 1, 1.0, 3),    # closed form, every first trial accepted
+    (W.OBJ_SQNORM, 9000, 2, 5e3, 2),    # closed form, more rejections than one round of 64 holds
+    (W.OBJ_L1, 8193, 1, 1e-4, 4),       # no entry changes sign: closed form
+    (W.OBJ_L1, 10007, 1, 30.0, 4),      # signs change: trials summed
+    (W.OBJ_L1, 8500, 4, 400.0, 2),      # rejected sums, several slices
+    (W.OBJ_L1, 131072, 1, 300.0, 1),    # the longest x of this form
+])
+def test_phase_on_the_line(smx, obj, n, B, gamma, n_red):
+    """Squared norm and L1 beyond n = 8,192: two launches, whose trial values
+    come from f along the line.  x0 spreads over both signs with a tenth of
+    its entries zero."""
+    w = W.random_sparse(400, n, 10, seed=90 + n % 7, B=B, obj=obj, K=1)
+    rng = np.random.default_rng(n)
+    x0 = rng.uniform(-0.2, 1.0, (n, B)).astype(np.float32)
+    x0[rng.random((n, B)) < 0.1] = 0.0
+    w = w.with_params(gamma=gamma, alpha=0.9, n_red=n_red, x0=x0)
+    check_iteration(smx, w, expect_launches=2)
+
+
+def test_phase_on_the_line_ends_at_the_trial_cap(smx):
+    """Every trial of the first step is rejected: the cap ends the phase and x
+    stays, in closed form (squared norm) and by summation (L1)."""
+    for obj in (W.OBJ_SQNORM, W.OBJ_L1):
+        w = W.random_sparse(300, 8300, 10, seed=97, obj=obj, K=1).with_params(gamma=1e6, alpha=0.99, n_red=2,
+                                                                             max_trials=21)
+        st = check_iteration(smx, w, expect_launches=2)
+        assert st[0]["trials"] == 21 and st[0]["accepts"] == 0 and st[0]["cap_hits"] == 1
