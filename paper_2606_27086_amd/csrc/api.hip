@@ -845,10 +845,15 @@ PhaseKind phase_kind(const smx_problem *p)
 }
 
 // Trial launches of the chain: each reduction step needs at most two (a short
-// batch, then every remaining trial up to the cap).
+// batch, then every remaining trial up to the cap), and a phase gets two more
+// than its steps: most first batches succeed, a launch that finds the phase
+// over costs as much as any (~4.5 us), and after two that failed the rest
+// evaluate every trial at once (trial_width).  Four steps: six launches
+// instead of eight.
 int chain_trial_launches(const smx_problem *p)
 {
-    return (p->pp.max_trials > p->pp.first_width ? 2 : 1) * p->pp.n_red;
+    const int n = p->pp.n_red;
+    return p->pp.max_trials > p->pp.first_width ? std::min(2 * n, n + 2) : n;
 }
 
 // State-buffer flips of one perturbation phase: one per launch that moves
@@ -935,7 +940,7 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
         for (int t = 0; t < launches; ++t) {
             double *out = p->part_trial[t & 1].as<double>();
             hip_check(launch_trial(p->pp, p->x.as<float>(), gvec, p->state(cur), p->state(cur ^ 1), t == 0 ? 1 : 0,
-                                   1, prev, out, s),
+                                   launches - 1 - t, prev, out, s),
                       "trial");
             cur ^= 1;
             prev = out;

@@ -1965,19 +1965,20 @@ __device__ inline double trial_beta(const PertParams &pp, const SliceState &S, l
     return pp.adaptive ? S.beta_ad : pp.gamma * pow(pp.alpha, (double)e);
 }
 
-// Number of trials a trial launch evaluates for slice state S: a short batch
-// when a reduction step starts, all remaining ones (up to the cap) after that.
-// Trials a launch evaluates: the first batch of a reduction step is the
-// default width, widened to 1.5x the trials the previous step needed (step
-// sizes shrink along the phase, so that is usually enough); a second batch
-// takes every trial left up to the cap.  The width only decides how many
-// trials are evaluated speculatively: the accepted trial is the first
-// acceptable one in order whatever the width.
-__device__ inline int trial_width(const SliceState &S, const PertParams &pp)
+// Trials a launch evaluates for slice state S, with `after` evaluating
+// launches behind it: the first batch of a reduction step is the default
+// width, widened to 1.5x the trials the previous step needed (step sizes
+// shrink along the phase, so that is usually enough); a second batch takes
+// every trial left up to the cap.  A first batch that fails costs the step a
+// second launch: where the launches left would then not reach for one per
+// remaining step, the first batch takes every trial at once.  The width only
+// decides how many trials are evaluated speculatively: the accepted trial is
+// the first acceptable one in order whatever the width.
+__device__ inline int trial_width(const SliceState &S, const PertParams &pp, int after)
 {
     if (!S.phase) return 0;
     const int left = pp.max_trials - S.step_tried;
-    if (S.step_tried != 0) return left;
+    if (S.step_tried != 0 || after < pp.n_red - S.n_done) return left;
     int w = pp.first_width;
     const int want = S.need_last + (S.need_last >> 1);
     if (want > w) w = ((want + kFirstWidth - 1) / kFirstWidth) * kFirstWidth;
@@ -2122,11 +2123,11 @@ __device__ inline void record_decision(SliceState &S, const PertParams &pp, int 
 // accepted; reading stops at the chunk holding it.
 template <int BS>
 __device__ inline void derive_decision(SliceState &sS, const PertParams &pp, const double *__restrict__ part_prev,
-                                       long long nslots, int s, int nt, double *tot)
+                                       long long nslots, int s, int nt, double *tot, int after)
 {
     __shared__ int acc_t;
     __shared__ double acc_f;
-    const int ntr = trial_width(sS, pp);
+    const int ntr = trial_width(sS, pp, after + 1); // as the launch before this one saw it
     if (ntr == 0) return;
     if (threadIdx.x == 0) acc_t = -1;
     for (int t0 = 0; t0 < ntr; t0 += kTrialChunk) {
@@ -2149,11 +2150,13 @@ __device__ inline void derive_decision(SliceState &sS, const PertParams &pp, con
 }
 
 // Every workgroup: state of slice s at the start of this launch, in sS.
-// mode 0: the first trial launch (opens the phase from the gradient partials);
-// otherwise: the decision of the previous trial launch.
+// first: the first trial launch (opens the phase from the gradient partials);
+// otherwise the decision of the previous trial launch (`after`: evaluating
+// launches behind this one, -1 in the closing launch).
 template <int BS>
 __device__ inline void derive_state(SliceState &sS, const SliceState *__restrict__ st_in, const PertParams &pp,
-                                    int first, const double *__restrict__ part_prev, int s, int nt, double *tot)
+                                    int first, const double *__restrict__ part_prev, int s, int nt, double *tot,
+                                    int after = 0)
 {
     if (threadIdx.x == 0) sS = st_in[s];
     const long long nslots = (long long)pp.B * nt;
@@ -2163,7 +2166,7 @@ __device__ inline void derive_state(SliceState &sS, const SliceState *__restrict
         __syncthreads();
     } else {
         __syncthreads();
-        derive_decision<BS>(sS, pp, part_prev, nslots, s, nt, tot);
+        derive_decision<BS>(sS, pp, part_prev, nslots, s, nt, tot, after);
     }
 }
 
@@ -2330,7 +2333,7 @@ __global__ __launch_bounds__(kBlock) void k_eval_objective(SliceState *__restric
 __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x, const float *__restrict__ g,
                                                           const SliceState *__restrict__ st_in,
                                                           SliceState *__restrict__ st_out, PertParams pp, int first,
-                                                          int evaluate, const double *__restrict__ part_prev,
+                                                          int after, const double *__restrict__ part_prev,
                                                           double *__restrict__ part_out)
 {
     static_assert(kTile * kTile == 256, "tile of 256 pixels");
@@ -2358,10 +2361,10 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x,
             pgv = g[((long long)gi * C + gj) * B + s];
         }
     }
-    derive_state<kTrialBlock>(sS, st_in, pp, first, part_prev, s, nt, tot);
+    derive_state<kTrialBlock>(sS, st_in, pp, first, part_prev, s, nt, tot, after);
     const SliceState &S = sS; // read from LDS (a register copy of the struct spills)
     const bool apply = must_apply(S);
-    const int ntr = (evaluate && !apply) ? trial_width(S, pp) : 0;
+    const int ntr = apply ? 0 : trial_width(S, pp, after);
     if (!apply && ntr == 0) {
         publish_state(S, st_out, s, false);
         return;
@@ -2402,6 +2405,19 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x,
         v00[h] = -(double)tg[li][lj] * inv_gn;
         v10[h] = -(double)tg[li + 1][lj] * inv_gn;
         v01[h] = -(double)tg[li][lj + 1] * inv_gn;
+    }
+    if (ntr <= W) { // short batches: one trial a wave, so that no wave holds four trials' chains
+        if (wid < ntr) {
+            const double cf = coef[wid];
+            double acc[1] = {0.0};
+#pragma unroll
+            for (int h = 0; h < 4; ++h)
+                if (has[h])
+                    acc[0] += tv_tau(x00[h] + cf * v00[h], x10[h] + cf * v10[h], x01[h] + cf * v01[h], pp.tv_eps2);
+            wave_sum<1>(acc);
+            if (lane == 0) part_out[(long long)wid * nslots + slot] = acc[0];
+        }
+        return;
     }
     for (int t0 = wid * 4; t0 < ntr; t0 += W * 4) {
         double acc[4];
@@ -2555,13 +2571,13 @@ __device__ inline void slice_totals(const double *__restrict__ part, int nt, int
 // slice (thread s < B holds slice s's), then each slice either evaluates its
 // next batch of trials or gets its accepted step, whichever its state asks
 // for.  The totals a decision needs are read one trial first (usually
-// accepted), the rest of the batch only while a slice is undecided.  With
-// evaluate = 0 this is the phase's closing launch.
+// accepted), the rest of the batch only while a slice is undecided.  `after`:
+// evaluating launches behind this one; -1 in the phase's closing launch.
 template <int B, int BS>
 __global__ __launch_bounds__(BS) void k_trial_tv_mm(float *__restrict__ x, const float *__restrict__ g,
                                                     const SliceState *__restrict__ st_in,
                                                     SliceState *__restrict__ st_out, PertParams pp, int th,
-                                                    int first, int evaluate, const double *__restrict__ part_prev,
+                                                    int first, int after, const double *__restrict__ part_prev,
                                                     double *__restrict__ part_out)
 {
     constexpr int PX = BS / B, T = 8; // trials evaluated at a time
@@ -2592,7 +2608,7 @@ __global__ __launch_bounds__(BS) void k_trial_tv_mm(float *__restrict__ x, const
         double acc_f = 0.0;
         bool need = false;
         if (threadIdx.x < B) {
-            ntr = trial_width(sS[threadIdx.x], pp);
+            ntr = trial_width(sS[threadIdx.x], pp, after + 1); // as the launch before this one saw it
             need = ntr > 0;
         }
         for (int t0 = 0, nv = 1; __syncthreads_or(need); t0 += nv, nv = T) { // ends: t0 passes every ntr
@@ -2612,7 +2628,7 @@ __global__ __launch_bounds__(BS) void k_trial_tv_mm(float *__restrict__ x, const
     }
     const SliceState &S = sS[s];
     const bool apply = must_apply(S);
-    const int ntr = (evaluate && !apply) ? trial_width(S, pp) : 0;
+    const int ntr = (after >= 0 && !apply) ? trial_width(S, pp, after) : 0;
     if (threadIdx.x < B && ntr > 0) atomicMax(&most, ntr);
     if (blockIdx.x == 0 && threadIdx.x < B) {
         SliceState o = S;
@@ -2680,7 +2696,7 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_close(float *__restrict__
     __shared__ SliceState sS;
     const int s = blockIdx.y, B = pp.B;
     const bool lin = pp.obj == OBJ_LINEAR;
-    derive_state<kTrialBlock>(sS, st_in, pp, 0, part_prev, s, nt, tot);
+    derive_state<kTrialBlock>(sS, st_in, pp, 0, part_prev, s, nt, tot, -1);
     const SliceState &S = sS;
     const bool apply = must_apply(S);
     if (apply) {
@@ -2845,7 +2861,7 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
 __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, const float *__restrict__ g,
                                                        const SliceState *__restrict__ st_in,
                                                        SliceState *__restrict__ st_out, PertParams pp, int first,
-                                                       int evaluate, const double *__restrict__ part_prev,
+                                                       int after, const double *__restrict__ part_prev,
                                                        double *__restrict__ part_out)
 {
     __shared__ double coef[1024];
@@ -2854,7 +2870,7 @@ __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, co
     __shared__ SliceState sS;
     const int s = blockIdx.y, B = pp.B, nt = gridDim.x;
     const bool lin = pp.obj == OBJ_LINEAR;
-    derive_state<kBlock>(sS, st_in, pp, first, part_prev, s, nt, tot);
+    derive_state<kBlock>(sS, st_in, pp, first, part_prev, s, nt, tot, after);
     const SliceState &S = sS; // read from LDS (a register copy of the struct spills)
     if (must_apply(S)) {
         const double inv_gn = 1.0 / S.gn;
@@ -2866,7 +2882,7 @@ __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, co
         return;
     }
     publish_state(S, st_out, s, false);
-    const int ntr = evaluate ? trial_width(S, pp) : 0;
+    const int ntr = trial_width(S, pp, after);
     if (ntr == 0) return;
     const long long nslots = (long long)B * nt, slot = (long long)s * nt + blockIdx.x;
     const double inv_gn = 1.0 / S.gn;
@@ -4679,17 +4695,17 @@ hipError_t launch_trial_linear(const PertParams &pp, float *x, const float *c, c
 }
 
 static hipError_t trial_tv_mm(const PertParams &pp, float *x, const float *g, const SliceState *st_in,
-                              SliceState *st_out, int first, int evaluate, const double *part_prev, double *part_out,
+                              SliceState *st_out, int first, int after, const double *part_prev, double *part_out,
                               hipStream_t s)
 {
 #define SMX_TTV(NB)                                                                                                    \
     case NB:                                                                                                           \
         if (tv_small_block(pp))                                                                                        \
             hipLaunchKernelGGL((k_trial_tv_mm<NB, kTrialSmallBlock>), dim3(phase_grid(pp)), dim3(kTrialSmallBlock), 0, \
-                               s, x, g, st_in, st_out, pp, tv_tile_rows(pp), first, evaluate, part_prev, part_out);    \
+                               s, x, g, st_in, st_out, pp, tv_tile_rows(pp), first, after, part_prev, part_out);       \
         else                                                                                                           \
             hipLaunchKernelGGL((k_trial_tv_mm<NB, kTrialBlock>), dim3(phase_grid(pp)), dim3(kTrialBlock), 0, s, x, g,  \
-                               st_in, st_out, pp, tv_tile_rows(pp), first, evaluate, part_prev, part_out);             \
+                               st_in, st_out, pp, tv_tile_rows(pp), first, after, part_prev, part_out);                \
         break
     switch (pp.B) {
         SMX_TTV(2);
@@ -4707,7 +4723,7 @@ hipError_t launch_trial_close(const PertParams &pp, float *x, const float *g, co
                               SliceState *st_out, const double *part_prev, hipStream_t s)
 {
     if (pp.max_trials < 1 || pp.max_trials > 1024) return hipErrorInvalidValue;
-    if (pp.obj == OBJ_TV2D && pp.B > 1) return trial_tv_mm(pp, x, g, st_in, st_out, 0, 0, part_prev, nullptr, s);
+    if (pp.obj == OBJ_TV2D && pp.B > 1) return trial_tv_mm(pp, x, g, st_in, st_out, 0, -1, part_prev, nullptr, s);
     const long long g_need = (pp.n + kTrialBlock - 1) / kTrialBlock; // one unknown a thread, at most 256 workgroups
     const unsigned grid = (unsigned)std::max(1LL, std::min(g_need, 256LL));
     hipLaunchKernelGGL(k_trial_close, dim3(grid, pp.B), dim3(kTrialBlock), 0, s, x, g, st_in, st_out, pp,
@@ -4716,17 +4732,17 @@ hipError_t launch_trial_close(const PertParams &pp, float *x, const float *g, co
 }
 
 hipError_t launch_trial(const PertParams &pp, float *x, const float *g, const SliceState *st_in, SliceState *st_out,
-                        int first, int evaluate, const double *part_prev, double *part_out, hipStream_t s)
+                        int first, int after, const double *part_prev, double *part_out, hipStream_t s)
 {
-    if (pp.max_trials < 1 || pp.max_trials > 1024) return hipErrorInvalidValue;
+    if (pp.max_trials < 1 || pp.max_trials > 1024 || after < 0) return hipErrorInvalidValue;
     if (pp.obj == OBJ_TV2D && pp.B > 1)
-        return trial_tv_mm(pp, x, g, st_in, st_out, first, evaluate, part_prev, part_out, s);
+        return trial_tv_mm(pp, x, g, st_in, st_out, first, after, part_prev, part_out, s);
     const dim3 grid(phase_grid(pp), pp.B), block(kBlock);
     if (pp.obj == OBJ_TV2D)
-        hipLaunchKernelGGL(k_trial_tv, grid, dim3(kTrialBlock), 0, s, x, g, st_in, st_out, pp, first, evaluate,
+        hipLaunchKernelGGL(k_trial_tv, grid, dim3(kTrialBlock), 0, s, x, g, st_in, st_out, pp, first, after,
                            part_prev, part_out);
     else
-        hipLaunchKernelGGL(k_trial_flat, grid, block, 0, s, x, g, st_in, st_out, pp, first, evaluate, part_prev,
+        hipLaunchKernelGGL(k_trial_flat, grid, block, 0, s, x, g, st_in, st_out, pp, first, after, part_prev,
                            part_out);
     return hipGetLastError();
 }

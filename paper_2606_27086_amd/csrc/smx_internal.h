@@ -394,9 +394,10 @@ hipError_t launch_eval_objective(SliceState *st, const PertParams &pp, const dou
                                  hipStream_t s);
 // One trial launch: derives the state (first: the phase opening from the
 // gradient partials; otherwise the previous launch's decision from its trial
-// partials), then with `evaluate` the next batch of trial steps (partials
+// partials), then the next batch of trial steps (partials
 // [max_trials][B*tiles] into part_out), or adds the accepted step to x once
-// the phase is over.  The derived state goes to st_out.
+// the phase is over.  The derived state goes to st_out.  after: trial launches
+// behind this one in the phase.
 // the closing launch of a phase (one workgroup per slice)
 // Whether the perturbation phase runs as one launch (flat objectives, short
 // vectors), and that launch: state st_in in, st_out out.
@@ -413,6 +414,6 @@ hipError_t launch_trial_linear(const PertParams &pp, float *x, const float *c, c
 hipError_t launch_trial_close(const PertParams &pp, float *x, const float *g, const SliceState *st_in,
                               SliceState *st_out, const double *part_prev, hipStream_t s);
 hipError_t launch_trial(const PertParams &pp, float *x, const float *g, const SliceState *st_in, SliceState *st_out,
-                        int first, int evaluate, const double *part_prev, double *part_out, hipStream_t s);
+                        int first, int after, const double *part_prev, double *part_out, hipStream_t s);
 
 } // namespace smx

@@ -82,3 +82,12 @@ def test_phase_on_the_line_ends_at_the_trial_cap(smx):
                                                                              max_trials=21)
         st = check_iteration(smx, w, expect_launches=2)
         assert st[0]["trials"] == 21 and st[0]["accepts"] == 0 and st[0]["cap_hits"] == 1
+
+
+@pytest.mark.parametrize("B,gamma,alpha", [(1, 200.0, 0.93), (1, 3.0, 0.97), (2, 200.0, 0.93), (1, 1e6, 0.99)])
+def test_tv_phase_with_failing_batches(smx, B, gamma, alpha):
+    """Four reduction steps in six trial launches: first batches of 8 that fail
+    (each costs its step a second launch, and after two the rest take every
+    trial at once), batches that succeed, and a step that meets the cap."""
+    w = W.random_sparse(900, 33 * 21, 6, seed=93, B=B, obj=W.OBJ_TV2D, K=1, tv_shape=(33, 21))
+    check_iteration(smx, w.with_params(gamma=gamma, alpha=alpha, n_red=4), expect_launches=8)
