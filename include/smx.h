@@ -487,8 +487,9 @@ int smx_set_fused(smx_problem *p, int32_t mode);
  *     device (one for a short first batch of each reduction step, one for the
  *     rest up to the trial cap), a closing launch;
  *   SMX_PHASE_ONE_LAUNCH: the whole phase in one workgroup per slice, x and
- *     the direction in its LDS, trials in batches of 8 (squared norm, L1 and
- *     linear objectives, n <= 20,000);
+ *     the direction in its LDS, each trial's value from f along the line
+ *     x + t v where that is known in closed form, else summed in batches of 8
+ *     (squared norm, L1 and linear objectives, n <= 20,000);
  *   SMX_PHASE_CLOSED_FORM (linear objective f = c^T x): the direction
  *     launch (f(x^k), ||c||), then one launch in which every workgroup takes
  *     each trial's value from f(x + t v) = f(x) - t ||c|| (v = -c/||c||), so

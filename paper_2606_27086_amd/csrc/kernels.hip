@@ -2710,6 +2710,56 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_close(float *__restrict__
     publish_state(S, st_out, s, apply);
 }
 
+// Trials of a flat objective valued along the line x + t v, v = -g/||g||,
+// where f is known from the direction's sums (f0 = f(x), gsq = ||g||^2):
+//   f = c^T x       f0 - t ||g||,
+//   f = ||x||^2     (1 - 2t/||g||)^2 f0,
+//   f = ||x||_1     f0 - t gsq/||g|| while t/||g|| <= least, the least nonzero
+//                   |x_j| (no entry changes sign).
+// Wave 0 (all 64 lanes) calls it: lane l values the l-th next trial, the first
+// acceptable one in order is recorded, and so on until the phase is over (0
+// is returned) or a trial's value is not known (the trials the caller has to
+// sum before calling again).  The power law's steps are formed once per 64
+// trials.  Ends: a round accepts a trial, rejects at least one, or returns.
+template <int OBJ>
+__device__ inline int line_trials(SliceState &sS, const PertParams &pp, double f0, double gsq, double least, int most)
+{
+    const int l = threadIdx.x & 63;
+    long long base = 0; // beta holds the steps of trials base .. base + 63
+    double beta = 0.0;
+    bool formed = false;
+    while (sS.phase) {
+        if (!formed || sS.ell - base >= 64) {
+            base = sS.ell;
+            beta = trial_beta(pp, sS, base + l);
+            formed = true;
+        }
+        const int off = (int)(sS.ell - base), left = pp.max_trials - sS.step_tried, nb = min(left, 64 - off);
+        const double t = sS.s_acc + __shfl(beta, (off + l) & 63, 64), gn = sS.gn;
+        double ft;
+        bool known = true;
+        if constexpr (OBJ == OBJ_LINEAR) {
+            ft = f0 - t * gn;
+        } else if constexpr (OBJ == OBJ_SQNORM) {
+            const double a = 1.0 - 2.0 * t / gn;
+            ft = f0 * a * a;
+        } else {
+            known = t <= least * gn;
+            ft = f0 - t * (gsq / gn);
+        }
+        const unsigned long long ok = __ballot(l < nb && known && ft <= sS.f_cur), un = __ballot(l < nb && !known);
+        const int a = ok ? __ffsll(ok) - 1 : 64, u = un ? __ffsll(un) - 1 : 64;
+        if (u < a) return min(most, left);
+        const double fa = __shfl(ft, a & 63, 64);
+        __threadfence_block(); // every lane has read the state ...
+        __builtin_amdgcn_wave_barrier();
+        if (l == 0) record_decision(sS, pp, nb, a < 64 ? a : -1, fa);
+        __threadfence_block(); // ... and reads it anew
+        __builtin_amdgcn_wave_barrier();
+    }
+    return 0;
+}
+
 // The phase of the linear objective f(x) = c^T x from its direction partials
 // (sum c_j^2 and sum c_j x_j per workgroup of the launch that left them).  On
 // v = -c/||c|| the objective at a trial point is known in closed form,
@@ -2723,15 +2773,7 @@ __device__ inline bool linear_phase(SliceState &sS, const SliceState *__restrict
                                    SliceState *__restrict__ st_out)
 {
     derive_state<BS>(sS, st_in, pp, 1, part, s, nt, tot);
-    if (threadIdx.x == 0) {
-        SliceState &S = sS;
-        const double f = S.f_cur; // f(x^k)
-        while (S.phase) { // one trial a round: bounded by n_red acceptances or the trial cap
-            const double t = S.s_acc + trial_beta(pp, S, S.ell);
-            const double ft = f - t * S.gn;
-            record_decision(S, pp, 1, ft <= S.f_cur ? 0 : -1, ft);
-        }
-    }
+    if (threadIdx.x < 64) (void)line_trials<OBJ_LINEAR>(sS, pp, tot[1], tot[0], 0.0, 0);
     __syncthreads();
     const bool apply = must_apply(sS);
     publish_state(sS, st_out, s, apply);
@@ -2757,16 +2799,14 @@ __global__ __launch_bounds__(kBlock) void k_trial_linear(float *__restrict__ x, 
 
 // The phase of the squared norm or the L1 norm in one launch after the
 // direction launch (k_phase_flat with part_min, which also left a copy xc of
-// x).  Every trial point lies on the line x + t v, v = -g/||g||, where f is
-// known from what the direction launch summed: (1 - 2t/||g||)^2 ||x||^2 for
-// ||x||^2, and f(x) - t ||g||^2/||g|| for ||x||_1 while t/||g|| reaches no
-// nonzero entry's magnitude (part_min).  Beyond that ||x||_1 is summed over
-// xc, trials in batches as in k_phase_small, by every workgroup alike.  So
-// each workgroup takes the same decisions in the same order, adds the
-// accepted step to its own part of x, reading xc (another workgroup may have
-// moved its part of x already), and workgroup 0 publishes the state.  The
-// chain this replaces took one or two launches a reduction step: on n =
-// 16,384 with four steps ten launches, 75 us, against 16 us for these two.
+// x): the trials valued along the line (line_trials); where ||x||_1 is not
+// known there it is summed over xc, trials in batches as in k_phase_small,
+// by every workgroup alike.  So each workgroup takes the same decisions in
+// the same order, adds the accepted step to its own part of x, reading xc
+// (another workgroup may have moved its part of x already), and workgroup 0
+// publishes the state.  The chain this replaces took up to two launches a
+// reduction step: on n = 16,384 with four steps ten launches, 80 us, against
+// 14.5 us for these two.
 template <int OBJ>
 __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ x, const float *__restrict__ xc,
                                                             const SliceState *__restrict__ st_in,
@@ -2789,29 +2829,10 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
     }
     derive_state<BS>(sS, st_in, pp, 1, part, s, nt, tot);
     const double gsq = tot[0], f0 = tot[1];
-    while (sS.phase) { // sS changes only in thread 0, between barriers; a round accepts or rejects a trial
-        const int left = pp.max_trials - sS.step_tried;
-        if (threadIdx.x < 64) { // wave 0: the next trials' values, one a lane
-            const int nb = min(left, 64), l = threadIdx.x;
-            double ft = 0.0;
-            bool known = true;
-            if (l < nb) {
-                const double t = sS.s_acc + trial_beta(pp, sS, sS.ell + l);
-                if constexpr (OBJ == OBJ_SQNORM) {
-                    const double a = 1.0 - 2.0 * t / sS.gn;
-                    ft = f0 * a * a;
-                } else {
-                    known = t <= least * sS.gn;
-                    ft = f0 - t * (gsq / sS.gn);
-                }
-            }
-            const unsigned long long ok = __ballot(l < nb && known && ft <= sS.f_cur), un = __ballot(!known);
-            const int a = ok ? __ffsll(ok) - 1 : 64, u = un ? __ffsll(un) - 1 : 64;
-            const double fa = __shfl(ft, a & 63, 64);
-            if (l == 0) {
-                summed = u < a ? min(T, left) : 0;
-                if (!summed) record_decision(sS, pp, nb, a < 64 ? a : -1, fa);
-            }
+    while (sS.phase) { // sS changes only in wave 0, between barriers
+        if (threadIdx.x < 64) {
+            const int ns = line_trials<OBJ>(sS, pp, f0, gsq, least, T);
+            if (threadIdx.x == 0) summed = ns;
         }
         __syncthreads();
         const int ntr = summed;
@@ -2916,98 +2937,108 @@ __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, co
 // The whole perturbation phase of a flat objective in one launch, for short
 // vectors (n <= kSmallPhaseMaxN): one workgroup per slice copies its entries
 // of x and of the direction into LDS (float32, 8n bytes), forms ||g||^2 and
-// f(x^k), opens the phase, evaluates every reduction step's trials in
-// batches of kSmallTrials (the first acceptable trial in order is taken, as
-// in the launch-per-batch form: the batching only decides how many trials
-// are evaluated speculatively), and adds the accepted step to x.  The same
-// arithmetic per entry as k_phase_flat / k_trial_flat; only the order of the
-// float64 sums differs.  One workgroup is a latency chain, so every thread
-// issues all of its loads of x (and c) before using any.  Reads state
-// st_in[s], writes st_out[s].
-template <int OBJ>
+// f(x^k), opens the phase, values the trials along the line (line_trials;
+// L1 trials past a change of sign are summed from LDS, in batches of
+// kSmallTrials), and adds the accepted step to x.  One workgroup is a latency
+// chain, so every thread issues all of its U loads of x (and c) before using
+// any.  Reads state st_in[s], writes st_out[s].
+template <int OBJ, int U>
 __global__ __launch_bounds__(kSmallPhaseBlock) void k_phase_small(float *__restrict__ x,
                                                                   const float *__restrict__ lin_c,
                                                                   const SliceState *__restrict__ st_in,
                                                                   SliceState *__restrict__ st_out, PertParams pp)
 {
-    constexpr int BS = kSmallPhaseBlock, T = kSmallTrials, U = (kSmallPhaseMaxN + BS - 1) / BS;
+    constexpr int BS = kSmallPhaseBlock, T = kSmallTrials;
     extern __shared__ __align__(16) unsigned char phase_lds[];
     __shared__ double lds[(BS / 64) * T];
     __shared__ double coef[T];
+    __shared__ double open[3]; // sum g^2, f(x^k), least nonzero |x_j|
     __shared__ SliceState sS;
+    __shared__ int summed;
     const int s = blockIdx.y, B = pp.B, n = (int)pp.n;
     float *xs = reinterpret_cast<float *>(phase_lds);
     float *gs = xs + n;
     if (threadIdx.x == 0) sS = st_in[s];
-    __syncthreads();
-    double v[2] = {0.0, 0.0}; // sum g^2, f(x^k)
-    if (sS.live) {
-        for (int j0 = threadIdx.x; j0 < n; j0 += U * BS) {
-            float xf[U], cf[U];
+    double v[2] = {0.0, 0.0}, least = INFINITY; // sum g^2, f(x^k)
+    for (int j0 = threadIdx.x; j0 < n; j0 += U * BS) {
+        float xf[U], cf[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int j = min(j0 + u * BS, n - 1);
-                xf[u] = x[(long long)j * B + s];
-                if constexpr (OBJ == OBJ_LINEAR) cf[u] = lin_c[j];
-            }
+        for (int u = 0; u < U; ++u) {
+            const int j = min(j0 + u * BS, n - 1);
+            xf[u] = x[(long long)j * B + s];
+            if constexpr (OBJ == OBJ_LINEAR) cf[u] = lin_c[j];
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int j = j0 + u * BS;
-                if (j >= n) break;
-                const double xj = (double)xf[u];
-                float gf;
-                if constexpr (OBJ == OBJ_SQNORM) {
-                    v[1] += xj * xj;
-                    gf = (float)(2.0 * xj);
-                } else if constexpr (OBJ == OBJ_L1) { // subgradient sign(x), 0 at 0
-                    v[1] += fabs(xj);
-                    gf = xj > 0.0 ? 1.f : (xj < 0.0 ? -1.f : 0.f);
-                } else {
-                    gf = cf[u];
-                    v[1] += (double)gf * xj;
-                }
-                v[0] += (double)gf * (double)gf;
-                xs[j] = xf[u];
-                gs[j] = gf;
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * BS;
+            if (j >= n) break;
+            const double xj = (double)xf[u];
+            float gf;
+            if constexpr (OBJ == OBJ_SQNORM) {
+                v[1] += xj * xj;
+                gf = (float)(2.0 * xj);
+            } else if constexpr (OBJ == OBJ_L1) { // subgradient sign(x), 0 at 0
+                v[1] += fabs(xj);
+                gf = xj > 0.0 ? 1.f : (xj < 0.0 ? -1.f : 0.f);
+                if (gf != 0.f) least = fmin(least, fabs(xj));
+            } else {
+                gf = cf[u];
+                v[1] += (double)gf * xj;
             }
+            v[0] += (double)gf * (double)gf;
+            xs[j] = xf[u];
+            gs[j] = gf;
         }
     }
-    block_sum<2, BS>(v, lds); // its barriers also publish xs and gs
-    if (threadIdx.x == 0) open_phase_state(sS, pp, v[0], v[1]);
-    __syncthreads();
-    while (sS.phase) { // sS changes only in thread 0, between barriers
-        const int ntr = min(T, pp.max_trials - sS.step_tried);
-        if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + trial_beta(pp, sS, sS.ell + threadIdx.x);
+    if constexpr (OBJ == OBJ_L1) {
+        for (int off = 32; off > 0; off >>= 1) least = fmin(least, __shfl_xor(least, off, 64));
+        if ((threadIdx.x & 63) == 0) lds[threadIdx.x >> 6] = least;
         __syncthreads();
-        const double inv_gn = 1.0 / sS.gn;
-        double acc[T], cw[T];
-#pragma unroll
-        for (int w = 0; w < T; ++w) {
-            acc[w] = 0.0;
-            cw[w] = w < ntr ? coef[w] : 0.0;
+        if (threadIdx.x == 0)
+            for (int w = 1; w < BS / 64; ++w) least = fmin(least, lds[w]);
+        __syncthreads();
+    }
+    block_sum<2, BS>(v, lds); // its barriers also publish xs and gs
+    if (threadIdx.x == 0) {
+        open_phase_state(sS, pp, v[0], v[1]);
+        open[0] = v[0];
+        open[1] = v[1];
+        open[2] = least;
+    }
+    __syncthreads();
+    while (sS.phase) { // sS changes only in wave 0, between barriers
+        if (threadIdx.x < 64) {
+            const int ns = line_trials<OBJ>(sS, pp, open[1], open[0], open[2], T);
+            if (threadIdx.x == 0) summed = ns;
         }
-#pragma unroll 4
-        for (int j = threadIdx.x; j < n; j += BS) {
-            const double xj = (double)xs[j], gj = (double)gs[j], vj = -gj * inv_gn;
+        __syncthreads();
+        const int ntr = summed;
+        if (ntr > 0) { // L1 only
+            if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + trial_beta(pp, sS, sS.ell + threadIdx.x);
+            __syncthreads();
+            const double inv_gn = 1.0 / sS.gn;
+            double acc[T], cw[T];
 #pragma unroll
             for (int w = 0; w < T; ++w) {
-                if (w < ntr) {
-                    const double z = xj + cw[w] * vj;
-                    if constexpr (OBJ == OBJ_LINEAR) acc[w] += gj * z;
-                    else if constexpr (OBJ == OBJ_L1) acc[w] += fabs(z);
-                    else acc[w] += z * z;
-                }
+                acc[w] = 0.0;
+                cw[w] = w < ntr ? coef[w] : 0.0;
             }
-        }
-        block_sum<T, BS>(acc, lds);
-        if (threadIdx.x == 0) {
-            int t = -1;
-            for (int w = 0; w < ntr; ++w)
-                if (acc[w] <= sS.f_cur) {
-                    t = w;
-                    break;
-                }
-            record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0);
+#pragma unroll 4
+            for (int j = threadIdx.x; j < n; j += BS) {
+                const double xj = (double)xs[j], vj = -(double)gs[j] * inv_gn;
+#pragma unroll
+                for (int w = 0; w < T; ++w) acc[w] += fabs(xj + cw[w] * vj);
+            }
+            block_sum<T, BS>(acc, lds);
+            if (threadIdx.x == 0) {
+                int t = -1;
+                for (int w = 0; w < ntr; ++w)
+                    if (acc[w] <= sS.f_cur) {
+                        t = w;
+                        break;
+                    }
+                record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0);
+            }
         }
         __syncthreads();
     }
@@ -4656,16 +4687,36 @@ bool phase_in_one_launch(const PertParams &pp)
 
 static size_t phase_small_lds(const PertParams &pp) { return 2 * sizeof(float) * size_t(pp.n); }
 
+// Loads a thread keeps in flight, the least of 2, 8 and 20 that takes x in one
+// round (20: kSmallPhaseMaxN).
+template <typename F>
+static hipError_t phase_small_dispatch(int obj, int64_t n, F &&go)
+{
+    const int u = n <= 2 * kSmallPhaseBlock ? 2 : (n <= 8 * kSmallPhaseBlock ? 8 : 20);
+#define SMX_PSM(O)                                                                                                     \
+    (u == 2 ? go(k_phase_small<O, 2>) : (u == 8 ? go(k_phase_small<O, 8>) : go(k_phase_small<O, 20>)))
+    switch (obj) {
+    case OBJ_SQNORM: return SMX_PSM(OBJ_SQNORM);
+    case OBJ_L1: return SMX_PSM(OBJ_L1);
+    case OBJ_LINEAR: return SMX_PSM(OBJ_LINEAR);
+    default: return hipErrorInvalidValue;
+    }
+#undef SMX_PSM
+}
+static_assert(20 * kSmallPhaseBlock >= kSmallPhaseMaxN, "one round of loads");
+
 hipError_t prepare_phase_small()
 {
     // the largest size any problem asks for: the attribute is the kernel's, not a problem's
     const int bytes = (int)(2 * sizeof(float) * kSmallPhaseMaxN);
-    for (const void *k : {reinterpret_cast<const void *>(k_phase_small<OBJ_SQNORM>),
-                          reinterpret_cast<const void *>(k_phase_small<OBJ_L1>),
-                          reinterpret_cast<const void *>(k_phase_small<OBJ_LINEAR>)}) {
-        const hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e != hipSuccess) return e;
-    }
+    for (int obj : {OBJ_SQNORM, OBJ_L1, OBJ_LINEAR})
+        for (int64_t n : {1, 8 * kSmallPhaseBlock, kSmallPhaseMaxN}) {
+            const hipError_t e = phase_small_dispatch(obj, n, [&](auto kern) {
+                return hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+            });
+            if (e != hipSuccess) return e;
+        }
     return hipSuccess;
 }
 
@@ -4673,15 +4724,11 @@ hipError_t launch_phase_small(const PertParams &pp, float *x, const float *lin_c
                               SliceState *st_out, hipStream_t s)
 {
     if (!phase_in_one_launch(pp) || pp.max_trials < 1 || pp.max_trials > 1024 || pp.B < 1) return hipErrorInvalidValue;
-    const dim3 grid(1, pp.B), block(kSmallPhaseBlock);
-    const size_t lds = phase_small_lds(pp);
-    if (pp.obj == OBJ_SQNORM)
-        hipLaunchKernelGGL(k_phase_small<OBJ_SQNORM>, grid, block, lds, s, x, lin_c, st_in, st_out, pp);
-    else if (pp.obj == OBJ_L1)
-        hipLaunchKernelGGL(k_phase_small<OBJ_L1>, grid, block, lds, s, x, lin_c, st_in, st_out, pp);
-    else
-        hipLaunchKernelGGL(k_phase_small<OBJ_LINEAR>, grid, block, lds, s, x, lin_c, st_in, st_out, pp);
-    return hipGetLastError();
+    return phase_small_dispatch(pp.obj, pp.n, [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(1, pp.B), dim3(kSmallPhaseBlock), phase_small_lds(pp), s, x, lin_c, st_in, st_out,
+                           pp);
+        return hipGetLastError();
+    });
 }
 
 hipError_t launch_trial_linear(const PertParams &pp, float *x, const float *c, const SliceState *st_in,
