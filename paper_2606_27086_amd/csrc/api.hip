@@ -320,10 +320,19 @@ struct smx_problem {
     bool tiles_ok = false; // pass 2 may use the operator's image-tile layout (a tile's rows x B fit in LDS)
     bool stop_var = false; // the variance stopping rule: x at each iteration's start, norms after it
     DBuf xprev, part_var;
-    // dose-volume constraints: their rows' values, keys, per-constraint
-    // histograms and selection state, and the band kernel's partials
+    // dose-volume constraints: their rows' values, per-round histograms and
+    // selection states, and the last round's counts per workgroup
     DvcTable dvc{};
-    DBuf dvc_dose, dvc_key, dvc_hist, dvc_sel, dvc_part;
+    DBuf dvc_dose, dvc_tie, dvc_hist, dvc_sel;
+    DvcScratch dvc_scratch() const
+    {
+        DvcScratch W;
+        W.sel = dvc_sel.as<DvcSel>();
+        W.hist = dvc_hist.as<unsigned>();
+        W.tie = dvc_tie.as<uint16_t>();
+        W.ncand = reinterpret_cast<unsigned *>(W.tie + size_t(kDvcTieBins) * dvc.nblk * B);
+        return W;
+    }
     RowW row_weights(int vk) const
     {
         const float *D = (vk == VK_F32) ? D32.as<float>() : D16.as<float>();
@@ -340,9 +349,8 @@ struct smx_problem {
     void enqueue_dvc(int vk, double *partials, int nparts1, int which, int query, hipStream_t s)
     {
         const RowW rw = row_weights(vk);
-        hip_check(launch_dvc(dvc, dvc_dose.as<double>(), dvc_key.as<unsigned long long>(), dvc_hist.as<unsigned>(),
-                             dvc_sel.as<DvcSel>(), rw.D, rw.S, c.as<float>(), dvc_part.as<double>(), partials,
-                             nparts1, state(which), B, query, s),
+        hip_check(launch_dvc(dvc, dvc_dose.as<double>(), dvc_scratch(), rw.D, rw.S, c.as<float>(), partials, nparts1,
+                             state(which), B, query, s),
                   "dose-volume constraints");
     }
     ColStep col_step(bool defer) const
@@ -368,7 +376,7 @@ struct smx_problem {
                               &part_pass, &part_query, &part_phase, &part_trial[0], &part_trial[1], &h_prox, &h_fs,
                               &h_fe, &h_tr, &h_ac, &ypart, &part_lin, &S32, &S16, &ybuf, &ybuf32, &part_y, &part_q,
                               &ypanel,
-                              &xprev, &part_var, &dvc_dose, &dvc_key, &dvc_hist, &dvc_sel, &dvc_part})
+                              &xprev, &part_var, &dvc_dose, &dvc_tie, &dvc_hist, &dvc_sel})
             t += b->bytes;
         return t;
     }
@@ -1245,6 +1253,15 @@ bool lds_passes_available(int B) { return B == 1 && fused_lds_limit() >= sizeof(
 // Row panels of the column copy an operator with m rows holds.
 int64_t panel_count(int64_t m) { return m > kLdsPassFloats ? (m + kLdsPassFloats - 1) / kLdsPassFloats : 0; }
 
+// Device bytes of the dose-volume kernels' last-round counts (16-bit, and one
+// 32-bit count a workgroup after them), histograms and selection states.
+size_t dvc_tie_bytes(const DvcTable &dt, int B)
+{
+    return (sizeof(uint16_t) * size_t(kDvcTieBins) + sizeof(unsigned)) * size_t(dt.nblk) * B;
+}
+size_t dvc_hist_bytes(const DvcTable &dt, int B) { return sizeof(unsigned) * size_t(kDvcBins) * kDvcRounds * dt.n * B; }
+size_t dvc_sel_bytes(const DvcTable &dt, int B) { return sizeof(DvcSel) * size_t(kDvcRounds - 1) * dt.n * B; }
+
 // Device bytes of every buffer create_problem allocates for an operator with
 // m rows, n columns, float32 values (has_f32) and/or the reduced-precision
 // kind lp, and the descriptor d (whose fields the sizes depend on are
@@ -1281,10 +1298,9 @@ size_t problem_plan_bytes(int64_t m, int64_t n, bool has_f32, int lp, const smx_
     }
     if (dt.n > 0) {
         add(8 * size_t(dt.span) * B);
-        add(8 * size_t(dt.span) * B);
-        add(sizeof(unsigned) * size_t(kDvcBins) * dt.n * B);
-        add(sizeof(DvcSel) * dt.n * B);
-        add(8 * size_t(dt.nblk) * B);
+        add(dvc_tie_bytes(dt, d->B));
+        add(dvc_hist_bytes(dt, d->B));
+        add(dvc_sel_bytes(dt, d->B));
     }
     FusedCfg fc;
     size_t lds = 0;
@@ -1553,13 +1569,11 @@ int create_problem(smx_operator *op, const smx_problem_desc *d, hipStream_t s, s
     p->dvc = dt;
     if (dt.n > 0) {
         p->dvc_dose.alloc(sizeof(double) * size_t(dt.span) * B, "dose-volume rows");
-        p->dvc_key.alloc(sizeof(unsigned long long) * size_t(dt.span) * B, "dose-volume keys");
-        p->dvc_hist.alloc(sizeof(unsigned) * size_t(kDvcBins) * dt.n * B, "dose-volume histograms");
-        hip_check(hipMemsetAsync(p->dvc_hist.p, 0, sizeof(unsigned) * size_t(kDvcBins) * dt.n * B, s),
-                  "dose-volume histograms");
-        p->dvc_sel.alloc(sizeof(DvcSel) * dt.n * B, "dose-volume selection");
-        hip_check(hipMemsetAsync(p->dvc_sel.p, 0, sizeof(DvcSel) * dt.n * B, s), "dose-volume selection");
-        p->dvc_part.alloc(sizeof(double) * size_t(dt.nblk) * B, "dose-volume partials");
+        p->dvc_tie.alloc(dvc_tie_bytes(dt, B), "dose-volume counts");
+        p->dvc_hist.alloc(dvc_hist_bytes(dt, B), "dose-volume histograms");
+        hip_check(hipMemsetAsync(p->dvc_hist.p, 0, dvc_hist_bytes(dt, B), s), "dose-volume histograms");
+        p->dvc_sel.alloc(dvc_sel_bytes(dt, B), "dose-volume selection");
+        hip_check(hipMemsetAsync(p->dvc_sel.p, 0, dvc_sel_bytes(dt, B), s), "dose-volume selection");
     }
     setup_fused(p.get());
     if (lds_passes_available(B)) { // the LDS-staged pass 1

@@ -4323,10 +4323,18 @@ hipError_t launch_step_apply(int64_t n, int B, const double *y, float *x, const 
 // (MIN); as bands, the k highest rows get (-inf, inf) / [d, inf) and the
 // others (-inf, d] / (-inf, inf).  Rows rank by the float32-rounded value,
 // equal values by row.  Pass 1 stores the rows' values; a radix select over
-// 64-bit keys (value bits, then the complement of the row's position) finds
-// the k-th highest key; the band kernel then forms c_i and the proximity
-// terms, and a one-workgroup kernel per slice adds their sum to pass 1's
-// partial 0.  Histogram counts are integers, so their atomic sums are exact.
+// their order-preserving 32-bit patterns (11, 11 and 10 bits, a launch each)
+// finds the k-th highest value, and the band kernel forms c_i and the
+// proximity terms; where only some of the rows with exactly that value rank
+// high, it counts them in row order.  A round's histogram is made by all the
+// constraint's workgroups (integer counts, so their atomic sums are exact) and
+// its digit is found by every workgroup of the next launch alike, from the
+// same 2,048 counts, while its rows' values are on their way.  Four launches,
+// each a latency chain of about six microseconds; with a launch for every
+// histogram, digit and sum these were fourteen, 68 us against 29 us on 33k
+// rows in three constraints.  (Four launches whose last workgroup, by a
+// ticket, took the digit and the sum: 36 us, the ticket's and the counts'
+// round trips across the XCDs costing what the saved launches did.)
 // ---------------------------------------------------------------------------
 
 __device__ inline int dvc_group(const DvcTable &T, int blk)
@@ -4336,203 +4344,240 @@ __device__ inline int dvc_group(const DvcTable &T, int blk)
     return g;
 }
 
-__device__ inline int dvc_shift(int round) { return round < kDvcRounds - 1 ? 53 - 11 * round : 0; }
-__device__ inline int dvc_bits(int round) { return round < kDvcRounds - 1 ? 11 : 9; }
+__device__ inline int dvc_shift(int round) { return round == 0 ? 21 : (round == 1 ? 10 : 0); }
+__device__ inline int dvc_bits(int round) { return round < kDvcRounds - 1 ? 11 : 10; }
 
-// Order-preserving key of a value rounded to float32 (higher value, higher
-// key; -0 counts as +0) with the row's position i in its block.
-__device__ inline unsigned long long dvc_key(double r, long long i)
+// Order-preserving pattern of a value rounded to float32 (higher value,
+// higher pattern; -0 counts as +0).
+__device__ inline unsigned dvc_order(double r)
 {
     float f = (float)r;
     if (f == 0.0f) f = 0.0f;
     const unsigned u = __float_as_uint(f);
-    const unsigned o = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-    return ((unsigned long long)o << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)i);
+    return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
 __device__ inline bool dvc_slice_runs(const SliceState *st, int s, int query) { return query || st[s].live != 0; }
 
-// One histogram round: the digit of every candidate key of each constraint
-// (round 0: every row, whose key it also stores; later rounds: the keys that
-// share the digits fixed so far) into hist[(g * B + s) * kDvcBins + digit].
-__global__ __launch_bounds__(kBlock) void k_dvc_hist(DvcTable T, int round, const double *__restrict__ dose,
-                                                     unsigned long long *__restrict__ key, unsigned *__restrict__ hist,
-                                                     const DvcSel *__restrict__ sel,
-                                                     const SliceState *__restrict__ st, int B, int query)
+// Selection state of constraint g and slice s after the first `rounds` rounds
+// (none: only whether there is anything to select), the same in every
+// workgroup: the state the first rounds - 1 left, and the digit of the last
+// one's histogram that holds the k-th highest value, from the highest digit
+// down.  The selection ends once every row of that digit ranks high (mode 2),
+// or after the last round, where a digit is one value, of whose rows the
+// first krem rank high (mode 4).  Every thread calls it.
+__device__ inline DvcSel dvc_state(const DvcTable &T, const DvcScratch &W, int rounds, int g, int s, int B)
+{
+    __shared__ long long wsum[kDvcBlock / 64];
+    __shared__ DvcSel found;
+    const long long N = T.end[g] - T.begin[g], k = T.k[g];
+    DvcSel S;
+    S.krem = k;
+    S.value = 0u;
+    S.mode = k <= 0 ? 1 : (k >= N ? 3 : 0);
+    if (S.mode != 0 || rounds == 0) return S;
+    const int gs = g * B + s, ngs = T.n * B, r = rounds - 1;
+    constexpr int PER = kDvcBins / kDvcBlock;
+    static_assert(PER == 2, "one 8-byte load a thread");
+    const uint2 h2 = reinterpret_cast<const uint2 *>(W.hist + ((size_t)r * ngs + gs) * kDvcBins)[threadIdx.x];
+    if (r > 0) S = W.sel[(size_t)(r - 1) * ngs + gs];
+    if (S.mode != 0) return S; // the same in every thread
+    const unsigned cnt[PER] = {h2.x, h2.y};
+    long long tsum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) tsum += cnt[j];
+    // incl: counts of bins >= threadIdx.x * PER
+    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    long long incl = tsum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const long long v = __shfl_down(incl, off, 64);
+        if (lane + off < 64) incl += v;
+    }
+    if (lane == 0) wsum[wid] = incl;
+    __syncthreads();
+#pragma unroll
+    for (int w = 1; w < kDvcBlock / 64; ++w)
+        if (w > wid) incl += wsum[w];
+    const long long excl = incl - tsum;
+    if (excl < S.krem && S.krem <= incl) { // one thread: 0 < krem <= the rows counted
+        long long above = excl, kr = 0;
+        int dig = 0;
+        unsigned c_dig = 0;
+#pragma unroll
+        for (int j = PER - 1; j >= 0; --j) {
+            if (c_dig == 0 && above + (long long)cnt[j] >= S.krem) {
+                dig = threadIdx.x * PER + j;
+                kr = S.krem - above;
+                c_dig = cnt[j];
+            }
+            above += cnt[j];
+        }
+        const unsigned v = (S.value << dvc_bits(r)) | (unsigned)dig;
+        found.krem = kr;
+        const bool all = (long long)c_dig == kr;
+        found.mode = all ? 2 : (r == kDvcRounds - 1 ? 4 : 0);
+        found.value = all ? v << dvc_shift(r) : v;
+    }
+    __syncthreads();
+    return found;
+}
+
+// Clears round r's histogram of (g, s), by the constraint's first workgroup: in
+// a launch after the one that read it and before the one that fills it again.
+__device__ inline void dvc_clear(const DvcTable &T, const DvcScratch &W, int r, int g, int s, int B)
+{
+    if ((int)blockIdx.x != T.blk_begin[g]) return;
+    unsigned *H = W.hist + ((size_t)r * T.n * B + (g * B + s)) * kDvcBins;
+    for (int b = threadIdx.x; b < kDvcBins; b += kDvcBlock) H[b] = 0u;
+}
+
+// One round of the selection: the digits of the rows that share the digits
+// fixed so far into the round's histogram.  The last round also leaves each
+// workgroup's own counts (tie, ncand), from which the band kernel tells a
+// row's place among the rows of that value.
+__global__ __launch_bounds__(kDvcBlock) void k_dvc_select(DvcTable T, int round, const double *__restrict__ dose,
+                                                       DvcScratch W, const SliceState *__restrict__ st, int B,
+                                                       int query)
 {
     __shared__ unsigned h[kDvcBins];
+    __shared__ unsigned cand;
     const int s = blockIdx.y;
     if (!dvc_slice_runs(st, s, query)) return;
     const int g = dvc_group(T, blockIdx.x);
-    const DvcSel S = sel[g * B + s];
-    if (round > 0 && S.mode != 0) return;
-    for (int b = threadIdx.x; b < kDvcBins; b += kBlock) h[b] = 0u;
-    __syncthreads();
     const long long N = T.end[g] - T.begin[g];
     const long long i0 = (long long)(blockIdx.x - T.blk_begin[g]) * kDvcChunk;
     const long long i1 = i0 + kDvcChunk < N ? i0 + kDvcChunk : N;
-    const int shift = dvc_shift(round);
-    const unsigned mask = (1u << dvc_bits(round)) - 1u;
-    const int pshift = shift + dvc_bits(round); // the digits above this round's
-    for (long long i = i0 + threadIdx.x; i < i1; i += kBlock) {
-        const long long at = (T.begin[g] + i - T.lo) * B + s;
-        unsigned long long kk;
-        if (round == 0) {
-            kk = dvc_key(dose[at], i);
-            key[at] = kk;
-        } else {
-            kk = key[at];
-            if ((kk >> pshift) != S.prefix) continue;
-        }
-        atomicAdd(&h[(unsigned)(kk >> shift) & mask], 1u);
+    constexpr int PERT = kDvcChunk / kDvcBlock;
+    double d[PERT];
+#pragma unroll
+    for (int q = 0; q < PERT; ++q) { // past the end the last row again, not counted
+        const long long i = i0 + q * kDvcBlock + threadIdx.x;
+        d[q] = dose[(T.begin[g] + (i < i1 ? i : i1 - 1) - T.lo) * B + s];
     }
+    for (int b = threadIdx.x; b < kDvcBins; b += kDvcBlock) h[b] = 0u;
+    if (threadIdx.x == 0) cand = 0u;
+    const DvcSel S = dvc_state(T, W, round, g, s, B);
+    if (round > 0 && (int)blockIdx.x == T.blk_begin[g] && threadIdx.x == 0)
+        W.sel[(size_t)(round - 1) * T.n * B + (g * B + s)] = S; // read by the next launch
+    // the histogram read two launches ago (round 0: by the last band kernel)
+    if (round != 1) dvc_clear(T, W, round == 0 ? kDvcRounds - 1 : 0, g, s, B);
+    if (S.mode != 0) return; // the same in every thread
     __syncthreads();
-    unsigned *H = hist + (size_t)(g * B + s) * kDvcBins;
-    for (int b = threadIdx.x; b < kDvcBins; b += kBlock)
-        if (h[b]) atomicAdd(&H[b], h[b]);
-}
-
-// One workgroup per constraint and slice: the digit that holds the k-th
-// highest key among the candidates, from the highest digit down; then the
-// histogram is cleared for the next round.  The selection ends once every
-// candidate of that digit ranks high (or after the last round, where a digit
-// holds one key).
-__global__ __launch_bounds__(kBlock) void k_dvc_pick(DvcTable T, int round, unsigned *__restrict__ hist,
-                                                     DvcSel *__restrict__ sel, const SliceState *__restrict__ st,
-                                                     int B, int query)
-{
-    __shared__ unsigned long long suf[kBlock];
-    const int g = blockIdx.x, s = blockIdx.y;
-    if (!dvc_slice_runs(st, s, query)) return;
-    DvcSel *S = sel + (g * B + s);
-    if (round > 0 && S->mode != 0) return;
-    unsigned *H = hist + (size_t)(g * B + s) * kDvcBins;
-    constexpr int PER = kDvcBins / kBlock;
-    const long long N = T.end[g] - T.begin[g], k = T.k[g];
-    unsigned cnt[PER];
-    unsigned long long tsum = 0;
+    const int shift = dvc_shift(round), bits = dvc_bits(round), pshift = shift + bits;
+    const unsigned mask = (1u << bits) - 1u;
+    unsigned mine = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        cnt[j] = H[threadIdx.x * PER + j];
-        tsum += cnt[j];
-    }
-    if (round == 0 && (k <= 0 || k >= N)) {
-        if (threadIdx.x == 0) {
-            S->mode = k <= 0 ? 1 : 3;
-            S->prefix = 0;
-            S->thr = 0;
-            S->krem = 0;
-        }
-    } else {
-        const long long krem = round == 0 ? k : S->krem;
-        const unsigned long long prefix = round == 0 ? 0ull : S->prefix;
-        // suffix sums over threads: suf[t] = counts of bins >= t * PER
-        suf[threadIdx.x] = tsum;
-        __syncthreads();
-        for (int off = 1; off < kBlock; off <<= 1) {
-            const unsigned long long v = suf[threadIdx.x] + (threadIdx.x + off < kBlock ? suf[threadIdx.x + off] : 0ull);
-            __syncthreads();
-            suf[threadIdx.x] = v;
-            __syncthreads();
-        }
-        const long long incl = (long long)suf[threadIdx.x], excl = incl - (long long)tsum;
-        if (excl < krem && krem <= incl) {
-            long long above = excl;
-            int dig = threadIdx.x * PER;
-            long long kr = 0;
-            unsigned c_dig = 0;
-            for (int j = PER - 1; j >= 0; --j) {
-                if (above + (long long)cnt[j] >= krem) {
-                    dig = threadIdx.x * PER + j;
-                    kr = krem - above;
-                    c_dig = cnt[j];
-                    break;
-                }
-                above += cnt[j];
-            }
-            const unsigned long long np = (prefix << dvc_bits(round)) | (unsigned long long)dig;
-            if ((long long)c_dig == kr || round == kDvcRounds - 1) {
-                S->mode = 2;
-                S->thr = np << dvc_shift(round);
-            } else {
-                S->mode = 0;
-                S->prefix = np;
-                S->krem = kr;
-            }
+    for (int q = 0; q < PERT; ++q) {
+        const unsigned o = dvc_order(d[q]);
+        if (i0 + q * kDvcBlock + threadIdx.x < i1 && (round == 0 || (o >> pshift) == S.value)) {
+            atomicAdd(&h[(o >> shift) & mask], 1u);
+            ++mine;
         }
     }
-#pragma unroll
-    for (int j = 0; j < PER; ++j) H[threadIdx.x * PER + j] = 0u;
+    if (mine) atomicAdd(&cand, mine);
+    __syncthreads();
+    unsigned *H = W.hist + ((size_t)round * T.n * B + (g * B + s)) * kDvcBins;
+    if (cand)
+        for (int b = threadIdx.x; b < kDvcBins; b += kDvcBlock)
+            if (h[b]) atomicAdd(&H[b], h[b]);
+    if (round == kDvcRounds - 1) {
+        const size_t wg = (size_t)s * T.nblk + blockIdx.x;
+        if (threadIdx.x == 0) W.ncand[wg] = cand;
+        if (cand) // at most kDvcChunk a bin: 16 bits
+            for (int b = threadIdx.x; b < kDvcTieBins; b += kDvcBlock) W.tie[wg * kDvcTieBins + b] = (uint16_t)h[b];
+    }
 }
 
-// The bands the selection gives, c_i = S_i t_i and per-workgroup partials of
-// the proximity terms D_i t_i^2 in epart[s * nblk + workgroup].
-__global__ __launch_bounds__(kBlock) void k_dvc_bands(DvcTable T, const double *__restrict__ dose,
-                                                      const unsigned long long *__restrict__ key,
-                                                      const DvcSel *__restrict__ sel, const float *__restrict__ D,
-                                                      const float *__restrict__ Sw, float *__restrict__ c,
-                                                      double *__restrict__ epart, const SliceState *__restrict__ st,
-                                                      int B, int query)
+// The bands the selection gives, c_i = S_i t_i and the proximity terms D_i
+// t_i^2, which a workgroup adds to pass 1's partial of its own number (the
+// grid has at most nparts1 workgroups a slice; each takes chunks of rows
+// blockIdx.x, blockIdx.x + gridDim.x, ...).
+__global__ __launch_bounds__(kDvcBlock) void k_dvc_bands(DvcTable T, const double *__restrict__ dose, DvcScratch W,
+                                                      const float *__restrict__ D, const float *__restrict__ Sw,
+                                                      float *__restrict__ c, double *__restrict__ part1, int nparts1,
+                                                      const SliceState *__restrict__ st, int B, int query)
 {
-    __shared__ double lds[4];
+    __shared__ double lds[kDvcBlock / 64];
+    __shared__ unsigned wsum[kDvcBlock / 64];
+    __shared__ double total;
     const int s = blockIdx.y;
     if (!dvc_slice_runs(st, s, query)) return;
-    const int g = dvc_group(T, blockIdx.x);
-    const DvcSel S = sel[g * B + s];
-    const long long N = T.end[g] - T.begin[g];
-    const long long i0 = (long long)(blockIdx.x - T.blk_begin[g]) * kDvcChunk;
-    const long long i1 = i0 + kDvcChunk < N ? i0 + kDvcChunk : N;
-    const double dref = T.dose[g];
-    const bool upper_kind = T.sense[g] == 0;
+    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
     double pacc[1] = {0.0};
-    for (long long i = i0 + threadIdx.x; i < i1; i += kBlock) {
-        const long long row = T.begin[g] + i;
-        const long long at = (row - T.lo) * B + s;
-        const double r = dose[at];
-        const bool high = S.mode == 3 || (S.mode == 2 && key[at] >= S.thr);
-        double lo = -INFINITY, up = INFINITY;
-        if (upper_kind) {
-            if (!high) up = dref;
-        } else if (high) {
-            lo = dref;
+    for (int blk = blockIdx.x; blk < T.nblk; blk += gridDim.x) {
+        const int g = dvc_group(T, blk);
+        const long long N = T.end[g] - T.begin[g];
+        const long long i0 = (long long)(blk - T.blk_begin[g]) * kDvcChunk;
+        const long long i1 = i0 + kDvcChunk < N ? i0 + kDvcChunk : N;
+        const double dref = T.dose[g];
+        const bool upper_kind = T.sense[g] == 0;
+        const DvcSel S = dvc_state(T, W, kDvcRounds, g, s, B);
+        if (blk == T.blk_begin[g]) { // the second round's histogram, read by the launch before this one
+            unsigned *H = W.hist + ((size_t)1 * T.n * B + (g * B + s)) * kDvcBins;
+            for (int b = threadIdx.x; b < kDvcBins; b += kDvcBlock) H[b] = 0u;
         }
-        const double t = fmin(fmax(r, lo), up) - r;
-        c[row * B + s] = (float)((double)Sw[row] * t);
-        pacc[0] += (double)D[row] * t * t;
+        long long before = 0; // mode 4: rows of the value in the constraint's chunks before this one
+        if (S.mode == 4) {
+            double n0[1] = {0.0};
+            const unsigned dig = S.value & (kDvcTieBins - 1);
+            for (int b = T.blk_begin[g] + (int)threadIdx.x; b < blk; b += kDvcBlock) {
+                const size_t wg = (size_t)s * T.nblk + b;
+                if (W.ncand[wg]) n0[0] += (double)W.tie[wg * kDvcTieBins + dig];
+            }
+            block_sum<1, kDvcBlock>(n0, lds);
+            if (threadIdx.x == 0) total = n0[0];
+            __syncthreads();
+            before = (long long)total;
+        }
+        for (long long r0 = i0; r0 < i1; r0 += kDvcBlock) { // the same rounds in every thread
+            const long long i = r0 + threadIdx.x;
+            const bool in = i < i1;
+            const long long row = T.begin[g] + (in ? i : i1 - 1);
+            const double r = dose[(row - T.lo) * B + s];
+            const unsigned o = dvc_order(r);
+            bool high = S.mode == 3 || (S.mode == 2 && o >= S.value) || (S.mode == 4 && o > S.value);
+            if (S.mode == 4) { // the same in every thread
+                const bool tie = in && o == S.value;
+                const unsigned long long m = __ballot(tie);
+                if (lane == 0) wsum[wid] = (unsigned)__popcll(m);
+                __syncthreads();
+                long long place = before + __popcll(m & ((1ull << lane) - 1ull));
+                for (int w = 0; w < kDvcBlock / 64; ++w) {
+                    if (w < wid) place += wsum[w];
+                    before += wsum[w];
+                }
+                if (tie && place < S.krem) high = true;
+                __syncthreads();
+            }
+            if (!in) continue;
+            double lo = -INFINITY, up = INFINITY;
+            if (upper_kind) {
+                if (!high) up = dref;
+            } else if (high) {
+                lo = dref;
+            }
+            const double t = fmin(fmax(r, lo), up) - r;
+            c[row * B + s] = (float)((double)Sw[row] * t);
+            pacc[0] += (double)D[row] * t * t;
+        }
+        __syncthreads(); // before the next chunk's use of the shared state
     }
-    block_sum<1>(pacc, lds);
-    if (threadIdx.x == 0) epart[(long long)s * T.nblk + blockIdx.x] = pacc[0];
+    block_sum<1, kDvcBlock>(pacc, lds);
+    if (threadIdx.x == 0) part1[(long long)s * nparts1 + blockIdx.x] += pacc[0];
 }
 
-// Adds the band kernel's partials of slice s (summed in workgroup order) to
-// pass 1's partial 0 of that slice.
-__global__ __launch_bounds__(kBlock) void k_dvc_fold(const double *__restrict__ epart, int nblk,
-                                                     double *__restrict__ part1, int nparts1,
-                                                     const SliceState *__restrict__ st, int query)
+hipError_t launch_dvc(const DvcTable &T, const double *dose, const DvcScratch &W, const float *D, const float *S,
+                      float *c, double *part1, int nparts1, const SliceState *st, int B, int query, hipStream_t s)
 {
-    __shared__ double lds[4];
-    const int s = blockIdx.x;
-    if (!dvc_slice_runs(st, s, query)) return;
-    double tot[1];
-    sum_slots<1>(epart, (long long)s * nblk, nblk, tot, lds);
-    if (threadIdx.x == 0) part1[(long long)s * nparts1] += tot[0];
-}
-
-hipError_t launch_dvc(const DvcTable &T, const double *dose, unsigned long long *key, unsigned *hist, DvcSel *sel,
-                      const float *D, const float *S, float *c, double *epart, double *part1, int nparts1,
-                      const SliceState *st, int B, int query, hipStream_t s)
-{
-    if (T.n < 1 || T.n > kMaxDvc || T.nblk < 1 || B < 1 || B > 32) return hipErrorInvalidValue;
-    const dim3 blk(kBlock), gall(T.nblk, B), gsel(T.n, B);
-    for (int r = 0; r < kDvcRounds; ++r) {
-        hipLaunchKernelGGL(k_dvc_hist, gall, blk, 0, s, T, r, dose, key, hist, sel, st, B, query);
-        hipLaunchKernelGGL(k_dvc_pick, gsel, blk, 0, s, T, r, hist, sel, st, B, query);
-    }
-    hipLaunchKernelGGL(k_dvc_bands, gall, blk, 0, s, T, dose, key, sel, D, S, c, epart, st, B, query);
-    hipLaunchKernelGGL(k_dvc_fold, dim3(B), blk, 0, s, epart, T.nblk, part1, nparts1, st, query);
+    if (T.n < 1 || T.n > kMaxDvc || T.nblk < 1 || B < 1 || B > 32 || nparts1 < 1) return hipErrorInvalidValue;
+    const dim3 blk(kDvcBlock);
+    for (int r = 0; r < kDvcRounds; ++r)
+        hipLaunchKernelGGL(k_dvc_select, dim3(T.nblk, B), blk, 0, s, T, r, dose, W, st, B, query);
+    hipLaunchKernelGGL(k_dvc_bands, dim3(std::min(T.nblk, nparts1), B), blk, 0, s, T, dose, W, D, S, c, part1, nparts1,
+                       st, B, query);
     return hipGetLastError();
 }
-
 
 hipError_t launch_query_prox(SliceState *st, int B, const double *partials, int nparts, double *out, hipStream_t s)
 {

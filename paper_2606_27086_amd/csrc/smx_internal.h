@@ -156,16 +156,15 @@ struct RowW {
 };
 
 // ---- dose-volume constraints ----
-// A constraint's rows are ranked by a 64-bit key: the order-preserving bits of
-// the float32-rounded value in the high half, the complement of the row's
-// position in its block in the low half (equal values rank by row), so keys are
-// unique.  The k-th highest key is found by a radix select over 11-bit digits
-// (at most six rounds: shifts 53, 42, 31, 20, 9 and a last 9-bit digit), one
-// launch per round; a round's last workgroup of a constraint picks the digit.
+// A constraint's rows are ranked by their value rounded to float32, equal
+// values by row.  The k-th highest value is found by a radix select over the
+// digits (11, 11 and 10 bits) of its order-preserving pattern.
 constexpr int kMaxDvc = 16;
 constexpr int kDvcChunk = 2048; // rows per workgroup of the selection and band kernels
+constexpr int kDvcBlock = 1024; // threads of those workgroups (two rows and two bins each: latency chains)
 constexpr int kDvcBins = 2048;  // 11-bit digits
-constexpr int kDvcRounds = 6;
+constexpr int kDvcRounds = 3;
+constexpr int kDvcTieBins = 1024; // the last round's 10-bit digits
 
 struct DvcTable {
     int n;                       // constraints
@@ -180,11 +179,22 @@ struct DvcTable {
 
 // Selection state of one constraint and slice.
 struct DvcSel {
-    unsigned long long prefix; // digits fixed so far
-    unsigned long long thr;    // mode 2: rows with key >= thr rank high
-    long long krem;            // rank still to find below the prefix
-    int mode;                  // 0: searching, 1: no row ranks high, 2: threshold, 3: every row ranks high
-    int pad;
+    long long krem; // rank still to find below the digits fixed (mode 4: rows of the value that rank high)
+    unsigned value; // mode 0: the digits fixed; modes 2, 4: the pattern below
+    int mode;       // 0: searching, 1: no row ranks high, 2: rows at or above value do, 3: every row does,
+                    // 4: rows above value do and the first krem rows at it
+};
+
+// Device scratch of the dose-volume kernels: per round the selection states
+// [(kDvcRounds - 1) * n * B] and the histograms [kDvcRounds * n * B *
+// kDvcBins] (zero when their round starts), and the last round's counts per
+// workgroup (tie [nblk * B * kDvcTieBins], filled where ncand [nblk * B] is
+// not 0).
+struct DvcScratch {
+    DvcSel *sel;
+    unsigned *hist;
+    uint16_t *tie;
+    unsigned *ncand;
 };
 
 // Column step of pass 2 (and of the fused pass's apply kernel):
@@ -365,17 +375,14 @@ size_t fused_lds_limit();
 // raise the dynamic-LDS attribute of the fused kernel of this shape (call
 // before its first launch, outside stream capture)
 hipError_t prepare_fused(const FusedCfg &cfg, int vk, int64_t n);
-// query: proximity from pass 1's partials into out[B]
 // dose-volume constraints after pass 1 (which stored the rows' values in
-// dose): the radix-select rounds (keys, per-constraint histograms in hist,
-// which must start zeroed and are left zeroed, selection state in sel), then
-// the bands of the rows, their c = S t, and their proximity terms (partials in
-// epart, nblk * B), added in a fixed order to pass 1's partial 0 of each slice
-// (part1 with nparts1 partials per slice).
-hipError_t launch_dvc(const DvcTable &T, const double *dose, unsigned long long *key, unsigned *hist, DvcSel *sel,
-                      const float *D, const float *S, float *c, double *epart, double *part1, int nparts1,
-                      const SliceState *st, int B, int query, hipStream_t s);
+// dose): the selection of each constraint's k-th highest value, then the bands
+// of the rows, their c = S t, and their proximity terms, added to pass 1's
+// partials (part1 with nparts1 per slice), each workgroup's to its own.
+hipError_t launch_dvc(const DvcTable &T, const double *dose, const DvcScratch &W, const float *D, const float *S,
+                      float *c, double *part1, int nparts1, const SliceState *st, int B, int query, hipStream_t s);
 
+// query: proximity from pass 1's partials into out[B]
 hipError_t launch_query_prox(SliceState *st, int B, const double *partials, int nparts, double *out, hipStream_t s);
 
 int phase_grid(const PertParams &pp);
