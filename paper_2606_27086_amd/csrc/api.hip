@@ -989,11 +989,12 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
         int nvec = p->fcfg[vk].grid;
         if (p->dvc.n > 0) { // rank the dose-volume rows, then add their c_i a_i as a second set of partials
             p->enqueue_dvc(vk, p->part_pass.as<double>(), p->fcfg[vk].grid, cur, 0, s);
+            const int sg = scatter_rows_grid(p->dvc.span, nvec);
             hip_check(launch_scatter_rows(view_for(p->op, false, fused_fmt(p, vk)), fused_fmt(p, vk), p->n, p->dvc.lo,
                                           p->dvc.lo + p->dvc.span, p->c.as<float>(), p->state(cur),
-                                          p->ypart.as<float>() + size_t(nvec) * size_t(p->n), nvec, s),
+                                          p->ypart.as<float>() + size_t(nvec) * size_t(p->n), sg, s),
                       "dose-volume rows");
-            nvec *= 2;
+            nvec += sg;
         }
         if (timed) hip_check(hipEventRecord(e[2], s), "event");
         const bool lin = lin_from_apply(p, vk);
@@ -1137,8 +1138,8 @@ int run_impl(smx_problem *p, int32_t K, uint32_t flags)
 
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
-// Launch shapes of the fused pass tried by the autotuner (same grid and
-// accumulator type as `base`): 8/16/32 lanes per row with 4 or 8 entries per
+// Launch shapes of the fused pass tried by the autotuner (accumulator type
+// and workgroups per CU as `base` has them): 8/16/32 lanes per row with 4 or 8 entries per
 // load re-reading the entries for the scatter, and the register-cached shapes
 // (256 entries of a row in registers); zl_only: only the shapes with z in LDS
 // (the ones that store dose-volume rows' values).
@@ -1172,6 +1173,18 @@ std::vector<FusedCfg> fused_candidates(const FusedCfg &base, int64_t n, bool zl_
                 t.cap = fused_zl_cap(lpr, vec); // the row's first entries kept in registers
                 out.push_back(t);
             }
+    // where two workgroups fit a CU, also at one: half the partial vectors to
+    // write and to sum (2 x 4n bytes a workgroup), against the second
+    // workgroup's rows in flight
+    const size_t shapes = out.size();
+    for (size_t i = 0; i < shapes; ++i) {
+        out[i].grid = base.most;
+        if (base.cus < base.most) {
+            FusedCfg t = out[i];
+            t.grid = base.cus;
+            out.push_back(t);
+        }
+    }
     return out;
 }
 
@@ -1241,7 +1254,8 @@ bool fused_plan(int64_t n, int B, int n_dvc, FusedCfg &c, size_t &lds_bytes)
     c = FusedCfg{};
     c.vec = 4;
     c.cap = 0;
-    c.grid = std::max(1, std::min(cus * per_cu, kMaxPassGrid));
+    c.grid = c.most = std::max(1, std::min(cus * per_cu, kMaxPassGrid));
+    c.cus = std::max(1, std::min(cus, kMaxPassGrid));
     c.acc64 = acc64;
     return true;
 }
@@ -1354,7 +1368,7 @@ void setup_fused(smx_problem *p)
         if (!present) continue;
         bool ok = true;
         for (const FusedCfg &t : fused_candidates(c, p->n, dvc))
-            if (prepare_fused(t, fused_fmt(p, vk), p->n) != hipSuccess) ok = false;
+            if (t.grid == c.most && prepare_fused(t, fused_fmt(p, vk), p->n) != hipSuccess) ok = false;
         if (dvc && prepare_scatter_rows(fused_fmt(p, vk), p->n) != hipSuccess) ok = false;
         (void)hipGetLastError();
         p->fused_ok[vk] = p->fused[vk] = ok;
@@ -1823,9 +1837,21 @@ int autotune_impl(smx_problem *p, int reps)
             p->cfg2[vk] = bestc2;
             // the fused single pass, timed with its apply kernel, against the two passes
             if (p->fused_ok[vk] && p->fused_mode == 1) {
+                hip_check(hipMemcpyAsync(xs.p, p->x.p, sizeof(float) * n, hipMemcpyDeviceToDevice, s), "tuning copy");
+                if (p->dvc.n > 0) { // c of the dose-volume rows at the tuned point, from the values the last pass 1 kept
+                    hip_check(launch_pass1(bestc, view_for(p->op, false, p->fmt1[vk]), p->op->csr.blocks(), p->fmt1[vk],
+                                           xs.as<float>(), p->lower.as<float>(), p->upper.as<float>(), rw,
+                                           p->c.as<float>(), st0, p->B, 1, p->part_query.as<double>(), s),
+                              "tuning pass 1");
+                    p->enqueue_dvc(vk, p->part_query.as<double>(), bestc.grid, p->cur, 1, s);
+                }
                 double bestf = 1e30;
                 FusedCfg bestfc = p->fcfg[vk];
                 for (const FusedCfg &c : fused_candidates(p->fcfg[vk], n, p->dvc.n > 0)) {
+                    // every candidate from the problem's own iterate: the steps timed
+                    // before move it, and with it the rows outside their bands, whose
+                    // scatter is part of the pass
+                    hip_check(hipMemcpyAsync(xs.p, p->x.p, sizeof(float) * n, hipMemcpyDeviceToDevice, s), "tuning copy");
                     auto launch = [&]() {
                         hip_check(launch_fused(c, view_for(p->op, false, fused_fmt(p, vk)), fused_fmt(p, vk), n, xs.as<float>(),
                                                p->lower.as<float>(), p->upper.as<float>(), rw, st0,
@@ -1833,12 +1859,13 @@ int autotune_impl(smx_problem *p, int reps)
                                   "tuning fused pass");
                         int nvec = c.grid;
                         if (p->dvc.n > 0) { // the dose-volume rows' own scatter
+                            const int sg = scatter_rows_grid(p->dvc.span, c.grid);
                             hip_check(launch_scatter_rows(view_for(p->op, false, fused_fmt(p, vk)), fused_fmt(p, vk),
                                                           n, p->dvc.lo, p->dvc.lo + p->dvc.span, p->c.as<float>(),
                                                           st0, p->ypart.as<float>() + size_t(c.grid) * size_t(n),
-                                                          c.grid, s),
+                                                          sg, s),
                                       "tuning dose-volume rows");
-                            nvec *= 2;
+                            nvec += sg;
                         }
                         hip_check(launch_fused_apply(c, n, p->ypart.p, nvec, xs.as<float>(), cstep, st0, st1,
                                                      p->part_query.as<double>(), none, s),

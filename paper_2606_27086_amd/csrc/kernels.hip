@@ -4071,10 +4071,15 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zlr(SpView A, int n, cons
 
 // y += sum of c_i a_i over rows [r_lo, r_hi) with c_i already set (the
 // dose-volume rows of a problem taking the fused pass, after their ranking):
-// one 1024-thread workgroup per CU adds its share of the rows (strided over
-// the grid) into an LDS copy of y and leaves it as one float32 partial
-// vector, beside the fused pass's own.
-template <int LPR, int VEC, typename VT>
+// each 1024-thread workgroup adds its share of the rows (strided over the
+// grid) into an LDS copy of y and leaves it as one float32 partial vector,
+// beside the fused pass's own.  A group has few rows, so a row is a latency
+// chain: its LPR lanes request CAP * VEC entries each (256 of the row) at
+// once, and the next row's offsets and c_i meanwhile.  (One chunk of 32
+// entries at a time, as scatter_row goes, took 36 us for 33k rows of 184
+// entries, 36 MB; 9 us so.)  As in k_fused_zlr lane l of a group holds
+// the chunk slots of lane (l + group) mod LPR.
+template <int LPR, int VEC, int CAP, typename VT>
 __global__ __launch_bounds__(kFusedBlock) void k_scatter_rows(SpView A, int n, long long r_lo, long long r_hi,
                                                               const float *__restrict__ c,
                                                               const SliceState *__restrict__ st,
@@ -4082,22 +4087,56 @@ __global__ __launch_bounds__(kFusedBlock) void k_scatter_rows(SpView A, int n, l
 {
     extern __shared__ __align__(16) unsigned char scat_lds[];
     float *y = reinterpret_cast<float *>(scat_lds);
-    constexpr int RPB = kFusedBlock / LPR;
+    constexpr int RPB = kFusedBlock / LPR, STEP = LPR * VEC;
     const int lane = threadIdx.x & (LPR - 1);
     const int grp = threadIdx.x / LPR;
+    const int slot = (lane + grp) & (LPR - 1);
     if (st[0].live == 0) return; // the same in every workgroup: the apply reads nothing then
+    const long long stride = (long long)gridDim.x * RPB;
+    long long row = r_lo + (long long)blockIdx.x * RPB + grp;
+    float ci = 0.f;
+    int beg = 0, end = 0;
+    if (row < r_hi) {
+        ci = c[row];
+        beg = A.ptr[row];
+        end = A.ptr[row + 1];
+    }
     for (int j = threadIdx.x; j < n; j += kFusedBlock) y[j] = 0.f;
     __syncthreads();
-    const long long stride = (long long)gridDim.x * RPB;
-    for (long long row = r_lo + (long long)blockIdx.x * RPB + grp; row < r_hi; row += stride) {
-        const float ci = c[row];
-        const int beg = A.ptr[row], end = A.ptr[row + 1];
-        if (ci != 0.f && end > beg)
-            scatter_row<LPR, VEC, VT, float>(A, beg, end, lane, grp, (double)ci * (double)A.vscale_inv, y);
+    for (; row < r_hi; row += stride) {
+        float nci = 0.f;
+        int nbeg = 0, nend = 0;
+        if (row + stride < r_hi) {
+            nci = c[row + stride];
+            nbeg = A.ptr[row + stride];
+            nend = A.ptr[row + stride + 1];
+        }
+        if (ci != 0.f) {
+            const double sc = (double)ci * (double)A.vscale_inv;
+            for (int p = beg; p < end; p += CAP * STEP) {
+                RowRegs<VEC, CAP> R;
+                fetch_entries<LPR, VEC, CAP, VT>(A, p, end, slot, R);
+#pragma unroll
+                for (int q = 0; q < CAP; ++q)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e)
+                        if (R.v[q][e] != 0.f) lds_add(&y[R.c[q][e]], sc * (double)R.v[q][e]);
+            }
+        }
+        ci = nci;
+        beg = nbeg;
+        end = nend;
     }
     __syncthreads();
     float *out = ypart + (long long)blockIdx.x * n;
     for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = y[j];
+}
+
+// Workgroups of that kernel: two rows a group, at most `most`.
+int scatter_rows_grid(long long rows, int most)
+{
+    constexpr int per = 2 * kFusedBlock / 16;
+    return (int)std::max(1LL, std::min((rows + per - 1) / per, (long long)most));
 }
 
 size_t fused_lds_bytes(int64_t n, int acc64) { return size_t(n) * (acc64 ? sizeof(double) : sizeof(float)); }
@@ -4264,7 +4303,7 @@ template <typename VT>
 hipError_t scatter_rows_go(int prepare, const SpView &A, int64_t n, long long r_lo, long long r_hi, const float *c,
                            const SliceState *st, float *ypart, int grid, hipStream_t s)
 {
-    auto kern = k_scatter_rows<8, 4, VT>;
+    auto kern = k_scatter_rows<16, 8, 2, VT>;
     const size_t bytes = sizeof(float) * size_t(n);
     if (prepare)
         return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,

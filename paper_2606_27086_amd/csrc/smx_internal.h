@@ -222,6 +222,8 @@ struct FusedCfg {
     int grid;  // workgroups, each with an LDS copy of y
     int acc64; // 1: float64 LDS accumulators, 0: float32
     int zl = 0; // 1: z staged in LDS beside a float32 y (k_fused_zl, k_fused_zlr; acc64 = 0)
+    int cus = 0; // workgroups at one per CU
+    int most = 0; // workgroups at as many per CU as the LDS allows (the partial vectors' room)
 };
 
 // Column layout grouped by image tiles (A^T for an operator whose unknowns
@@ -367,6 +369,7 @@ hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double
 // y partials of rows [r_lo, r_hi) whose c is set (the dose-volume rows of a
 // fused-pass problem, after their ranking): grid float32 vectors of n at ypart
 hipError_t prepare_scatter_rows(int vk, int64_t n);
+int scatter_rows_grid(long long rows, int most); // workgroups it is launched with, at most `most`
 hipError_t launch_scatter_rows(const SpView &A, int vk, int64_t n, long long r_lo, long long r_hi, const float *c,
                                const SliceState *st, float *ypart, int grid, hipStream_t s);
 // largest dynamic LDS one fused workgroup may take on the current device, after
