@@ -1138,8 +1138,8 @@ int run_impl(smx_problem *p, int32_t K, uint32_t flags)
 
 bool is_pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 
-// Launch shapes of the fused pass tried by the autotuner (accumulator type
-// and workgroups per CU as `base` has them): 8/16/32 lanes per row with 4 or 8 entries per
+// Launch shapes of the fused pass tried by the autotuner (workgroups per CU as
+// `base` has them): 8/16/32 lanes per row with 4 or 8 entries per
 // load re-reading the entries for the scatter, and the register-cached shapes
 // (256 entries of a row in registers); zl_only: only the shapes with z in LDS
 // (the ones that store dose-volume rows' values).
@@ -1154,20 +1154,23 @@ std::vector<FusedCfg> fused_candidates(const FusedCfg &base, int64_t n, bool zl_
             t.vec = vec;
             t.cap = 0;
             t.zl = 0;
+            t.out32 = 0;
+            t.acc64 = fused_lds_bytes(n, 1) <= fused_lds_limit() ? 1 : 0;
             out.push_back(t);
             if (lpr >= 16) {
                 t.cap = 256 / (lpr * vec);
                 out.push_back(t);
             }
         }
-    if (fused_zl_lds_bytes(n) <= fused_lds_limit()) // z in LDS beside a float32 y
+    if (fused_zl_lds_bytes(n, 0) <= fused_lds_limit()) // z in LDS beside y, in float64 if that fits
         for (int lpr : {8, 16, 32})
             for (int vec : {4, 8}) {
                 FusedCfg t = base;
                 t.lpr = lpr;
                 t.vec = vec;
                 t.cap = 0;
-                t.acc64 = 0;
+                t.acc64 = fused_zl_lds_bytes(n, 1) <= fused_lds_limit() ? 1 : 0;
+                t.out32 = zl_only ? 1 : 0;
                 t.zl = 1;
                 out.push_back(t);
                 t.cap = fused_zl_cap(lpr, vec); // the row's first entries kept in registers
@@ -1238,7 +1241,7 @@ bool fused_plan(int64_t n, int B, int n_dvc, FusedCfg &c, size_t &lds_bytes)
     if (B != 1) return false;
     // dose-volume rows: the shapes with z in LDS store their values for the
     // ranking, and a second kernel adds their c_i a_i once it has set them
-    if (n_dvc > 0 && fused_zl_lds_bytes(n) > fused_lds_limit()) return false;
+    if (n_dvc > 0 && fused_zl_lds_bytes(n, 0) > fused_lds_limit()) return false;
     const size_t lim = fused_lds_limit();
     int acc64 = -1;
     if (fused_lds_bytes(n, 1) <= lim) acc64 = 1;
@@ -1359,7 +1362,8 @@ void setup_fused(smx_problem *p)
     const bool dvc = p->dvc.n > 0;
     if (dvc) { // z in LDS: two sets of float32 partials fit the float64 plan's bytes
         c.zl = 1;
-        c.acc64 = 0;
+        c.acc64 = fused_zl_lds_bytes(p->n, 1) <= fused_lds_limit() ? 1 : 0;
+        c.out32 = 1;
         c.lpr = 8;
     }
     bool any = false;

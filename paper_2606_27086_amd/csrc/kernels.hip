@@ -385,6 +385,31 @@ __device__ inline void load_chunks(const SpView &A, int p, int step, const bool 
     for (int u = 0; u < U; ++u) raw[u].decode(v[u], c[u]);
 }
 
+// Exchanges a chunk's entries so that place e holds entry e ^ (l mod VEC).
+// Lanes l = 0, 1, ... hold consecutive chunks of a row, whose columns often
+// follow one another: at one place of the unrolled loops the lanes' columns
+// are then VEC apart, and their LDS words share banks (16 lanes of 8 entries:
+// 64 clocks for a wave's ds_add_f64 against 16).  Exchanged, one place covers
+// all residues.
+template <int VEC>
+__device__ inline void spread_entries(float (&v)[VEC], int (&c)[VEC], int l)
+{
+#pragma unroll
+    for (int bit = 1; bit < VEC; bit <<= 1) {
+        const bool sw = (l & bit) != 0;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+            if ((e & bit) == 0) {
+                const float va = v[e], vb = v[e | bit];
+                const int ca = c[e], cb = c[e | bit];
+                v[e] = sw ? vb : va;
+                v[e | bit] = sw ? va : vb;
+                c[e] = sw ? cb : ca;
+                c[e | bit] = sw ? ca : cb;
+            }
+    }
+}
+
 // One entry at p: its value as float and its index.
 template <typename VT>
 __device__ inline void entry1(const SpView &A, int p, float &v, int &c);
@@ -3892,25 +3917,42 @@ __device__ inline double fused_epilogue(const RowW &w, long long row, double r, 
 // z_j through the vector memory path once per stored entry, about one
 // address per CU per clock, which bounds it on long operators.  Here each
 // workgroup (one per CU, 1024 threads) first copies all of z into LDS, beside
-// a float32 copy of y (2 x 4n bytes, n up to about 20k), and runs the rows as
+// y in float64 where both fit (12n bytes, n up to about 13k) and in float32
+// otherwise (8n bytes, n up to about 20k), and runs the rows as
 // the LDS-staged pass 1 does (LPR lanes per row, four loads of VEC entries in
 // flight per lane, rows strided over the grid), gathering from LDS; a row
 // outside its band then reads its entries again (from the cache) and adds
 // c_i a_i into y with LDS atomics, each group of a wave starting at another
 // chunk so that neighbouring rows, which list the same columns in the same
-// order, touch different words at once.  y leaves as one float32 partial
-// vector per workgroup; k_fused_apply adds them in float64.
-template <int LPR, int VEC, typename VT>
+// order, touch different words at once.  y leaves as one partial vector per
+// workgroup; k_fused_apply adds them in float64.  A float64 y costs half
+// the adds' time or less: ds_add_f32 takes 192 clocks a wave whatever its
+// addresses (3 a lane), ds_add_f64 8 to 16 where they spread over the banks.
+// A workgroup's y as its partial vector, float64 or (out32, or a float32 y)
+// float32.
+template <typename AccT>
+__device__ inline void write_partial(void *ypart, int out32, int n, const AccT *y)
+{
+    if (out32 || sizeof(AccT) == sizeof(float)) {
+        float *out = static_cast<float *>(ypart) + (long long)blockIdx.x * n;
+        for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = (float)y[j];
+    } else {
+        double *out = static_cast<double *>(ypart) + (long long)blockIdx.x * n;
+        for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = (double)y[j];
+    }
+}
+
+template <int LPR, int VEC, typename VT, typename AccT>
 __global__ __launch_bounds__(kFusedBlock) void k_fused_zl(SpView A, int n, const float *__restrict__ x,
                                                           const float *__restrict__ lower,
                                                           const float *__restrict__ upper, RowW w,
                                                           const SliceState *__restrict__ st,
-                                                          double *__restrict__ partials, float *__restrict__ ypart,
-                                                          LinPhase L)
+                                                          double *__restrict__ partials, void *__restrict__ ypart,
+                                                          int out32, LinPhase L)
 {
     extern __shared__ __align__(16) unsigned char fused_lds[];
     float *zl = reinterpret_cast<float *>(fused_lds);
-    float *y = zl + ((n + 3) & ~3);
+    AccT *y = reinterpret_cast<AccT *>(zl + ((n + 3) & ~3));
     __shared__ double lds[kFusedBlock / 64];
     __shared__ double tot[kTrialChunk];
     __shared__ SliceState sS;
@@ -3920,7 +3962,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zl(SpView A, int n, const
     const int grp = threadIdx.x / LPR;
     const bool step = L.c && linear_phase<kFusedBlock>(sS, st, L.pp, L.part, 0, L.nparts, tot, L.st_out);
     const bool live = (L.c ? sS.live : st[0].live) != 0;
-    for (int j = threadIdx.x; j < n; j += kFusedBlock) y[j] = 0.f;
+    for (int j = threadIdx.x; j < n; j += kFusedBlock) y[j] = AccT(0);
     double pacc[1] = {0.0};
     if (live) {
         if (step) stage_linear_point<kFusedBlock>(reinterpret_cast<float4 *>(zl), x, L.c, n, sS.s_acc, 1.0 / sS.gn);
@@ -3946,7 +3988,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zl(SpView A, int n, const
             if (lane == 0) ct = fused_epilogue(w, row, r, lo, up, d, sw, pacc[0]);
             ct = __shfl(ct, 0, LPR);
             if (ct != 0.0 && end > beg)
-                scatter_row<LPR, VEC, VT, float>(A, beg, end, lane, grp, ct * (double)A.vscale_inv, y);
+                scatter_row<LPR, VEC, VT, AccT>(A, beg, end, lane, grp, ct * (double)A.vscale_inv, y);
             beg = nbeg;
             end = nend;
         }
@@ -3954,8 +3996,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zl(SpView A, int n, const
     block_sum<1, kFusedBlock>(pacc, lds); // its barriers also order the LDS adds before the copy-out
     if (!live) return;
     if (threadIdx.x == 0) partials[blockIdx.x] = pacc[0];
-    float *out = ypart + (long long)blockIdx.x * n;
-    for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = y[j];
+    write_partial(ypart, out32, n, y);
 }
 
 // k_fused_zl with each row's first CAP chunks (CAP * LPR * VEC entries) held
@@ -3966,17 +4007,17 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zl(SpView A, int n, const
 // LPR (fetch_entries), so neighbouring rows, which list the same columns in
 // the same order, hit different LDS addresses in one atomic instruction.
 // Entries past CAP chunks are read again as in k_fused_zl.
-template <int LPR, int VEC, int CAP, typename VT>
+template <int LPR, int VEC, int CAP, typename VT, typename AccT>
 __global__ __launch_bounds__(kFusedBlock) void k_fused_zlr(SpView A, int n, const float *__restrict__ x,
                                                            const float *__restrict__ lower,
                                                            const float *__restrict__ upper, RowW w,
                                                            const SliceState *__restrict__ st,
-                                                           double *__restrict__ partials, float *__restrict__ ypart,
-                                                           LinPhase L)
+                                                           double *__restrict__ partials, void *__restrict__ ypart,
+                                                           int out32, LinPhase L)
 {
     extern __shared__ __align__(16) unsigned char fused_lds[];
     float *zl = reinterpret_cast<float *>(fused_lds);
-    float *y = zl + ((n + 3) & ~3);
+    AccT *y = reinterpret_cast<AccT *>(zl + ((n + 3) & ~3));
     __shared__ double lds[kFusedBlock / 64];
     __shared__ double tot[kTrialChunk];
     __shared__ SliceState sS;
@@ -3987,7 +4028,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zlr(SpView A, int n, cons
     const int slot = (lane + grp) & (LPR - 1);
     const bool step = L.c && linear_phase<kFusedBlock>(sS, st, L.pp, L.part, 0, L.nparts, tot, L.st_out);
     const bool live = (L.c ? sS.live : st[0].live) != 0;
-    for (int j = threadIdx.x; j < n; j += kFusedBlock) y[j] = 0.f;
+    for (int j = threadIdx.x; j < n; j += kFusedBlock) y[j] = AccT(0);
     double pacc[1] = {0.0};
     if (live) {
         if (step) stage_linear_point<kFusedBlock>(reinterpret_cast<float4 *>(zl), x, L.c, n, sS.s_acc, 1.0 / sS.gn);
@@ -4019,7 +4060,10 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zlr(SpView A, int n, cons
             const float lo = lower[row], up = upper[row], d = w.D[row], sw = w.S[row]; // read by every lane
             RowRegs<VEC, CAP> R;
 #pragma unroll
-            for (int q = 0; q < CAP; ++q) raw[q].decode(R.v[q], R.c[q]);
+            for (int q = 0; q < CAP; ++q) {
+                raw[q].decode(R.v[q], R.c[q]);
+                if constexpr (sizeof(AccT) == sizeof(double)) spread_entries<VEC>(R.v[q], R.c[q], slot);
+            }
             double acc[2] = {0.0, 0.0};
 #pragma unroll
             for (int q = 0; q < CAP; ++q)
@@ -4065,15 +4109,14 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zlr(SpView A, int n, cons
     block_sum<1, kFusedBlock>(pacc, lds); // its barriers also order the LDS adds before the copy-out
     if (!live) return;
     if (threadIdx.x == 0) partials[blockIdx.x] = pacc[0];
-    float *out = ypart + (long long)blockIdx.x * n;
-    for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = y[j];
+    write_partial(ypart, out32, n, y);
 }
 
 // y += sum of c_i a_i over rows [r_lo, r_hi) with c_i already set (the
 // dose-volume rows of a problem taking the fused pass, after their ranking):
 // each 1024-thread workgroup adds its share of the rows (strided over the
-// grid) into an LDS copy of y and leaves it as one float32 partial vector,
-// beside the fused pass's own.  A group has few rows, so a row is a latency
+// grid) into a float64 LDS copy of y and leaves it as one float32 partial
+// vector, beside the fused pass's own.  A group has few rows, so a row is a latency
 // chain: its LPR lanes request CAP * VEC entries each (256 of the row) at
 // once, and the next row's offsets and c_i meanwhile.  (One chunk of 32
 // entries at a time, as scatter_row goes, took 36 us for 33k rows of 184
@@ -4086,7 +4129,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_scatter_rows(SpView A, int n, l
                                                               float *__restrict__ ypart)
 {
     extern __shared__ __align__(16) unsigned char scat_lds[];
-    float *y = reinterpret_cast<float *>(scat_lds);
+    double *y = reinterpret_cast<double *>(scat_lds);
     constexpr int RPB = kFusedBlock / LPR, STEP = LPR * VEC;
     const int lane = threadIdx.x & (LPR - 1);
     const int grp = threadIdx.x / LPR;
@@ -4101,7 +4144,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_scatter_rows(SpView A, int n, l
         beg = A.ptr[row];
         end = A.ptr[row + 1];
     }
-    for (int j = threadIdx.x; j < n; j += kFusedBlock) y[j] = 0.f;
+    for (int j = threadIdx.x; j < n; j += kFusedBlock) y[j] = 0.0;
     __syncthreads();
     for (; row < r_hi; row += stride) {
         float nci = 0.f;
@@ -4117,6 +4160,8 @@ __global__ __launch_bounds__(kFusedBlock) void k_scatter_rows(SpView A, int n, l
                 RowRegs<VEC, CAP> R;
                 fetch_entries<LPR, VEC, CAP, VT>(A, p, end, slot, R);
 #pragma unroll
+                for (int q = 0; q < CAP; ++q) spread_entries<VEC>(R.v[q], R.c[q], slot);
+#pragma unroll
                 for (int q = 0; q < CAP; ++q)
 #pragma unroll
                     for (int e = 0; e < VEC; ++e)
@@ -4128,8 +4173,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_scatter_rows(SpView A, int n, l
         end = nend;
     }
     __syncthreads();
-    float *out = ypart + (long long)blockIdx.x * n;
-    for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = y[j];
+    write_partial(ypart, 1, n, y);
 }
 
 // Workgroups of that kernel: two rows a group, at most `most`.
@@ -4141,7 +4185,10 @@ int scatter_rows_grid(long long rows, int most)
 
 size_t fused_lds_bytes(int64_t n, int acc64) { return size_t(n) * (acc64 ? sizeof(double) : sizeof(float)); }
 
-size_t fused_zl_lds_bytes(int64_t n) { return 2 * size_t((n + 3) & ~int64_t(3)) * sizeof(float); }
+size_t fused_zl_lds_bytes(int64_t n, int acc64)
+{
+    return size_t((n + 3) & ~int64_t(3)) * (sizeof(float) + (acc64 ? sizeof(double) : sizeof(float)));
+}
 
 int fused_apply_grid(int64_t n) { return (int)grid_for(n, 64, 4096); }
 
@@ -4169,28 +4216,26 @@ struct FusedArgs {
 
 // prepare != 0: only raise the kernel's dynamic-LDS attribute (done outside
 // any stream capture, before the first launch of this shape)
-template <int LPR, typename VT, int VEC>
+template <int LPR, typename VT, int VEC, typename AccT>
 hipError_t fused_zl_go(const FusedCfg &cfg, const FusedArgs &a, int prepare, hipStream_t s)
 {
     constexpr int CAP = fused_zl_cap(LPR, VEC);
     if (cfg.cap != 0 && cfg.cap != CAP) return hipErrorInvalidValue;
-    auto kern = cfg.cap ? k_fused_zlr<LPR, VEC, CAP, VT> : k_fused_zl<LPR, VEC, VT>;
-    const size_t bytes = fused_zl_lds_bytes(a.n);
+    auto kern = cfg.cap ? k_fused_zlr<LPR, VEC, CAP, VT, AccT> : k_fused_zl<LPR, VEC, VT, AccT>;
+    const size_t bytes = fused_zl_lds_bytes(a.n, sizeof(AccT) == sizeof(double));
     if (prepare)
         return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)bytes);
     hipLaunchKernelGGL(kern, dim3(cfg.grid), dim3(kFusedBlock), bytes, s, *a.A, (int)a.n, a.x, a.lower, a.upper, a.w,
-                       a.st, a.partials, static_cast<float *>(a.ypart), a.lp);
+                       a.st, a.partials, a.ypart, cfg.out32, a.lp);
     return hipGetLastError();
 }
 
 template <int LPR, typename VT, int VEC, typename AccT>
 hipError_t fused_go(const FusedCfg &cfg, const FusedArgs &a, int prepare, hipStream_t s)
 {
-    if (cfg.zl) {
-        if constexpr (sizeof(AccT) != sizeof(float)) return hipErrorInvalidValue; // float32 partials only
-        else return fused_zl_go<LPR, VT, VEC>(cfg, a, prepare, s);
-    }
+    if (cfg.zl) return fused_zl_go<LPR, VT, VEC, AccT>(cfg, a, prepare, s);
+    if (cfg.out32 && cfg.acc64) return hipErrorInvalidValue; // the other shapes' partials are their y's type
     if (a.lp.c) return hipErrorInvalidValue; // the linear phase rides only on the shapes with z in LDS
     auto kern = k_fused<LPR, VEC, VT, AccT>;
     if (cfg.cap > 0) {
@@ -4277,11 +4322,12 @@ hipError_t launch_fused_apply(const FusedCfg &cfg, int64_t n, const void *ypart,
                               const SliceState *st_in, SliceState *st_out, const double *part1, Hist h,
                               hipStream_t s, const float *lin_c, double *lin_part, int lin_z)
 {
+    const bool wide = cfg.acc64 && !cfg.out32;
     if (cfg.grid < 1 || cfg.grid > kMaxPassGrid || n < 1 || nvec < cfg.grid || nvec > 2 * cfg.grid ||
-        (cfg.acc64 && nvec != cfg.grid) || (lin_part && (!lin_c || cs.defer)) || (lin_z && (!lin_c || cs.defer)))
+        (wide && nvec != cfg.grid) || (lin_part && (!lin_c || cs.defer)) || (lin_z && (!lin_c || cs.defer)))
         return hipErrorInvalidValue;
     const unsigned grid = (unsigned)fused_apply_grid(n);
-    if (cfg.acc64)
+    if (wide)
         hipLaunchKernelGGL(k_fused_apply<double>, dim3(grid), dim3(kApplyBlock), 0, s, static_cast<const double *>(ypart),
                            nvec, (int)n, x, cs, st_in, st_out, part1, cfg.grid, h, lin_c, lin_part, lin_z);
     else
@@ -4304,7 +4350,7 @@ hipError_t scatter_rows_go(int prepare, const SpView &A, int64_t n, long long r_
                            const SliceState *st, float *ypart, int grid, hipStream_t s)
 {
     auto kern = k_scatter_rows<16, 8, 2, VT>;
-    const size_t bytes = sizeof(float) * size_t(n);
+    const size_t bytes = sizeof(double) * size_t(n);
     if (prepare)
         return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)bytes);

@@ -221,7 +221,8 @@ struct FusedCfg {
                // registers (cap * lpr * vec = 256 entries; with zl, 16 a lane)
     int grid;  // workgroups, each with an LDS copy of y
     int acc64; // 1: float64 LDS accumulators, 0: float32
-    int zl = 0; // 1: z staged in LDS beside a float32 y (k_fused_zl, k_fused_zlr; acc64 = 0)
+    int zl = 0; // 1: z staged in LDS beside y (k_fused_zl, k_fused_zlr)
+    int out32 = 0; // 1: a float64 y leaves as float32 partial vectors (zl; problems with dose-volume rows)
     int cus = 0; // workgroups at one per CU
     int most = 0; // workgroups at as many per CU as the LDS allows (the partial vectors' room)
 };
@@ -337,8 +338,8 @@ hipError_t launch_step_apply(int64_t n, int B, const double *y, float *x, const 
 // workgroup, and one partial vector of y = A^T c per workgroup in ypart
 // (grid x n, float64 or float32 by cfg.acc64).  lds_bytes: dynamic LDS it needs.
 size_t fused_lds_bytes(int64_t n, int acc64);
-// dynamic LDS of the fused pass with z in LDS (z and a float32 y)
-size_t fused_zl_lds_bytes(int64_t n);
+// dynamic LDS of the fused pass with z in LDS (z and y, float64 or float32)
+size_t fused_zl_lds_bytes(int64_t n, int acc64);
 // chunks of a row the fused pass with z in LDS keeps in registers for the
 // scatter (cap != 0): 16 entries a lane (more, beside the LDS reads in
 // flight, would not fit the 128 registers of a 1024-thread workgroup's lane)
