@@ -1176,13 +1176,14 @@ std::vector<FusedCfg> fused_candidates(const FusedCfg &base, int64_t n, bool zl_
                 t.cap = fused_zl_cap(lpr, vec); // the row's first entries kept in registers
                 out.push_back(t);
             }
-    // where two workgroups fit a CU, also at one: half the partial vectors to
-    // write and to sum (2 x 4n bytes a workgroup), against the second
-    // workgroup's rows in flight
+    // where two workgroups fit a CU, z in LDS at one: half the partial vectors
+    // to write and to sum (4n + 8n bytes a workgroup; 6,293 columns, bf16: 34
+    // us against 39), but up to 2,048 columns, where those are small beside
+    // the second workgroup's rows in flight, both are tried
     const size_t shapes = out.size();
     for (size_t i = 0; i < shapes; ++i) {
-        out[i].grid = base.most;
-        if (base.cus < base.most) {
+        out[i].grid = out[i].zl && n > 2048 ? base.cus : base.most;
+        if (out[i].zl && n <= 2048 && base.cus < base.most) {
             FusedCfg t = out[i];
             t.grid = base.cus;
             out.push_back(t);
@@ -1372,7 +1373,7 @@ void setup_fused(smx_problem *p)
         if (!present) continue;
         bool ok = true;
         for (const FusedCfg &t : fused_candidates(c, p->n, dvc))
-            if (t.grid == c.most && prepare_fused(t, fused_fmt(p, vk), p->n) != hipSuccess) ok = false;
+            if (prepare_fused(t, fused_fmt(p, vk), p->n) != hipSuccess) ok = false;
         if (dvc && prepare_scatter_rows(fused_fmt(p, vk), p->n) != hipSuccess) ok = false;
         (void)hipGetLastError();
         p->fused_ok[vk] = p->fused[vk] = ok;

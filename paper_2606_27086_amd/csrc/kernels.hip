@@ -1280,8 +1280,58 @@ __device__ inline int first_row_at(const int *__restrict__ ptr, int rows, long l
     return lo;
 }
 
-__device__ inline void lds_add(double *a, double v) { atomicAdd(a, v); }
-__device__ inline void lds_add(float *a, double v) { atomicAdd(a, (float)v); }
+// y[c_e] += sc * v_e for a lane's VEC entries (y in LDS; entries of value 0,
+// padding among them, add nothing).  ds_add_f64 takes 8 to 16 clocks a wave
+// where the addresses spread over the banks.  ds_add_f32 takes 3 clocks a
+// lane whatever its addresses (192 a wave), a read and a compare-and-swap 15
+// a wave: so a float32 y is added to by one compare-and-swap round for all
+// VEC entries, a second one from the values the first found, and only the
+// entries another row changed both times by ds_add_f32.
+template <int VEC>
+__device__ inline void lds_add_entries(double *y, const int (&c)[VEC], const float (&v)[VEC], double sc)
+{
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+        if (v[e] != 0.f) atomicAdd(&y[c[e]], sc * (double)v[e]);
+}
+template <int VEC>
+__device__ inline void lds_add_entries(float *y, const int (&c)[VEC], const float (&v)[VEC], double sc)
+{
+    unsigned *const w = reinterpret_cast<unsigned *>(y);
+    float a[VEC];
+    unsigned was[VEC], now[VEC];
+    bool any = false;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        a[e] = (float)(sc * (double)v[e]);
+        was[e] = __hip_atomic_load(&w[c[e]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    }
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) now[e] = atomicCAS(&w[c[e]], was[e], __float_as_uint(__uint_as_float(was[e]) + a[e]));
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) any = any || (now[e] != was[e] && a[e] != 0.f);
+    if (!any) return;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+        if (now[e] != was[e] && a[e] != 0.f) {
+            was[e] = atomicCAS(&w[c[e]], now[e], __float_as_uint(__uint_as_float(now[e]) + a[e]));
+            if (was[e] != now[e]) atomicAdd(&y[c[e]], a[e]);
+        }
+    }
+}
+
+// The same for entries held in registers since the dot product, by the
+// plain adds: the rows of a workgroup that wait for one another's loads reach
+// their scatter together, and on the columns they share the swaps mostly fail
+// (radiotherapy, 400M entries, 16 x 8 with a float32 y: 556 us by swaps,
+// 547 by adds; without held entries 473 us by swaps, 660 by adds).
+template <int VEC, typename AccT>
+__device__ inline void lds_add_held(AccT *y, const int (&c)[VEC], const float (&v)[VEC], double sc)
+{
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+        if (v[e] != 0.f) atomicAdd(&y[c[e]], (AccT)(sc * (double)v[e]));
+}
 
 // y[c_j] += sc * a_ij over row [beg, end) (y in LDS), by lane `lane` of an
 // LPR-lane group, the row's entries read again (from the cache) one chunk at
@@ -1303,9 +1353,7 @@ __device__ inline void scatter_row(const SpView &A, int beg, int end, int lane, 
         float v[VEC];
         int c[VEC];
         Entries<VT, VEC>::load(A, p, v, c);
-#pragma unroll
-        for (int e = 0; e < VEC; ++e)
-            if (v[e] != 0.f) lds_add(&y[c[e]], sc * (double)v[e]);
+        lds_add_entries<VEC>(y, c, v, sc);
     }
 }
 
@@ -1455,18 +1503,13 @@ __global__ __launch_bounds__(kFusedRcBlock) void k_fused_rc(SpView A, int n, con
             if (ct != 0.0) {
                 const double sc = ct * (double)A.vscale_inv;
 #pragma unroll
-                for (int q = 0; q < CAP; ++q)
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e)
-                        if (cur.v[q][e] != 0.f) lds_add(&y[cur.c[q][e]], sc * (double)cur.v[q][e]);
+                for (int q = 0; q < CAP; ++q) lds_add_held<VEC>(y, cur.c[q], cur.v[q], sc);
                 if (tail) {
                     for (int p = beg + CAP * STEP + lane * VEC; p < end; p += STEP) {
                         float v[VEC];
                         int c[VEC];
                         Entries<VT, VEC>::load(A, p, v, c);
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e)
-                            if (v[e] != 0.f) lds_add(&y[c[e]], sc * (double)v[e]);
+                        lds_add_entries<VEC>(y, c, v, sc);
                     }
                 }
             }
@@ -4087,18 +4130,13 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zlr(SpView A, int n, cons
             if (ct != 0.0) {
                 const double sc = ct * (double)A.vscale_inv;
 #pragma unroll
-                for (int q = 0; q < CAP; ++q)
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e)
-                        if (R.v[q][e] != 0.f) lds_add(&y[R.c[q][e]], sc * (double)R.v[q][e]);
+                for (int q = 0; q < CAP; ++q) lds_add_held<VEC>(y, R.c[q], R.v[q], sc);
                 if (tail) {
                     for (int p = beg + CAP * STEP + lane * VEC; p < end; p += STEP) {
                         float v[VEC];
                         int c[VEC];
                         Entries<VT, VEC>::load(A, p, v, c);
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e)
-                            if (v[e] != 0.f) lds_add(&y[c[e]], sc * (double)v[e]);
+                        lds_add_entries<VEC>(y, c, v, sc);
                     }
                 }
             }
@@ -4162,10 +4200,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_scatter_rows(SpView A, int n, l
 #pragma unroll
                 for (int q = 0; q < CAP; ++q) spread_entries<VEC>(R.v[q], R.c[q], slot);
 #pragma unroll
-                for (int q = 0; q < CAP; ++q)
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e)
-                        if (R.v[q][e] != 0.f) lds_add(&y[R.c[q][e]], sc * (double)R.v[q][e]);
+                for (int q = 0; q < CAP; ++q) lds_add_held<VEC>(y, R.c[q], R.v[q], sc);
             }
         }
         ci = nci;
