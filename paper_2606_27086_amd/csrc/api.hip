@@ -828,14 +828,26 @@ void enqueue_extrapolated_step(smx_problem *p, int vk, const RowW &rw, int npart
               "extrapolated step");
 }
 
+// Whether the fused pass is in use (for a value kind that runs) with the step
+// applied in its apply kernel, which then leaves the linear objective's
+// direction partials.
+bool lin_partials_from_apply(const smx_problem *p)
+{
+    if (p->basic == SMX_BASIC_EL || p->basic == SMX_BASIC_EMR || !p->part_lin.p) return false;
+    const int lp = p->op->lp_kind();
+    return lp != VK_F32 ? p->fused[lp] : p->fused[VK_F32];
+}
+
 enum PhaseKind { PHASE_CHAIN, PHASE_SMALL, PHASE_LINEAR, PHASE_LINE };
 
 // How the problem's perturbation phase runs: as asked, or by default in one
 // launch for flat objectives on vectors up to kSmallPhaseAutoN (one
 // workgroup streams x at one CU's rate, about 15 GB/s from memory, so its
 // time grows with n: ~6 us at n = 324, ~28 us at n = 19,881, where the
-// launch chain takes ~22-25 us whatever n), the linear objective beyond that
-// with its trials in closed form, the squared norm and L1 (up to kLineMaxN,
+// launch chain takes ~22-25 us whatever n), the linear objective beyond that,
+// and wherever the fused pass's apply kernel leaves its partials (the phase
+// then takes one launch of ~4.5 us or none, the one-launch form 8 us at n =
+// 6,293), with its trials in closed form, the squared norm and L1 (up to kLineMaxN,
 // past which summing the trials in every workgroup would cost more than the
 // chain's launches) with theirs valued along the line in one launch, anything
 // else as the chain of launches.
@@ -846,6 +858,7 @@ PhaseKind phase_kind(const smx_problem *p)
     case SMX_PHASE_ONE_LAUNCH: return PHASE_SMALL;   // eligibility checked when set
     case SMX_PHASE_CLOSED_FORM: return PHASE_LINEAR; // likewise
     default:
+        if (p->pp.obj == OBJ_LINEAR && lin_partials_from_apply(p)) return PHASE_LINEAR;
         if (phase_in_one_launch(p->pp) && p->n <= kSmallPhaseAutoN) return PHASE_SMALL;
         if (p->pp.obj == OBJ_LINEAR) return PHASE_LINEAR;
         return phase_on_line(p->pp) ? PHASE_LINE : PHASE_CHAIN;
@@ -1237,7 +1250,7 @@ int build_dvc_table(const smx_problem_desc *d, int64_t m, DvcTable &dt)
 // dose-volume rows (their ranking precedes c), an LDS copy of y that fits
 // (float64 if it can, else float32), one or two workgroups per CU as the LDS
 // allows.
-bool fused_plan(int64_t n, int B, int n_dvc, FusedCfg &c, size_t &lds_bytes)
+bool fused_plan(int64_t m, int64_t n, int64_t nnz, int B, int n_dvc, FusedCfg &c, size_t &lds_bytes)
 {
     if (B != 1) return false;
     // dose-volume rows: the shapes with z in LDS store their values for the
@@ -1258,8 +1271,14 @@ bool fused_plan(int64_t n, int B, int n_dvc, FusedCfg &c, size_t &lds_bytes)
     c = FusedCfg{};
     c.vec = 4;
     c.cap = 0;
-    c.grid = c.most = std::max(1, std::min(cus * per_cu, kMaxPassGrid));
-    c.cus = std::max(1, std::min(cus, kMaxPassGrid));
+    // beyond 64 no more workgroups than give each 64 rows (one for each of its 16-lane
+    // groups) or 8,192 entries: beyond that they only add partial vectors to
+    // write and sum (256 x 128 dense, 64 workgroups against 256: 5.5 and 3.5 us
+    // for the pass and the step against 8.3 and 6.8; 4,332 rows, 585k entries,
+    // 324 columns, 72 against 256: a single step 28 us against 34)
+    const int64_t use = std::max<int64_t>({64, (m + 63) / 64, (nnz + 8191) / 8192});
+    c.grid = c.most = (int)std::max<int64_t>(1, std::min<int64_t>({int64_t(cus) * per_cu, kMaxPassGrid, use}));
+    c.cus = std::min(c.most, std::max(1, cus));
     c.acc64 = acc64;
     return true;
 }
@@ -1281,11 +1300,12 @@ size_t dvc_hist_bytes(const DvcTable &dt, int B) { return sizeof(unsigned) * siz
 size_t dvc_sel_bytes(const DvcTable &dt, int B) { return sizeof(DvcSel) * size_t(kDvcRounds - 1) * dt.n * B; }
 
 // Device bytes of every buffer create_problem allocates for an operator with
-// m rows, n columns, float32 values (has_f32) and/or the reduced-precision
+// m rows, n columns, nnz entries, float32 values (has_f32) and/or the reduced-precision
 // kind lp, and the descriptor d (whose fields the sizes depend on are
 // validated by the caller), in the order it allocates them.  DBuf takes 256
 // bytes for an empty buffer.
-size_t problem_plan_bytes(int64_t m, int64_t n, bool has_f32, int lp, const smx_problem_desc *d, const DvcTable &dt)
+size_t problem_plan_bytes(int64_t m, int64_t n, int64_t nnz, bool has_f32, int lp, const smx_problem_desc *d,
+                          const DvcTable &dt)
 {
     const size_t B = size_t(d->B), M = size_t(m), N = size_t(n);
     size_t t = 0;
@@ -1322,7 +1342,7 @@ size_t problem_plan_bytes(int64_t m, int64_t n, bool has_f32, int lp, const smx_
     }
     FusedCfg fc;
     size_t lds = 0;
-    if (fused_plan(n, d->B, dt.n, fc, lds)) {
+    if (fused_plan(m, n, nnz, d->B, dt.n, fc, lds)) {
         add(lds * size_t(fc.grid)); // partial vectors of y
         if (d->obj_kind == SMX_OBJ_LINEAR) add(8 * 2 * size_t(fused_apply_grid(n))); // direction partials
     }
@@ -1356,7 +1376,7 @@ void setup_fused(smx_problem *p)
 {
     FusedCfg c;
     size_t bytes = 0;
-    if (!fused_plan(p->n, p->B, p->dvc.n, c, bytes)) return;
+    if (!fused_plan(p->m, p->n, p->op->nnz, p->B, p->dvc.n, c, bytes)) return;
     const DevLayout &L = p->op->csr;
     const double mean = L.rows > 0 ? double(L.slots) / double(L.rows) : 0.0;
     c.lpr = mean <= 64 ? 8 : (mean <= 256 ? 16 : 32);
@@ -2128,7 +2148,7 @@ int smx_footprint(int64_t m, int64_t n, int64_t nnz, int32_t value_storage, int3
             if (const int rc = build_dvc_table(d, m, dt); rc != SMX_OK) return rc;
             const bool lp = value_storage != SMX_STORE_F32;
             const int lk = value_storage == SMX_STORE_BF16 ? VK_BF16 : (value_storage == SMX_STORE_F16 ? VK_F16 : VK_F32);
-            pb = problem_plan_bytes(m, n, !lp || keep_f32 != 0, lk, d, dt);
+            pb = problem_plan_bytes(m, n, nnz, !lp || keep_f32 != 0, lk, d, dt);
         }
         *operator_bytes = ob;
         *problem_bytes = pb;

@@ -84,6 +84,15 @@ def test_phase_on_the_line_ends_at_the_trial_cap(smx):
         assert st[0]["trials"] == 21 and st[0]["accepts"] == 0 and st[0]["cap_hits"] == 1
 
 
+@pytest.mark.parametrize("m,n", [(1, 2), (70, 63), (4097, 65), (16500, 324), (300, 2049), (200, 8192)])
+def test_linear_phase_in_the_apply_kernel(smx, m, n):
+    """Linear objective below n = 8,192: the phase in closed form from the
+    partials that the fused pass leaves, and grids at both ends of the rule on
+    rows (64 workgroups, then one for 64 rows)."""
+    w = W.random_sparse(m, n, min(n, 6), seed=m, obj=W.OBJ_LINEAR, K=1)
+    check_iteration(smx, w.with_params(gamma=3.0, alpha=0.9, n_red=2))
+
+
 @pytest.mark.parametrize("B,gamma,alpha", [(1, 200.0, 0.93), (1, 3.0, 0.97), (2, 200.0, 0.93), (1, 1e6, 0.99)])
 def test_tv_phase_with_failing_batches(smx, B, gamma, alpha):
     """Four reduction steps in six trial launches: first batches of 8 that fail
