@@ -897,48 +897,75 @@ __device__ inline void stop_rules_after_step(SliceState &S, double prox)
     if (S.stop_reason == STOP_NONE && S.stop_max > 0 && S.k >= S.stop_max) S.stop_reason = STOP_MAXIT;
 }
 
-// End of an outer iteration: proximity from pass 1's partials, the history
-// record, k + 1, and whether the next iteration runs.  Called by every thread
-// of one workgroup (BS threads; lds holds BS/64 doubles).
+// End of an outer iteration for slice s, by one thread: proximity (prox2 is
+// pass 1's sum, twice of it), the history record, k + 1, and whether the next
+// iteration runs.
+__device__ inline void finish_slice(const SliceState *__restrict__ st_in, SliceState *__restrict__ st_out, int s,
+                                    int B, double prox2, const Hist &h)
+{
+    SliceState S = st_in[s];
+    S.ran = S.live;
+    if (S.live) {
+        const double prox = 0.5 * prox2;
+        S.prox = prox;
+        if (!isfinite(prox)) S.nonfinite = 1;
+        if (S.k < h.cap) {
+            const long long r = S.k * B + s;
+            h.prox[r] = prox;
+            h.f_start[r] = S.f_start;
+            h.f_end[r] = S.f_cur;
+            h.trials[r] = S.trials_it;
+            h.accepts[r] = S.accepts_it;
+        }
+        S.k += 1;
+        if (S.stop_on) stop_rules_after_step(S, prox);
+    }
+    if (!isnan(S.f_cur)) S.f_ref = S.f_cur; // where this iteration's phase ended
+    S.f_start = S.f_cur = nan64();
+    S.trials_it = 0;
+    S.accepts_it = 0;
+    S.phase = 0;
+    S.live = slice_runs(S);
+    st_out[s] = S;
+}
+
+// End of an outer iteration from pass 1's partials, called by every thread of
+// one workgroup (BS threads; lds holds BS/64 doubles): the whole workgroup for
+// one slice, a wave a slice for several.  It is a chain of loads, sums and
+// stores that needs nothing of the column step, so the launch has a workgroup
+// for it alone, the last one, beside those that take columns.  At the end of
+// workgroup 0, and slice after slice, as it was before, it was the tail of the
+// launch: 128 x 128 CT, 8 slices, pass 2 25.4 us, now 13.4; 64 x 64, one slice,
+// 25.3 us an iteration, now 24.2.
 template <int BS = kBlock>
 __device__ inline void finish_iteration(const SliceState *__restrict__ st_in, SliceState *__restrict__ st_out, int B,
                                         const double *__restrict__ part1, int nparts, const Hist &h, double *lds)
 {
-    for (int s = 0; s < B; ++s) {
+    if (B == 1) {
         double tot[1];
-        sum_slots<1, BS>(part1, (long long)s * nparts, nparts, tot, lds);
-        if (threadIdx.x == 0) {
-            SliceState S = st_in[s];
-            S.ran = S.live;
-            if (S.live) {
-                const double prox = 0.5 * tot[0];
-                S.prox = prox;
-                if (!isfinite(prox)) S.nonfinite = 1;
-                if (S.k < h.cap) {
-                    const long long r = S.k * B + s;
-                    h.prox[r] = prox;
-                    h.f_start[r] = S.f_start;
-                    h.f_end[r] = S.f_cur;
-                    h.trials[r] = S.trials_it;
-                    h.accepts[r] = S.accepts_it;
-                }
-                S.k += 1;
-                if (S.stop_on) stop_rules_after_step(S, prox);
-            }
-            if (!isnan(S.f_cur)) S.f_ref = S.f_cur; // where this iteration's phase ended
-            S.f_start = S.f_cur = nan64();
-            S.trials_it = 0;
-            S.accepts_it = 0;
-            S.phase = 0;
-            S.live = slice_runs(S);
-            st_out[s] = S;
-        }
+        sum_slots<1, BS>(part1, 0, nparts, tot, lds);
+        if (threadIdx.x == 0) finish_slice(st_in, st_out, 0, 1, tot[0], h);
+        return;
+    }
+    const int lane = threadIdx.x & 63;
+    for (int s = threadIdx.x >> 6; s < B; s += BS / 64) {
+        const double *p = part1 + (long long)s * nparts;
+        double tot[1] = {0.0};
+#pragma unroll 8
+        for (int b = lane; b < nparts; b += 64) tot[0] += p[b];
+        wave_sum<1>(tot);
+        if (lane == 0) finish_slice(st_in, st_out, s, B, tot[0], h);
     }
 }
 
+// Workgroups of a launch that take columns: all but the last, which closes
+// the outer iteration, or all of them where a later launch closes it.
+__device__ inline int column_groups(const ColStep &cs) { return (int)gridDim.x - (cs.defer ? 0 : 1); }
+static inline unsigned column_grid(int groups, const ColStep &cs) { return (unsigned)groups + (cs.defer ? 0u : 1u); }
+
 // ---------------------------------------------------------------------------
 // pass 2: y = A^T c, x = clip(z + lambda y, lo, hi) (DROP: lambda Z_j y);
-// workgroup 0 also closes the outer iteration.  For the extrapolated steps
+// one more workgroup closes the outer iteration.  For the extrapolated steps
 // (deferred mode) y itself is kept, with per-workgroup partials of ||y||^2,
 // and k_step_apply updates x and closes the iteration.
 // ---------------------------------------------------------------------------
@@ -959,20 +986,15 @@ __device__ inline double epi2(const ColStep &cs, long long col, long long e, dou
     return 0.0;
 }
 
-// End of a pass-2 launch (workgroups of BS threads): the ||y||^2 partials
-// (deferred mode), else workgroup 0 closes the outer iteration.
+// End of a workgroup's columns (BS threads): the ||y||^2 partials in deferred
+// mode.
 template <int BS = kBlock>
-__device__ inline void end_pass2(const ColStep &cs, double yacc, const SliceState *__restrict__ st_in,
-                                 SliceState *__restrict__ st_out, const double *__restrict__ part1, int nparts1,
-                                 const Hist &h, double *lds)
+__device__ inline void end_columns(const ColStep &cs, double yacc, double *lds)
 {
-    if (cs.defer) {
-        double v[1] = {yacc};
-        block_sum<1, BS>(v, lds);
-        if (threadIdx.x == 0) cs.ypart[blockIdx.x] = v[0];
-    } else if (blockIdx.x == 0) {
-        finish_iteration<BS>(st_in, st_out, 1, part1, nparts1, h, lds);
-    }
+    if (!cs.defer) return;
+    double v[1] = {yacc};
+    block_sum<1, BS>(v, lds);
+    if (threadIdx.x == 0) cs.ypart[blockIdx.x] = v[0];
 }
 
 template <int LPR, int VEC, typename VT>
@@ -982,12 +1004,17 @@ __global__ __launch_bounds__(kBlock) void k_pass2(SpView At, const float *__rest
                                                   int nparts1, Hist h)
 {
     __shared__ double lds[4];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration(st_in, st_out, 1, part1, nparts1, h, lds);
+        return;
+    }
     constexpr int RPB = kBlock / LPR;
     double yacc = 0.0;
     if (st_in[0].live) {
         const int lane = threadIdx.x & (LPR - 1);
         const int grp = threadIdx.x / LPR;
-        const long long stride = (long long)gridDim.x * RPB;
+        const long long stride = (long long)groups * RPB;
         for (long long col = (long long)blockIdx.x * RPB + grp; col < At.rows; col += stride) {
             const int beg = At.ptr[col], end = At.ptr[col + 1];
             float xo = 0.f, l = 0.f, u = 0.f;
@@ -1000,7 +1027,7 @@ __global__ __launch_bounds__(kBlock) void k_pass2(SpView At, const float *__rest
             if (lane == 0) yacc += epi2(cs, col, col, y, xo, l, u, x);
         }
     }
-    end_pass2(cs, yacc, st_in, st_out, part1, nparts1, h, lds);
+    end_columns(cs, yacc, lds);
 }
 
 // Pass 2 with the gathered residual partly in LDS, as k_pass1_lds: one
@@ -1016,6 +1043,11 @@ __global__ __launch_bounds__(kLdsPassBlock) void k_pass2_lds(SpView At, const fl
     extern __shared__ float4 cl4[];
     float *cl = reinterpret_cast<float *>(cl4);
     __shared__ double lds[kLdsPassBlock / 64];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration<kLdsPassBlock>(st_in, st_out, 1, part1, nparts1, h, lds);
+        return;
+    }
     constexpr int RPB = kLdsPassBlock / LPR;
     double yacc = 0.0;
     if (st_in[0].live) { // the same in every thread
@@ -1023,7 +1055,7 @@ __global__ __launch_bounds__(kLdsPassBlock) void k_pass2_lds(SpView At, const fl
         __syncthreads();
         const int lane = threadIdx.x & (LPR - 1);
         const int grp = threadIdx.x / LPR;
-        const long long stride = (long long)gridDim.x * RPB;
+        const long long stride = (long long)groups * RPB;
         long long col = (long long)blockIdx.x * RPB + grp;
         int beg = 0, end = 0;
         if (col < At.rows) {
@@ -1049,7 +1081,7 @@ __global__ __launch_bounds__(kLdsPassBlock) void k_pass2_lds(SpView At, const fl
             end = nend;
         }
     }
-    end_pass2<kLdsPassBlock>(cs, yacc, st_in, st_out, part1, nparts1, h, lds);
+    end_columns<kLdsPassBlock>(cs, yacc, lds);
 }
 
 // Sum of one column segment [beg, end) of the column copy whose rows all lie
@@ -1126,9 +1158,14 @@ __global__ __launch_bounds__(kBlock) void k_pass2_panel_sum(int np, int n, const
                                                             const double *__restrict__ part1, int nparts1, Hist h)
 {
     __shared__ double lds[4];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration(st_in, st_out, 1, part1, nparts1, h, lds);
+        return;
+    }
     double yacc = 0.0;
     if (st_in[0].live) {
-        for (int j = blockIdx.x * kBlock + threadIdx.x; j < n; j += gridDim.x * kBlock) {
+        for (int j = blockIdx.x * kBlock + threadIdx.x; j < n; j += groups * kBlock) {
             double y = 0.0;
             for (int p = 0; p < np; ++p) y += ypanel[(long long)p * n + j];
             float xo = 0.f;
@@ -1136,7 +1173,7 @@ __global__ __launch_bounds__(kBlock) void k_pass2_panel_sum(int np, int n, const
             yacc += epi2(cs, j, j, y * (double)vscale_inv, xo, cs.lo[j], cs.hi[j], x);
         }
     }
-    end_pass2(cs, yacc, st_in, st_out, part1, nparts1, h, lds);
+    end_columns(cs, yacc, lds);
 }
 
 template <int VEC, typename VT>
@@ -1149,9 +1186,14 @@ __global__ __launch_bounds__(kBlock) void k_pass2_stream(SpView At, RowBlocks RB
     __shared__ double prod[kStreamEntries / VEC];
     __shared__ int rp[kBlock + 1];
     __shared__ double lds[4];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration(st_in, st_out, 1, part1, nparts1, h, lds);
+        return;
+    }
     double yacc = 0.0;
     if (st_in[0].live) {
-        for (int b = blockIdx.x; b < RB.nblk; b += gridDim.x) {
+        for (int b = blockIdx.x; b < RB.nblk; b += groups) {
             const int r0 = RB.rb[b], r1 = RB.rb[b + 1];
             const int e0 = At.ptr[r0], e1 = At.ptr[r1];
             if (e1 - e0 > kStreamEntries) {
@@ -1180,7 +1222,7 @@ __global__ __launch_bounds__(kBlock) void k_pass2_stream(SpView At, RowBlocks RB
             __syncthreads();
         }
     }
-    end_pass2(cs, yacc, st_in, st_out, part1, nparts1, h, lds);
+    end_columns(cs, yacc, lds);
 }
 
 // Copies a tile's nr rows of c (B floats each, slice-interleaved as in
@@ -1225,12 +1267,17 @@ __global__ __launch_bounds__(kBlock) void k_pass2_tile(TileView T, const float *
 {
     extern __shared__ float cl[];
     __shared__ double lds[4];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration(st_in, st_out, 1, part1, nparts1, h, lds);
+        return;
+    }
     constexpr int RPB = kBlock / LPR;
     double yacc = 0.0;
     if (st_in[0].live) {
         const int lane = threadIdx.x & (LPR - 1);
         const int grp = threadIdx.x / LPR;
-        for (int t = blockIdx.x; t < T.ntiles; t += gridDim.x) {
+        for (int t = blockIdx.x; t < T.ntiles; t += groups) {
             const int r0 = T.rptr[t], nr = T.rptr[t + 1] - r0;
             __syncthreads(); // the previous tile's readers are done with cl
             stage_rows<1>(cl, c, T.rlist + r0, nr);
@@ -1250,7 +1297,7 @@ __global__ __launch_bounds__(kBlock) void k_pass2_tile(TileView T, const float *
             }
         }
     }
-    end_pass2(cs, yacc, st_in, st_out, part1, nparts1, h, lds);
+    end_columns(cs, yacc, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1539,17 +1586,17 @@ __global__ __launch_bounds__(kFusedRcBlock) void k_fused_rc(SpView A, int n, con
 
 // Direction partials of the linear objective f = c^T x for the next
 // perturbation phase: this workgroup's sums of c_j^2 and c_j x_j over the
-// unknowns j0 + l (l < 64, j0 = 64 blockIdx.x, stepping 64 gridDim.x),
+// unknowns j0 + l (l < 64, j0 = 64 blockIdx.x, stepping 64 groups),
 // added by the first wave's lanes in that order and then over the
 // workgroup, stored as the direction launch's partials would be (slot
-// blockIdx.x of 2 x gridDim.x).  k_fused_apply calls it after writing x and
+// blockIdx.x of 2 x groups).  k_fused_apply calls it after writing x and
 // k_lin_partials alone, with the same sums in the same order.
 __device__ inline void lin_partials_block(const float *__restrict__ x, const float *__restrict__ c, int n,
-                                          double *__restrict__ part, double *lds)
+                                          int groups, double *__restrict__ part, double *lds)
 {
     double v[2] = {0.0, 0.0}; // sum c^2, c^T x
     if ((threadIdx.x >> 6) == 0)
-        for (int j = blockIdx.x * 64 + (int)threadIdx.x; j < n; j += gridDim.x * 64) {
+        for (int j = blockIdx.x * 64 + (int)threadIdx.x; j < n; j += groups * 64) {
             const double cj = (double)c[j];
             v[0] += cj * cj;
             v[1] += cj * (double)x[j];
@@ -1557,7 +1604,7 @@ __device__ inline void lin_partials_block(const float *__restrict__ x, const flo
     block_sum<2, kApplyBlock>(v, lds);
     if (threadIdx.x == 0) {
         part[blockIdx.x] = v[0];
-        part[gridDim.x + blockIdx.x] = v[1];
+        part[groups + blockIdx.x] = v[1];
     }
 }
 
@@ -1566,13 +1613,13 @@ __global__ __launch_bounds__(kApplyBlock) void k_lin_partials(const float *__res
                                                               double *__restrict__ part)
 {
     __shared__ double lds[kApplyBlock / 64 * 2];
-    lin_partials_block(x, c, n, part, lds);
+    lin_partials_block(x, c, n, (int)gridDim.x, part, lds);
 }
 
 // x = clip(z + lambda * Z_j * sum_g ypart[g], lo, hi) (Z_j = 1 unless DROP);
 // 64 unknowns per workgroup, the four waves each sum every fourth partial
 // (loads issued four at a time, added in order) and the four sums are added in
-// a fixed order.  Workgroup 0 also closes the outer iteration.
+// a fixed order.  One more workgroup closes the outer iteration.
 template <typename AccT>
 __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restrict__ ypart, int G, int n,
                                                         float *__restrict__ x, ColStep cs,
@@ -1584,6 +1631,11 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
 {
     __shared__ double red[kApplyBlock / 64][64];
     __shared__ double lds[kApplyBlock / 64 * 2];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration<kApplyBlock>(st_in, st_out, 1, part1, nparts1, h, lds);
+        return;
+    }
     const int wid = threadIdx.x >> 6, wl = threadIdx.x & 63;
     double ysq = 0.0; // deferred mode: this thread's share of ||y||^2
     // the linear phase taken in the pass: x still holds x^k, z_j is formed here
@@ -1595,7 +1647,7 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
         zinv = 1.0 / st_in[0].gn;
     }
     if (st_in[0].live) {
-        for (int j0 = blockIdx.x * 64; j0 < n; j0 += gridDim.x * 64) {
+        for (int j0 = blockIdx.x * 64; j0 < n; j0 += groups * 64) {
             const int j = j0 + wl;
             constexpr int W = kApplyBlock / 64;
             double sum = 0.0;
@@ -1632,14 +1684,8 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
     }
     // the next phase's direction partials from the x just written (each
     // lane rereads its own entries)
-    if (lin_part) lin_partials_block(x, lin_c, n, lin_part, lds);
-    if (cs.defer) {
-        double v[1] = {ysq};
-        block_sum<1, kApplyBlock>(v, lds);
-        if (threadIdx.x == 0) cs.ypart[blockIdx.x] = v[0];
-    } else if (blockIdx.x == 0) {
-        finish_iteration<kApplyBlock>(st_in, st_out, 1, part1, nparts1, h, lds);
-    }
+    if (lin_part) lin_partials_block(x, lin_c, n, groups, lin_part, lds);
+    end_columns<kApplyBlock>(cs, ysq, lds);
 }
 
 // Extrapolated steps (one launch after pass 2, or after the quadratic-form
@@ -1647,7 +1693,8 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
 // workgroup order by every workgroup (EL: t^T D t / ||y||^2, with t^T D t
 // twice pass 1's proximity sum; EMR: ||y||^2 / sum_i w_i (A y)_i^2), 0 when the
 // denominator is 0 or the quotient is not finite; then
-// x = clip(z + lambda sigma y, lo, hi).  Workgroup 0 also closes the iteration.
+// x = clip(z + lambda sigma y, lo, hi).  One more workgroup, the last, closes
+// the iteration.
 __global__ __launch_bounds__(kBlock) void k_step_apply(int n, int B, const double *__restrict__ y,
                                                        float *__restrict__ x, const float *__restrict__ lo,
                                                        const float *__restrict__ hi, float lambda, int emr,
@@ -1660,6 +1707,11 @@ __global__ __launch_bounds__(kBlock) void k_step_apply(int n, int B, const doubl
     __shared__ double lds[4];
     __shared__ double sigma[32];
     __shared__ int live[32];
+    const int groups = (int)gridDim.x - 1;
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
+        return;
+    }
     for (int s = 0; s < B; ++s) {
         double num[1], den[1];
         if (emr) {
@@ -1677,14 +1729,13 @@ __global__ __launch_bounds__(kBlock) void k_step_apply(int n, int B, const doubl
     }
     __syncthreads();
     const long long total = (long long)n * B;
-    for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < total; e += (long long)gridDim.x * kBlock) {
+    for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < total; e += (long long)groups * kBlock) {
         const int s = (int)(e % B);
         if (!live[s]) continue;
         const long long j = e / B;
         const double z = fma((double)lambda * sigma[s], y[e], (double)x[e]);
         x[e] = (float)fmin(fmax(z, (double)lo[j]), (double)hi[j]);
     }
-    if (blockIdx.x == 0) finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -1899,6 +1950,11 @@ __global__ __launch_bounds__(kBlock) void k_pass2_mm(SpView At, const float *__r
                                                      const double *__restrict__ part1, int nparts1, Hist h)
 {
     __shared__ double lds[4];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
+        return;
+    }
     constexpr int RPB = kBlock / LPR, LS = SliceLanes<B>::LS, NS = SliceLanes<B>::NS;
     const int lane = threadIdx.x & (LPR - 1);
     const int grp = threadIdx.x / LPR;
@@ -1910,7 +1966,7 @@ __global__ __launch_bounds__(kBlock) void k_pass2_mm(SpView At, const float *__r
         live[k] = st_in[s0 + k].live != 0;
         yacc[k] = 0.0;
     }
-    const long long stride = (long long)gridDim.x * RPB;
+    const long long stride = (long long)groups * RPB;
     long long col = (long long)blockIdx.x * RPB + grp;
     int beg = 0, end = 0;
     if (col < At.rows) {
@@ -1937,7 +1993,6 @@ __global__ __launch_bounds__(kBlock) void k_pass2_mm(SpView At, const float *__r
         end = nend;
     }
     if (cs.defer) slice_partials<B>(yacc, cs.ypart);
-    else if (blockIdx.x == 0) finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
 }
 
 // Pass 2 over the image-tile column layout for B slices: the tile's rows of
@@ -1954,6 +2009,11 @@ __global__ __launch_bounds__(kBlock) void k_pass2_tile_mm(TileView T, const floa
     extern __shared__ float4 cl4[]; // 16-byte aligned: rows of B floats
     float *cl = reinterpret_cast<float *>(cl4);
     __shared__ double lds[4];
+    const int groups = column_groups(cs);
+    if ((int)blockIdx.x == groups) { // the same in every thread
+        finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
+        return;
+    }
     __shared__ int any_live;
     constexpr int RPB = kBlock / LPR, LS = SliceLanes<B>::LS, NS = SliceLanes<B>::NS;
     if (threadIdx.x == 0) any_live = 0;
@@ -1971,7 +2031,7 @@ __global__ __launch_bounds__(kBlock) void k_pass2_tile_mm(TileView T, const floa
         yacc[k] = 0.0;
     }
     if (any_live) {
-        for (int t = blockIdx.x; t < T.ntiles; t += gridDim.x) {
+        for (int t = blockIdx.x; t < T.ntiles; t += groups) {
             const int r0 = T.rptr[t], nr = T.rptr[t + 1] - r0;
             __syncthreads(); // the previous tile's readers are done with cl
             stage_rows<B>(cl, c, T.rlist + r0, nr);
@@ -1995,7 +2055,6 @@ __global__ __launch_bounds__(kBlock) void k_pass2_tile_mm(TileView T, const floa
         }
     }
     if (cs.defer) slice_partials<B>(yacc, cs.ypart);
-    else if (blockIdx.x == 0) finish_iteration(st_in, st_out, B, part1, nparts1, h, lds);
 }
 
 // Query: the proximity at the current x from pass 1's partials (query mode).
@@ -3560,7 +3619,7 @@ static hipError_t pass2_lds_go(const PassCfg &cfg, const SpView &At, const float
         return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)(sizeof(float) * kLdsPassFloats));
     const size_t shm = sizeof(float4) * size_t((cfg.xlds + 3) / 4);
-    hipLaunchKernelGGL(kern, dim3(cfg.grid), dim3(kLdsPassBlock), shm, s, At, c, cfg.xlds, x, cs, st_in, st_out,
+    hipLaunchKernelGGL(kern, dim3(column_grid(cfg.grid, cs)), dim3(kLdsPassBlock), shm, s, At, c, cfg.xlds, x, cs, st_in, st_out,
                        part1, nparts1, h);
     return hipGetLastError();
 }
@@ -3659,7 +3718,7 @@ hipError_t launch_pass2_panels(const PassCfg &cfg, const SpView &At, const Panel
     if (e != hipSuccess) return e;
     // the column sums in the same grid, so that the ||y||^2 partials of the
     // extrapolated steps number cfg.grid as for the other pass-2 shapes
-    hipLaunchKernelGGL(k_pass2_panel_sum, dim3(cfg.grid), dim3(kBlock), 0, s, PV.np, (int)At.rows, PV.ypanel,
+    hipLaunchKernelGGL(k_pass2_panel_sum, dim3(column_grid(cfg.grid, cs)), dim3(kBlock), 0, s, PV.np, (int)At.rows, PV.ypanel,
                        At.vscale_inv, x, cs, st_in, st_out, part1, nparts1, h);
     return hipGetLastError();
 }
@@ -3754,7 +3813,7 @@ static hipError_t pass2_vec(const PassCfg &cfg, const SpView &At, const float *c
                             const SliceState *st_in, SliceState *st_out, const double *part1, int nparts1, Hist h,
                             hipStream_t s)
 {
-    const dim3 grid(cfg.grid), block(kBlock);
+    const dim3 grid(column_grid(cfg.grid, cs)), block(kBlock);
 #define SMX_P2(L) hipLaunchKernelGGL((k_pass2<L, VEC, VT>), grid, block, 0, s, At, c, x, cs, st_in, st_out, part1, nparts1, h)
     switch (cfg.lpr) {
     case 2: SMX_P2(2); break;
@@ -3774,7 +3833,7 @@ static hipError_t pass2_stream(const PassCfg &cfg, const SpView &At, const RowBl
                                ColStep cs, const SliceState *st_in, SliceState *st_out, const double *part1,
                                int nparts1, Hist h, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_pass2_stream<VEC, VT>), dim3(cfg.grid), dim3(kBlock), 0, s, At, RB, c, x, cs,
+    hipLaunchKernelGGL((k_pass2_stream<VEC, VT>), dim3(column_grid(cfg.grid, cs)), dim3(kBlock), 0, s, At, RB, c, x, cs,
                        st_in, st_out, part1, nparts1, h);
     return hipGetLastError();
 }
@@ -3784,7 +3843,7 @@ static hipError_t pass2_mm(const PassCfg &cfg, const SpView &At, const float *c,
                            const SliceState *st_in, SliceState *st_out, const double *part1, int nparts1, Hist h,
                            hipStream_t s)
 {
-    const dim3 grid(cfg.grid), block(kBlock);
+    const dim3 grid(column_grid(cfg.grid, cs)), block(kBlock);
 #define SMX_P2MM(L) hipLaunchKernelGGL((k_pass2_mm<L, VEC, VT, B>), grid, block, 0, s, At, c, x, cs, st_in, st_out, part1, nparts1, h)
     constexpr int L0 = mm_lanes(B, 0), L1 = mm_lanes(B, 1), L2 = mm_lanes(B, 2);
     switch (cfg.lpr) {
@@ -3817,7 +3876,7 @@ static hipError_t pass2_tiles_mm(const PassCfg &cfg, const TileView &T, const fl
                                  const SliceState *st_in, SliceState *st_out, const double *part1, int nparts1,
                                  Hist h, hipStream_t s)
 {
-    const dim3 grid(cfg.grid), block(kBlock);
+    const dim3 grid(column_grid(cfg.grid, cs)), block(kBlock);
     const size_t shm = sizeof(float) * B * size_t(T.max_rows > 0 ? T.max_rows : 1);
 #define SMX_P2TM(L) hipLaunchKernelGGL((k_pass2_tile_mm<L, VEC, VT, B>), grid, block, shm, s, T, c, x, cs, st_in, st_out, part1, nparts1, h)
     constexpr int L0 = mm_lanes(B, 0), L1 = mm_lanes(B, 1), L2 = mm_lanes(B, 2);
@@ -3851,7 +3910,7 @@ hipError_t pass2_tiles(const PassCfg &cfg, const TileView &T, const float *c, fl
                        const SliceState *st_in, SliceState *st_out, const double *part1, int nparts1, Hist h,
                        hipStream_t s)
 {
-    const dim3 grid(cfg.grid), block(kBlock);
+    const dim3 grid(column_grid(cfg.grid, cs)), block(kBlock);
     const size_t shm = sizeof(float) * size_t(T.max_rows > 0 ? T.max_rows : 1);
 #define SMX_P2T(L) hipLaunchKernelGGL((k_pass2_tile<L, VEC, VT>), grid, block, shm, s, T, c, x, cs, st_in, st_out, part1, nparts1, h)
     switch (cfg.lpr) {
@@ -4361,7 +4420,7 @@ hipError_t launch_fused_apply(const FusedCfg &cfg, int64_t n, const void *ypart,
     if (cfg.grid < 1 || cfg.grid > kMaxPassGrid || n < 1 || nvec < cfg.grid || nvec > 2 * cfg.grid ||
         (wide && nvec != cfg.grid) || (lin_part && (!lin_c || cs.defer)) || (lin_z && (!lin_c || cs.defer)))
         return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)fused_apply_grid(n);
+    const unsigned grid = column_grid(fused_apply_grid(n), cs);
     if (wide)
         hipLaunchKernelGGL(k_fused_apply<double>, dim3(grid), dim3(kApplyBlock), 0, s, static_cast<const double *>(ypart),
                            nvec, (int)n, x, cs, st_in, st_out, part1, cfg.grid, h, lin_c, lin_part, lin_z);
@@ -4428,7 +4487,7 @@ hipError_t launch_step_apply(int64_t n, int B, const double *y, float *x, const 
                              hipStream_t s)
 {
     if (n < 1 || B < 1 || B > 32 || nparts1 < 1 || npartsy < 1 || (emr && npartsq < 1)) return hipErrorInvalidValue;
-    const unsigned grid = grid_for(n * B, kBlock, 2048);
+    const unsigned grid = grid_for(n * B, kBlock, 2048) + 1; // the last closes the iteration
     hipLaunchKernelGGL(k_step_apply, dim3(grid), dim3(kBlock), 0, s, (int)n, B, y, x, lo, hi, lambda, emr, part1,
                        nparts1, party, npartsy, partq, npartsq, st_in, st_out, h);
     return hipGetLastError();
