@@ -2092,6 +2092,36 @@ __device__ inline double trial_beta(const PertParams &pp, const SliceState &S, l
     return pp.adaptive ? S.beta_ad : pp.gamma * pow(pp.alpha, (double)e);
 }
 
+// The steps of 64 trials from exponent `base` on, formed by the last wave of a
+// workgroup while the others sum the partials that decide which of them are
+// asked for: pow in float64 is ~0.7 us, and stood twice in the chain of every
+// trial launch (187 x 171 CT, four steps a phase: 7.7 us a trial launch, now
+// 6.75; 256 x 256, one step: 5.6, now 5.2).
+struct StepWindow {
+    long long base;
+    double beta[64];
+};
+
+// Every thread calls it; the next barrier publishes the window.  first: the
+// phase opens in this launch, so the exponent is the one that
+// open_phase_state will start from.
+template <int BS>
+__device__ inline void form_steps(StepWindow &win, const PertParams &pp, const SliceState &S, int first)
+{
+    if (threadIdx.x < BS - 64 || pp.adaptive) return;
+    long long e = S.ell;
+    if (first && pp.restart_every > 0 && S.k > 0 && (S.k % pp.restart_every) == 0) e = S.restarts + 1;
+    const int l = threadIdx.x & 63;
+    win.beta[l] = pp.gamma * pow(pp.alpha, (double)(e + l));
+    if (l == 0) win.base = e;
+}
+
+__device__ inline double step_of(const StepWindow &win, const PertParams &pp, const SliceState &S, long long e)
+{
+    if (!pp.adaptive && e >= win.base && e < win.base + 64) return win.beta[e - win.base];
+    return trial_beta(pp, S, e);
+}
+
 // Trials a launch evaluates for slice state S, with `after` evaluating
 // launches behind it: the first batch of a reduction step is the default
 // width, widened to 1.5x the trials the previous step needed (step sizes
@@ -2215,12 +2245,14 @@ __device__ inline void open_phase_state(SliceState &S, const PertParams &pp, dou
 // The state after a batch of ntr trials (steps ell .. ell+ntr-1 of the power
 // law, or the one adaptive step) was evaluated: acc_t is the first trial in
 // order whose objective does not exceed f_cur (-1 when none does), acc_f its
-// objective.  Accepting ends the reduction step (and the phase after n_red of
-// them); a step that reaches the trial cap unaccepted ends the phase.
-__device__ inline void record_decision(SliceState &S, const PertParams &pp, int ntr, int acc_t, double acc_f)
+// objective and beta its step.  Accepting ends the reduction step (and the
+// phase after n_red of them); a step that reaches the trial cap unaccepted
+// ends the phase.
+__device__ inline void record_decision(SliceState &S, const PertParams &pp, int ntr, int acc_t, double acc_f,
+                                       double beta)
 {
     if (acc_t >= 0) {
-        S.s_acc = S.s_acc + trial_beta(pp, S, S.ell + acc_t);
+        S.s_acc = S.s_acc + beta;
         S.f_cur = acc_f;
         if (!isfinite(acc_f)) S.nonfinite = 1;
         S.ell += acc_t + 1;
@@ -2250,50 +2282,53 @@ __device__ inline void record_decision(SliceState &S, const PertParams &pp, int 
 // accepted; reading stops at the chunk holding it.
 template <int BS>
 __device__ inline void derive_decision(SliceState &sS, const PertParams &pp, const double *__restrict__ part_prev,
-                                       long long nslots, int s, int nt, double *tot, int after)
+                                       long long nslots, int s, int nt, double *tot, StepWindow &win, int after)
 {
     __shared__ int acc_t;
     __shared__ double acc_f;
     const int ntr = trial_width(sS, pp, after + 1); // as the launch before this one saw it
     if (ntr == 0) return;
     if (threadIdx.x == 0) acc_t = -1;
+    form_steps<BS>(win, pp, sS, 0);
     for (int t0 = 0; t0 < ntr; t0 += kTrialChunk) {
         const int nv = min(kTrialChunk, ntr - t0);
         chunk_totals<BS>(part_prev, nslots, s, nt, t0, nv, tot);
-        if (threadIdx.x == 0) {
-            for (int w = 0; w < nv; ++w) {
-                if (tot[w] <= sS.f_cur) {
-                    acc_t = t0 + w;
-                    acc_f = tot[w];
-                    break;
-                }
+        if (threadIdx.x < 64) {
+            const int l = threadIdx.x;
+            const unsigned long long ok = __ballot(l < nv && tot[min(l, nv - 1)] <= sS.f_cur);
+            if (l == 0 && ok) {
+                acc_t = t0 + __ffsll(ok) - 1;
+                acc_f = tot[acc_t - t0];
             }
         }
         __syncthreads();
         if (acc_t >= 0) break;
     }
-    if (threadIdx.x == 0) record_decision(sS, pp, ntr, acc_t, acc_f);
+    if (threadIdx.x == 0)
+        record_decision(sS, pp, ntr, acc_t, acc_f, acc_t >= 0 ? step_of(win, pp, sS, sS.ell + acc_t) : 0.0);
     __syncthreads();
 }
 
-// Every workgroup: state of slice s at the start of this launch, in sS.
+// Every workgroup: state of slice s at the start of this launch, in sS, and
+// the steps of the trials from there on, in win.
 // first: the first trial launch (opens the phase from the gradient partials);
 // otherwise the decision of the previous trial launch (`after`: evaluating
 // launches behind this one, -1 in the closing launch).
 template <int BS>
 __device__ inline void derive_state(SliceState &sS, const SliceState *__restrict__ st_in, const PertParams &pp,
                                     int first, const double *__restrict__ part_prev, int s, int nt, double *tot,
-                                    int after = 0)
+                                    StepWindow &win, int after = 0)
 {
     if (threadIdx.x == 0) sS = st_in[s];
     const long long nslots = (long long)pp.B * nt;
     if (first) { // the state's loads overlap the partials' (thread 0 alone reads sS before the barriers)
+        form_steps<BS>(win, pp, st_in[s], 1);
         chunk_totals<BS>(part_prev, nslots, s, nt, 0, 2, tot);
         if (threadIdx.x == 0) open_phase_state(sS, pp, tot[0], tot[1]);
         __syncthreads();
     } else {
         __syncthreads();
-        derive_decision<BS>(sS, pp, part_prev, nslots, s, nt, tot, after);
+        derive_decision<BS>(sS, pp, part_prev, nslots, s, nt, tot, win, after);
     }
 }
 
@@ -2469,6 +2504,7 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x,
     __shared__ double coef[1024];
     __shared__ double tot[kTrialChunk];
     __shared__ SliceState sS;
+    __shared__ StepWindow win;
     constexpr int W = kTrialBlock / 64;
     const int s = blockIdx.y, B = pp.B, nt = gridDim.x;
     const int R = pp.tv_rows, C = pp.tv_cols;
@@ -2488,7 +2524,7 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x,
             pgv = g[((long long)gi * C + gj) * B + s];
         }
     }
-    derive_state<kTrialBlock>(sS, st_in, pp, first, part_prev, s, nt, tot, after);
+    derive_state<kTrialBlock>(sS, st_in, pp, first, part_prev, s, nt, tot, win, after);
     const SliceState &S = sS; // read from LDS (a register copy of the struct spills)
     const bool apply = must_apply(S);
     const int ntr = apply ? 0 : trial_width(S, pp, after);
@@ -2516,7 +2552,7 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x,
     publish_state(S, st_out, s, false);
     const long long nslots = (long long)B * nt, slot = (long long)s * nt + blockIdx.x;
     const double inv_gn = 1.0 / S.gn;
-    for (int t = threadIdx.x; t < ntr; t += kTrialBlock) coef[t] = S.s_acc + trial_beta(pp, S, S.ell + t);
+    for (int t = threadIdx.x; t < ntr; t += kTrialBlock) coef[t] = S.s_acc + step_of(win, pp, S, S.ell + t);
     __syncthreads();
     double x00[4], x10[4], x01[4], v00[4], v10[4], v01[4];
     bool has[4];
@@ -2750,7 +2786,10 @@ __global__ __launch_bounds__(BS) void k_trial_tv_mm(float *__restrict__ x, const
                 need = acc_t < 0 && t0 + nv < ntr;
             }
         }
-        if (threadIdx.x < B && ntr > 0) record_decision(sS[threadIdx.x], pp, ntr, acc_t, acc_f);
+        if (threadIdx.x < B && ntr > 0) {
+            SliceState &D = sS[threadIdx.x];
+            record_decision(D, pp, ntr, acc_t, acc_f, acc_t >= 0 ? trial_beta(pp, D, D.ell + acc_t) : 0.0);
+        }
         __syncthreads();
     }
     const SliceState &S = sS[s];
@@ -2823,7 +2862,8 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_close(float *__restrict__
     __shared__ SliceState sS;
     const int s = blockIdx.y, B = pp.B;
     const bool lin = pp.obj == OBJ_LINEAR;
-    derive_state<kTrialBlock>(sS, st_in, pp, 0, part_prev, s, nt, tot, -1);
+    __shared__ StepWindow win;
+    derive_state<kTrialBlock>(sS, st_in, pp, 0, part_prev, s, nt, tot, win, -1);
     const SliceState &S = sS;
     const bool apply = must_apply(S);
     if (apply) {
@@ -2846,15 +2886,16 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_close(float *__restrict__
 // Wave 0 (all 64 lanes) calls it: lane l values the l-th next trial, the first
 // acceptable one in order is recorded, and so on until the phase is over (0
 // is returned) or a trial's value is not known (the trials the caller has to
-// sum before calling again).  The power law's steps are formed once per 64
-// trials.  Ends: a round accepts a trial, rejects at least one, or returns.
+// sum before calling again).  The power law's steps are those of the window,
+// and formed once per 64 trials beyond it.  Ends: a round accepts a trial, rejects at least one, or returns.
 template <int OBJ>
-__device__ inline int line_trials(SliceState &sS, const PertParams &pp, double f0, double gsq, double least, int most)
+__device__ inline int line_trials(SliceState &sS, const PertParams &pp, const StepWindow &win, double f0, double gsq,
+                                  double least, int most)
 {
     const int l = threadIdx.x & 63;
-    long long base = 0; // beta holds the steps of trials base .. base + 63
-    double beta = 0.0;
-    bool formed = false;
+    long long base = win.base; // beta holds the steps of trials base .. base + 63
+    double beta = win.beta[l];
+    bool formed = !pp.adaptive && sS.ell >= base;
     while (sS.phase) {
         if (!formed || sS.ell - base >= 64) {
             base = sS.ell;
@@ -2877,10 +2918,10 @@ __device__ inline int line_trials(SliceState &sS, const PertParams &pp, double f
         const unsigned long long ok = __ballot(l < nb && known && ft <= sS.f_cur), un = __ballot(l < nb && !known);
         const int a = ok ? __ffsll(ok) - 1 : 64, u = un ? __ffsll(un) - 1 : 64;
         if (u < a) return min(most, left);
-        const double fa = __shfl(ft, a & 63, 64);
+        const double fa = __shfl(ft, a & 63, 64), ba = __shfl(beta, (off + a) & 63, 64);
         __threadfence_block(); // every lane has read the state ...
         __builtin_amdgcn_wave_barrier();
-        if (l == 0) record_decision(sS, pp, nb, a < 64 ? a : -1, fa);
+        if (l == 0) record_decision(sS, pp, nb, a < 64 ? a : -1, fa, ba);
         __threadfence_block(); // ... and reads it anew
         __builtin_amdgcn_wave_barrier();
     }
@@ -2899,8 +2940,9 @@ __device__ inline bool linear_phase(SliceState &sS, const SliceState *__restrict
                                    const double *__restrict__ part, int s, int nt, double *tot,
                                    SliceState *__restrict__ st_out)
 {
-    derive_state<BS>(sS, st_in, pp, 1, part, s, nt, tot);
-    if (threadIdx.x < 64) (void)line_trials<OBJ_LINEAR>(sS, pp, tot[1], tot[0], 0.0, 0);
+    __shared__ StepWindow win;
+    derive_state<BS>(sS, st_in, pp, 1, part, s, nt, tot, win);
+    if (threadIdx.x < 64) (void)line_trials<OBJ_LINEAR>(sS, pp, win, tot[1], tot[0], 0.0, 0);
     __syncthreads();
     const bool apply = must_apply(sS);
     publish_state(sS, st_out, s, apply);
@@ -2946,6 +2988,7 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
     __shared__ double lds[(BS / 64) * T];
     __shared__ double coef[T];
     __shared__ SliceState sS;
+    __shared__ StepWindow win;
     __shared__ int summed; // trials the next batch sums over xc (0: decided in closed form)
     const int s = blockIdx.y, B = pp.B;
     const int n = (int)pp.n;
@@ -2954,17 +2997,17 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
         for (int b = threadIdx.x; b < nt; b += 64) least = fmin(least, part_min[(long long)s * nt + b]);
         for (int off = 32; off > 0; off >>= 1) least = fmin(least, __shfl_xor(least, off, 64));
     }
-    derive_state<BS>(sS, st_in, pp, 1, part, s, nt, tot);
+    derive_state<BS>(sS, st_in, pp, 1, part, s, nt, tot, win);
     const double gsq = tot[0], f0 = tot[1];
     while (sS.phase) { // sS changes only in wave 0, between barriers
         if (threadIdx.x < 64) {
-            const int ns = line_trials<OBJ>(sS, pp, f0, gsq, least, T);
+            const int ns = line_trials<OBJ>(sS, pp, win, f0, gsq, least, T);
             if (threadIdx.x == 0) summed = ns;
         }
         __syncthreads();
         const int ntr = summed;
         if (ntr > 0) {
-            if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + trial_beta(pp, sS, sS.ell + threadIdx.x);
+            if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + step_of(win, pp, sS, sS.ell + threadIdx.x);
             __syncthreads();
             const double inv_gn = 1.0 / sS.gn;
             double acc[T], cw[T];
@@ -2988,7 +3031,8 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
                         t = w;
                         break;
                     }
-                record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0);
+                record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0,
+                                t >= 0 ? step_of(win, pp, sS, sS.ell + t) : 0.0);
             }
         }
         __syncthreads();
@@ -3016,9 +3060,10 @@ __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, co
     __shared__ double lds[4 * kTrialChunk];
     __shared__ double tot[kTrialChunk];
     __shared__ SliceState sS;
+    __shared__ StepWindow win;
     const int s = blockIdx.y, B = pp.B, nt = gridDim.x;
     const bool lin = pp.obj == OBJ_LINEAR;
-    derive_state<kBlock>(sS, st_in, pp, first, part_prev, s, nt, tot, after);
+    derive_state<kBlock>(sS, st_in, pp, first, part_prev, s, nt, tot, win, after);
     const SliceState &S = sS; // read from LDS (a register copy of the struct spills)
     if (must_apply(S)) {
         const double inv_gn = 1.0 / S.gn;
@@ -3034,7 +3079,7 @@ __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, co
     if (ntr == 0) return;
     const long long nslots = (long long)B * nt, slot = (long long)s * nt + blockIdx.x;
     const double inv_gn = 1.0 / S.gn;
-    for (int t = threadIdx.x; t < ntr; t += kBlock) coef[t] = S.s_acc + trial_beta(pp, S, S.ell + t);
+    for (int t = threadIdx.x; t < ntr; t += kBlock) coef[t] = S.s_acc + step_of(win, pp, S, S.ell + t);
     __syncthreads();
     for (int t0 = 0; t0 < ntr; t0 += kTrialChunk) {
         double acc[kTrialChunk];
@@ -3081,12 +3126,14 @@ __global__ __launch_bounds__(kSmallPhaseBlock) void k_phase_small(float *__restr
     __shared__ double coef[T];
     __shared__ double open[3]; // sum g^2, f(x^k), least nonzero |x_j|
     __shared__ SliceState sS;
+    __shared__ StepWindow win;
     __shared__ int summed;
     const int s = blockIdx.y, B = pp.B, n = (int)pp.n;
     float *xs = reinterpret_cast<float *>(phase_lds);
     float *gs = xs + n;
     if (threadIdx.x == 0) sS = st_in[s];
     double v[2] = {0.0, 0.0}, least = INFINITY; // sum g^2, f(x^k)
+    if (n < BS) form_steps<BS>(win, pp, st_in[s], 1); // else between the last wave's loads and their use
     for (int j0 = threadIdx.x; j0 < n; j0 += U * BS) {
         float xf[U], cf[U];
 #pragma unroll
@@ -3095,6 +3142,7 @@ __global__ __launch_bounds__(kSmallPhaseBlock) void k_phase_small(float *__restr
             xf[u] = x[(long long)j * B + s];
             if constexpr (OBJ == OBJ_LINEAR) cf[u] = lin_c[j];
         }
+        if (n >= BS && j0 < BS) form_steps<BS>(win, pp, st_in[s], 1);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int j = j0 + u * BS;
@@ -3135,13 +3183,13 @@ __global__ __launch_bounds__(kSmallPhaseBlock) void k_phase_small(float *__restr
     __syncthreads();
     while (sS.phase) { // sS changes only in wave 0, between barriers
         if (threadIdx.x < 64) {
-            const int ns = line_trials<OBJ>(sS, pp, open[1], open[0], open[2], T);
+            const int ns = line_trials<OBJ>(sS, pp, win, open[1], open[0], open[2], T);
             if (threadIdx.x == 0) summed = ns;
         }
         __syncthreads();
         const int ntr = summed;
         if (ntr > 0) { // L1 only
-            if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + trial_beta(pp, sS, sS.ell + threadIdx.x);
+            if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + step_of(win, pp, sS, sS.ell + threadIdx.x);
             __syncthreads();
             const double inv_gn = 1.0 / sS.gn;
             double acc[T], cw[T];
@@ -3164,7 +3212,8 @@ __global__ __launch_bounds__(kSmallPhaseBlock) void k_phase_small(float *__restr
                         t = w;
                         break;
                     }
-                record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0);
+                record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0,
+                                t >= 0 ? step_of(win, pp, sS, sS.ell + t) : 0.0);
             }
         }
         __syncthreads();
