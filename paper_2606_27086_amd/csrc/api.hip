@@ -88,6 +88,23 @@ struct DBuf {
     }
 };
 
+// Pinned host memory that kernels write (dev: its device address).
+struct HBuf {
+    void *p = nullptr, *dev = nullptr;
+    HBuf() = default;
+    HBuf(const HBuf &) = delete;
+    HBuf &operator=(const HBuf &) = delete;
+    ~HBuf()
+    {
+        if (p) (void)hipHostFree(p);
+    }
+    void alloc(size_t b, const char *what)
+    {
+        hip_check(hipHostMalloc(&p, b, hipHostMallocMapped), what);
+        hip_check(hipHostGetDevicePointer(&dev, p, 0), what);
+    }
+};
+
 inline int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
 // One row-aligned layout on the host before upload.
@@ -280,7 +297,8 @@ struct smx_problem {
     float lambda = 1.f;
     int refine_iters = -1;
     PertParams pp{};
-    DBuf x, g, c, lower, upper, box_lo, box_hi, lin_c, w, D32, D16, st, qout;
+    DBuf x, g, c, lower, upper, box_lo, box_hi, lin_c, w, D32, D16, st;
+    HBuf qout; // query: proximity [B], objective [B]
     DBuf part_pass, part_query, part_phase, part_trial[2]; // per-workgroup partial sums of each kernel kind
     int cur = 0; // which of the two state buffers (st holds 2*B states) is current
     bool tuned = false;
@@ -372,7 +390,7 @@ struct smx_problem {
     size_t device_bytes() const
     {
         size_t t = 0;
-        for (const DBuf *b : {&x, &g, &c, &lower, &upper, &box_lo, &box_hi, &lin_c, &w, &D32, &D16, &st, &qout,
+        for (const DBuf *b : {&x, &g, &c, &lower, &upper, &box_lo, &box_hi, &lin_c, &w, &D32, &D16, &st,
                               &part_pass, &part_query, &part_phase, &part_trial[0], &part_trial[1], &h_prox, &h_fs,
                               &h_fe, &h_tr, &h_ac, &ypart, &part_lin, &S32, &S16, &ybuf, &ybuf32, &part_y, &part_q,
                               &ypanel,
@@ -1360,7 +1378,6 @@ size_t problem_plan_bytes(int64_t m, int64_t n, int64_t nnz, bool has_f32, int l
     add(8 * pgrid * B * 2);
     add(8 * pgrid * B * trials);
     add(8 * pgrid * B * trials);
-    add(8 * 2 * B); // query output
     if (d->history_cap > 0) {
         const size_t hc = size_t(d->history_cap) * B;
         for (int k = 0; k < 3; ++k) add(8 * hc);
@@ -2255,7 +2272,6 @@ int smx_query(smx_problem *p, double *proximity, double *objective)
         const int vk = p->op->has_f32 ? VK_F32 : p->op->lp_kind();
         RowW qw = p->row_weights(vk); // the proximity terms D t^2 (c is scratch here)
         qw.S = qw.D;
-        double *q = p->qout.as<double>();
         hip_check(launch_pass1(p->cfg1[vk], view_for(p->op, false, p->fmt1[vk]), p->op->csr.blocks(), p->fmt1[vk],
                                p->x.as<float>(), p->lower.as<float>(), p->upper.as<float>(), qw,
                                p->c.as<float>(),
@@ -2263,24 +2279,20 @@ int smx_query(smx_problem *p, double *proximity, double *objective)
                                p->part_query.as<double>(), p->stream),
                   "query proximity");
         if (p->dvc.n > 0) p->enqueue_dvc(vk, p->part_query.as<double>(), p->cfg1[vk].grid, p->cur, 1, p->stream);
-        hip_check(launch_query_prox(p->state(p->cur), B, p->part_query.as<double>(), p->cfg1[vk].grid, q,
-                                    p->stream),
-                  "query proximity");
-        std::vector<double> h(2 * B, 0.0);
-        if (p->pp.obj != OBJ_NONE) {
+        const bool obj = p->pp.obj != OBJ_NONE;
+        if (obj)
             hip_check(launch_phase(p->pp, p->x.as<float>(), p->g.as<float>(), p->lin_c.as<float>(),
                                    p->state(p->cur), 1, p->part_phase.as<double>(), p->stream),
                       "query objective");
-            hip_check(launch_eval_objective(p->state(p->cur), p->pp, p->part_phase.as<double>(), q + B, p->stream),
-                      "query objective");
-            hip_check(hipMemcpyAsync(h.data(), q, sizeof(double) * 2 * B, hipMemcpyDeviceToHost, p->stream), "query");
-        } else {
-            hip_check(hipMemcpyAsync(h.data(), q, sizeof(double) * B, hipMemcpyDeviceToHost, p->stream), "query");
-        }
+        hip_check(launch_query_out(p->state(p->cur), p->pp, p->part_query.as<double>(), p->cfg1[vk].grid,
+                                   obj ? p->part_phase.as<double>() : nullptr, static_cast<double *>(p->qout.dev),
+                                   p->stream),
+                  "query");
         hip_check(hipStreamSynchronize(p->stream), "query");
+        const double *h = static_cast<const double *>(p->qout.p);
         for (int s = 0; s < B; ++s) {
             if (proximity) proximity[s] = h[s];
-            if (objective) objective[s] = h[B + s];
+            if (objective) objective[s] = obj ? h[B + s] : 0.0;
         }
         return SMX_OK;
     })

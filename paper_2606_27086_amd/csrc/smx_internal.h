@@ -386,9 +386,6 @@ hipError_t prepare_fused(const FusedCfg &cfg, int vk, int64_t n);
 hipError_t launch_dvc(const DvcTable &T, const double *dose, const DvcScratch &W, const float *D, const float *S,
                       float *c, double *part1, int nparts1, const SliceState *st, int B, int query, hipStream_t s);
 
-// query: proximity from pass 1's partials into out[B]
-hipError_t launch_query_prox(SliceState *st, int B, const double *partials, int nparts, double *out, hipStream_t s);
-
 int phase_grid(const PertParams &pp);
 // gradient and per-tile partials [2][B*tiles] of ||g||^2 and f(x) (eval_only: no gradient)
 // (part_min, squared norm and L1: g gets a copy of x, part_min B*tiles minima of the nonzero |x_j|)
@@ -400,9 +397,10 @@ hipError_t launch_phase(const PertParams &pp, const float *x, float *g, const fl
 bool phase_on_line(const PertParams &pp);
 hipError_t launch_trial_line(const PertParams &pp, float *x, const float *xc, const SliceState *st_in,
                              SliceState *st_out, const double *part_phase, const double *part_min, hipStream_t s);
-// f(x) per slice from eval_only phase partials into out[B]
-hipError_t launch_eval_objective(SliceState *st, const PertParams &pp, const double *partials, double *out,
-                                 hipStream_t s);
+// query: per slice the proximity from pass 1's partials into out[B], and f(x)
+// from eval_only phase partials (part_obj, may be null) into out[B .. 2B - 1]
+hipError_t launch_query_out(SliceState *st, const PertParams &pp, const double *part_prox, int nparts,
+                            const double *part_obj, double *out, hipStream_t s);
 // One trial launch: derives the state (first: the phase opening from the
 // gradient partials; otherwise the previous launch's decision from its trial
 // partials), then the next batch of trial steps (partials
