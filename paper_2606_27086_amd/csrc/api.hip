@@ -1396,13 +1396,26 @@ void setup_fused(smx_problem *p)
     if (!fused_plan(p->m, p->n, p->op->nnz, p->B, p->dvc.n, c, bytes)) return;
     const DevLayout &L = p->op->csr;
     const double mean = L.rows > 0 ? double(L.slots) / double(L.rows) : 0.0;
-    c.lpr = mean <= 64 ? 8 : (mean <= 256 ? 16 : 32);
+    const int partials = c.grid; // of the largest grid
     const bool dvc = p->dvc.n > 0;
-    if (dvc) { // z in LDS: two sets of float32 partials fit the float64 plan's bytes
+    // z in LDS beside a float64 y wherever both fit: a row then reads z from LDS
+    // instead of gathering it from L2 (untuned shapes, pass and step: 4,332 rows
+    // of 324 columns 10.3 us against 14.8; 6,293 columns in bfloat16 35 against
+    // 62).  Eight or sixteen lanes of 8 entries were within 10 % of the fastest
+    // shape on each.  Up to 256 columns z is a few cache lines that stay in L1,
+    // and staging it costs more than it saves (256 x 128 dense, 40 iterations:
+    // 596 us against 570).  Only the tuner gives a float64 y up for z in LDS
+    if (dvc || (p->n > 256 && fused_zl_lds_bytes(p->n, 1) <= fused_lds_limit())) {
         c.zl = 1;
         c.acc64 = fused_zl_lds_bytes(p->n, 1) <= fused_lds_limit() ? 1 : 0;
-        c.out32 = 1;
-        c.lpr = 8;
+        c.out32 = dvc ? 1 : 0; // two sets of float32 partials fit the float64 plan's bytes
+        c.lpr = mean <= 64 ? 8 : 16;
+        c.vec = 8;
+        c.cap = c.acc64 ? fused_zl_cap(c.lpr, c.vec) : 0; // a float32 y is added to faster from entries read again
+        c.grid = p->n > 2048 ? c.cus : c.most;
+    } else {
+        // 32 lanes also where a workgroup has fewer rows than groups of 16 lanes
+        c.lpr = mean <= 64 ? 8 : (mean <= 256 && p->m > 32 * int64_t(c.grid) ? 16 : 32);
     }
     bool any = false;
     for (int vk = 0; vk < 3; ++vk) {
@@ -1417,7 +1430,7 @@ void setup_fused(smx_problem *p)
         p->fcfg[vk] = c;
         any = any || ok;
     }
-    if (any) p->ypart.alloc(bytes * size_t(c.grid), "fused partial vectors");
+    if (any) p->ypart.alloc(bytes * size_t(partials), "fused partial vectors");
     if (any && p->pp.obj == OBJ_LINEAR) // the next phase's direction partials, from the apply kernel
         p->part_lin.alloc(sizeof(double) * 2 * size_t(fused_apply_grid(p->n)), "direction partials");
 }
