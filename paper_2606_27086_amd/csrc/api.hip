@@ -831,7 +831,7 @@ hipError_t pass2_any(const smx_problem *p, int vk, const PassCfg &c, const float
 // the iteration into the other state buffer.  nparts1: partials of pass 1 (or
 // the fused pass), nparts_y: partials of ||y||^2.
 void enqueue_extrapolated_step(smx_problem *p, int vk, const RowW &rw, int nparts1, int nparts_y, int cur,
-                               hipStream_t s)
+                               hipStream_t s, bool lin = false, bool lin_z = false)
 {
     const bool emr = p->basic == SMX_BASIC_EMR;
     if (emr)
@@ -842,16 +842,17 @@ void enqueue_extrapolated_step(smx_problem *p, int vk, const RowW &rw, int npart
     hip_check(launch_step_apply(p->n, p->B, p->ybuf.as<double>(), p->x.as<float>(), p->box_lo.as<float>(),
                                 p->box_hi.as<float>(), p->lambda, emr ? 1 : 0, p->part_pass.as<double>(), nparts1,
                                 p->part_y.as<double>(), nparts_y, p->part_q.as<double>(), p->cfg1[vk].grid,
-                                p->state(cur), p->state(cur ^ 1), p->hist, s),
+                                p->state(cur), p->state(cur ^ 1), p->hist, s,
+                                lin ? p->lin_c.as<float>() : nullptr, lin ? p->part_lin.as<double>() : nullptr,
+                                lin_z ? 1 : 0),
               "extrapolated step");
 }
 
-// Whether the fused pass is in use (for a value kind that runs) with the step
-// applied in its apply kernel, which then leaves the linear objective's
-// direction partials.
+// Whether the fused pass is in use (for a value kind that runs): the kernel
+// that applies its step then leaves the linear objective's direction partials.
 bool lin_partials_from_apply(const smx_problem *p)
 {
-    if (p->basic == SMX_BASIC_EL || p->basic == SMX_BASIC_EMR || !p->part_lin.p) return false;
+    if (!p->part_lin.p) return false;
     const int lp = p->op->lp_kind();
     return lp != VK_F32 ? p->fused[lp] : p->fused[VK_F32];
 }
@@ -903,12 +904,18 @@ int phase_flips(const smx_problem *p)
 }
 
 // Whether iterations of value kind vk take the linear objective's direction
-// partials from the previous iteration's apply kernel (fused pass, the step
-// applied there), so that the phase is the one closed-form launch.
+// partials from the kernel that applied the previous iteration's step (fused
+// pass), so that the phase is the one closed-form launch.
 bool lin_from_apply(const smx_problem *p, int vk)
 {
+    return phase_kind(p) == PHASE_LINEAR && p->fused[vk] && p->part_lin.p;
+}
+
+// Slots of those partials: workgroups of the kernel that applies the step.
+int lin_slots(const smx_problem *p)
+{
     const bool extrap = p->basic == SMX_BASIC_EL || p->basic == SMX_BASIC_EMR;
-    return phase_kind(p) == PHASE_LINEAR && p->fused[vk] && !extrap && p->part_lin.p;
+    return extrap ? step_apply_grid(p->n, 1) : fused_apply_grid(p->n);
 }
 
 // Whether iterations of value kind vk take that phase inside the fused pass
@@ -949,8 +956,7 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
     } else if (perturb && p->pp.obj != OBJ_NONE && pk == PHASE_LINEAR) {
         if (lin_from_apply(p, vk)) { // the partials of x^k came from the last apply (or the run's start)
             hip_check(launch_trial_linear(p->pp, p->x.as<float>(), p->lin_c.as<float>(), p->state(cur),
-                                          p->state(cur ^ 1), p->part_lin.as<double>(), s,
-                                          fused_apply_grid(p->n)),
+                                          p->state(cur ^ 1), p->part_lin.as<double>(), s, lin_slots(p)),
                       "linear phase");
         } else {
             hip_check(launch_phase(p->pp, p->x.as<float>(), p->g.as<float>(), p->lin_c.as<float>(), p->state(cur), 0,
@@ -1007,7 +1013,7 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
         if (lin_pass) {
             lp.c = p->lin_c.as<float>();
             lp.part = p->part_lin.as<double>();
-            lp.nparts = fused_apply_grid(p->n);
+            lp.nparts = lin_slots(p);
             lp.st_out = p->state(cur ^ 1);
             lp.pp = p->pp;
         }
@@ -1028,14 +1034,15 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
             nvec += sg;
         }
         if (timed) hip_check(hipEventRecord(e[2], s), "event");
-        const bool lin = lin_from_apply(p, vk);
+        const bool lin = lin_from_apply(p, vk), lin_here = lin && !extrap; // else k_step_apply moves x
         hip_check(launch_fused_apply(p->fcfg[vk], p->n, p->ypart.p, nvec, p->x.as<float>(), p->col_step(extrap),
                                      p->state(cur), p->state(cur ^ 1), p->part_pass.as<double>(), p->hist, s,
-                                     lin ? p->lin_c.as<float>() : nullptr, lin ? p->part_lin.as<double>() : nullptr,
-                                     lin_pass ? 1 : 0),
+                                     lin_here ? p->lin_c.as<float>() : nullptr,
+                                     lin_here ? p->part_lin.as<double>() : nullptr, lin_here && lin_pass ? 1 : 0),
                   "fused apply");
         if (timed) hip_check(hipEventRecord(e[3], s), "event");
-        if (extrap) enqueue_extrapolated_step(p, vk, rw, p->fcfg[vk].grid, fused_apply_grid(p->n), cur, s);
+        if (extrap)
+            enqueue_extrapolated_step(p, vk, rw, p->fcfg[vk].grid, fused_apply_grid(p->n), cur, s, lin, lin_pass);
         cur ^= 1;
         return cur;
     }
@@ -1134,7 +1141,7 @@ int run_impl(smx_problem *p, int32_t K, uint32_t flags)
         // the first phase of the run of iterations needs its direction partials of x
         if (perturb && lin_from_apply(p, vk))
             hip_check(launch_lin_partials(p->x.as<float>(), p->lin_c.as<float>(), p->n, p->part_lin.as<double>(),
-                                          p->stream),
+                                          lin_slots(p), p->stream),
                       "direction partials");
         if (graph) {
             while (left > 0) {

@@ -1694,7 +1694,11 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
 // twice pass 1's proximity sum; EMR: ||y||^2 / sum_i w_i (A y)_i^2), 0 when the
 // denominator is 0 or the quotient is not finite; then
 // x = clip(z + lambda sigma y, lo, hi).  One more workgroup, the last, closes
-// the iteration.
+// the iteration.  lin_c (one slice, linear objective): the pass took the phase
+// and x still holds x^k where lin_z is set, so z_j is formed here, and the
+// workgroups' partials of the next phase's direction go to lin_part, as
+// k_fused_apply's do for the steps it applies (5,625 columns, dose-volume
+// rows: 113.1 us an iteration, 115.2 with the phase in a launch of its own).
 __global__ __launch_bounds__(kBlock) void k_step_apply(int n, int B, const double *__restrict__ y,
                                                        float *__restrict__ x, const float *__restrict__ lo,
                                                        const float *__restrict__ hi, float lambda, int emr,
@@ -1702,9 +1706,11 @@ __global__ __launch_bounds__(kBlock) void k_step_apply(int n, int B, const doubl
                                                        const double *__restrict__ party, int npartsy,
                                                        const double *__restrict__ partq, int npartsq,
                                                        const SliceState *__restrict__ st_in,
-                                                       SliceState *__restrict__ st_out, Hist h)
+                                                       SliceState *__restrict__ st_out, Hist h,
+                                                       const float *__restrict__ lin_c, double *__restrict__ lin_part,
+                                                       int lin_z)
 {
-    __shared__ double lds[4];
+    __shared__ double lds[4 * 2];
     __shared__ double sigma[32];
     __shared__ int live[32];
     const int groups = (int)gridDim.x - 1;
@@ -1728,6 +1734,28 @@ __global__ __launch_bounds__(kBlock) void k_step_apply(int n, int B, const doubl
         }
     }
     __syncthreads();
+    if (lin_c) {
+        const bool zstep = lin_z && st_in[0].applied && st_in[0].s_acc != 0.0;
+        const double zs = zstep ? st_in[0].s_acc : 0.0, zinv = zstep ? 1.0 / st_in[0].gn : 0.0;
+        double v[2] = {0.0, 0.0}; // sum c^2, c^T x
+        for (int j = blockIdx.x * kBlock + (int)threadIdx.x; j < n; j += groups * kBlock) {
+            const float cj = lin_c[j];
+            float xj = x[j];
+            if (live[0]) {
+                const float zj = zstep ? linear_step_point(xj, cj, zs, zinv) : xj;
+                xj = (float)fmin(fmax(fma((double)lambda * sigma[0], y[j], (double)zj), (double)lo[j]), (double)hi[j]);
+                x[j] = xj;
+            }
+            v[0] += (double)cj * (double)cj;
+            v[1] += (double)cj * (double)xj;
+        }
+        block_sum<2>(v, lds);
+        if (threadIdx.x == 0) {
+            lin_part[blockIdx.x] = v[0];
+            lin_part[groups + blockIdx.x] = v[1];
+        }
+        return;
+    }
     const long long total = (long long)n * B;
     for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < total; e += (long long)groups * kBlock) {
         const int s = (int)(e % B);
@@ -4476,11 +4504,10 @@ hipError_t launch_fused_apply(const FusedCfg &cfg, int64_t n, const void *ypart,
     return hipGetLastError();
 }
 
-hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, hipStream_t s)
+hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, int groups, hipStream_t s)
 {
-    if (n < 1 || !x || !c || !part) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_lin_partials, dim3((unsigned)fused_apply_grid(n)), dim3(kApplyBlock), 0, s, x, c, (int)n,
-                       part);
+    if (n < 1 || groups < 1 || !x || !c || !part) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_lin_partials, dim3((unsigned)groups), dim3(kApplyBlock), 0, s, x, c, (int)n, part);
     return hipGetLastError();
 }
 
@@ -4527,15 +4554,18 @@ hipError_t launch_scatter_rows(const SpView &A, int vk, int64_t n, long long r_l
     return scatter_rows_dispatch(0, A, vk, n, r_lo, r_hi, c, st, ypart, grid, s);
 }
 
+int step_apply_grid(int64_t n, int B) { return (int)grid_for(n * B, kBlock, 2048); }
+
 hipError_t launch_step_apply(int64_t n, int B, const double *y, float *x, const float *lo, const float *hi,
                              float lambda, int emr, const double *part1, int nparts1, const double *party, int npartsy,
                              const double *partq, int npartsq, const SliceState *st_in, SliceState *st_out, Hist h,
-                             hipStream_t s)
+                             hipStream_t s, const float *lin_c, double *lin_part, int lin_z)
 {
     if (n < 1 || B < 1 || B > 32 || nparts1 < 1 || npartsy < 1 || (emr && npartsq < 1)) return hipErrorInvalidValue;
-    const unsigned grid = grid_for(n * B, kBlock, 2048) + 1; // the last closes the iteration
+    if (lin_c ? (B != 1 || !lin_part) : (lin_part || lin_z)) return hipErrorInvalidValue;
+    const unsigned grid = (unsigned)step_apply_grid(n, B) + 1; // the last closes the iteration
     hipLaunchKernelGGL(k_step_apply, dim3(grid), dim3(kBlock), 0, s, (int)n, B, y, x, lo, hi, lambda, emr, part1,
-                       nparts1, party, npartsy, partq, npartsq, st_in, st_out, h);
+                       nparts1, party, npartsy, partq, npartsq, st_in, st_out, h, lin_c, lin_part, lin_z);
     return hipGetLastError();
 }
 

@@ -330,10 +330,13 @@ inline bool tiles_fit(int max_rows, int B) { return int64_t(max_rows) * B * 4 <=
 // per slice from the partials: EL (emr = 0) t^T D t / ||y||^2 from pass 1's
 // and pass 2's partials, EMR (emr = 1) ||y||^2 / sum w (A y)^2 from pass 2's and
 // the quadratic-form pass's; closes the iteration.
+// (lin_c, lin_part, lin_z as for launch_fused_apply, step_apply_grid slots)
+int step_apply_grid(int64_t n, int B);
 hipError_t launch_step_apply(int64_t n, int B, const double *y, float *x, const float *lo, const float *hi,
                              float lambda, int emr, const double *part1, int nparts1, const double *party, int npartsy,
                              const double *partq, int npartsq, const SliceState *st_in, SliceState *st_out, Hist h,
-                             hipStream_t s);
+                             hipStream_t s,
+                             const float *lin_c = nullptr, double *lin_part = nullptr, int lin_z = 0);
 // fused pass over the CSR: r = A z, t, c = D t, the proximity partial per
 // workgroup, and one partial vector of y = A^T c per workgroup in ypart
 // (grid x n, float64 or float32 by cfg.acc64).  lds_bytes: dynamic LDS it needs.
@@ -365,8 +368,8 @@ hipError_t launch_fused_apply(const FusedCfg &cfg, int64_t n, const void *ypart,
                               const SliceState *st_in, SliceState *st_out, const double *part1, Hist h,
                               hipStream_t s, const float *lin_c = nullptr, double *lin_part = nullptr,
                               int lin_z = 0);
-// the same direction partials of x alone (one slice)
-hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, hipStream_t s);
+// the same direction partials of x alone (one slice; `groups` slots)
+hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, int groups, hipStream_t s);
 // y partials of rows [r_lo, r_hi) whose c is set (the dose-volume rows of a
 // fused-pass problem, after their ranking): grid float32 vectors of n at ypart
 hipError_t prepare_scatter_rows(int vk, int64_t n);

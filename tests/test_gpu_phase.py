@@ -93,6 +93,38 @@ def test_linear_phase_in_the_apply_kernel(smx, m, n):
     check_iteration(smx, w.with_params(gamma=3.0, alpha=0.9, n_red=2))
 
 
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("basic", [W.BASIC_EL, W.BASIC_EMR])
+@pytest.mark.parametrize("m,n", [(5, 3), (300, 255), (300, 257), (900, 8193), (2500, 13000), (400, 30000)])
+def test_linear_phase_with_extrapolated_steps(smx, m, n, basic, graph):
+    """Linear objective with EL and EMR: the launch that moves x leaves the next
+    phase's partials (and forms z where the pass took the phase).  Against the
+    one-launch or two-launch phase: the same trials; z to one rounding, so x
+    after one step to 4 units of float32 at the largest entry; and the second
+    phase opens at c^T x of the first result, whose entries are rounded alike
+    to one unit."""
+    w = W.random_sparse(m, n, min(n, 8), seed=m, obj=W.OBJ_LINEAR, K=1)
+    w = w.with_params(gamma=2.0, alpha=0.9, n_red=3, basic=basic)
+    xs, ells, fs = [], [], []
+    for fused in (True, False):
+        p = smx.problem_from_workload(w, fused=fused, history_cap=4)
+        p.run(1, graph=graph)
+        xs.append(p.get_x().cpu().numpy().astype(np.float64)[:, 0])
+        ells.append(p.get_state()[0][0]["ell"])
+        p.reset(w.x0)
+        p.run(2, graph=graph)
+        h = p.history()
+        fs.append(h["f_start"][:, 0])
+        ells.append(tuple(h["trials"][:, 0]))
+        p.close()
+    u = 2.0 ** -24
+    assert ells[:2] == ells[2:]
+    assert np.max(np.abs(xs[0] - xs[1])) <= 8 * u * max(1.0, np.max(np.abs(xs[1])))
+    c = np.asarray(w.linear_c, np.float64)
+    for x, f in zip(xs, fs):
+        assert abs(f[1] - c @ x) <= 2 * u * np.sum(np.abs(c * x)) + 1e-12
+
+
 @pytest.mark.parametrize("B,gamma,alpha", [(1, 200.0, 0.93), (1, 3.0, 0.97), (2, 200.0, 0.93), (1, 1e6, 0.99)])
 def test_tv_phase_with_failing_batches(smx, B, gamma, alpha):
     """Four reduction steps in six trial launches: first batches of 8 that fail
