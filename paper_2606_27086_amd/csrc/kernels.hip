@@ -1586,17 +1586,18 @@ __global__ __launch_bounds__(kFusedRcBlock) void k_fused_rc(SpView A, int n, con
 
 // Direction partials of the linear objective f = c^T x for the next
 // perturbation phase: this workgroup's sums of c_j^2 and c_j x_j over the
-// unknowns j0 + l (l < 64, j0 = 64 blockIdx.x, stepping 64 groups),
+// unknowns j0 + l (l < CW, j0 = CW blockIdx.x, stepping CW groups),
 // added by the first wave's lanes in that order and then over the
 // workgroup, stored as the direction launch's partials would be (slot
 // blockIdx.x of 2 x groups).  k_fused_apply calls it after writing x and
 // k_lin_partials alone, with the same sums in the same order.
+template <int CW>
 __device__ inline void lin_partials_block(const float *__restrict__ x, const float *__restrict__ c, int n,
                                           int groups, double *__restrict__ part, double *lds)
 {
     double v[2] = {0.0, 0.0}; // sum c^2, c^T x
-    if ((threadIdx.x >> 6) == 0)
-        for (int j = blockIdx.x * 64 + (int)threadIdx.x; j < n; j += groups * 64) {
+    if (threadIdx.x < CW)
+        for (int j = blockIdx.x * CW + (int)threadIdx.x; j < n; j += groups * CW) {
             const double cj = (double)c[j];
             v[0] += cj * cj;
             v[1] += cj * (double)x[j];
@@ -1608,19 +1609,25 @@ __device__ inline void lin_partials_block(const float *__restrict__ x, const flo
     }
 }
 
+template <int CW>
 __global__ __launch_bounds__(kApplyBlock) void k_lin_partials(const float *__restrict__ x,
                                                               const float *__restrict__ c, int n,
                                                               double *__restrict__ part)
 {
     __shared__ double lds[kApplyBlock / 64 * 2];
-    lin_partials_block(x, c, n, (int)gridDim.x, part, lds);
+    lin_partials_block<CW>(x, c, n, (int)gridDim.x, part, lds);
 }
 
 // x = clip(z + lambda * Z_j * sum_g ypart[g], lo, hi) (Z_j = 1 unless DROP);
-// 64 unknowns per workgroup, the four waves each sum every fourth partial
-// (loads issued four at a time, added in order) and the four sums are added in
-// a fixed order.  One more workgroup closes the outer iteration.
-template <typename AccT>
+// CW unknowns per workgroup, whose waves' 64 / CW parts each sum every
+// (waves * 64 / CW)th partial (loads issued eight at a time, added in order);
+// a wave's parts are added by shuffles and the waves' sums in a fixed order.
+// One more workgroup closes the outer iteration.  CW = 16 up to 1,024 unknowns,
+// where the launch is a chain of loads over few vectors and a workgroup's
+// share of them the longest link (256 x 128 dense, 40 iterations 534 us
+// against 547 with 64); CW = 64 beyond (6,293 unknowns, 256 vectors: 6.5 us
+// against 7.8 with 16).
+template <typename AccT, int CW>
 __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restrict__ ypart, int G, int n,
                                                         float *__restrict__ x, ColStep cs,
                                                         const SliceState *__restrict__ st_in,
@@ -1629,14 +1636,14 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
                                                         const float *__restrict__ lin_c, double *__restrict__ lin_part,
                                                         int lin_z)
 {
-    __shared__ double red[kApplyBlock / 64][64];
+    __shared__ double red[kApplyBlock / 64][CW];
     __shared__ double lds[kApplyBlock / 64 * 2];
     const int groups = column_groups(cs);
     if ((int)blockIdx.x == groups) { // the same in every thread
         finish_iteration<kApplyBlock>(st_in, st_out, 1, part1, nparts1, h, lds);
         return;
     }
-    const int wid = threadIdx.x >> 6, wl = threadIdx.x & 63;
+    const int wid = threadIdx.x >> 6, wl = threadIdx.x & (CW - 1), part0 = (int)threadIdx.x / CW;
     double ysq = 0.0; // deferred mode: this thread's share of ||y||^2
     // the linear phase taken in the pass: x still holds x^k, z_j is formed here
     bool zstep = false;
@@ -1647,24 +1654,41 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
         zinv = 1.0 / st_in[0].gn;
     }
     if (st_in[0].live) {
-        for (int j0 = blockIdx.x * 64; j0 < n; j0 += groups * 64) {
+        for (int j0 = blockIdx.x * CW; j0 < n; j0 += groups * CW) {
             const int j = j0 + wl;
-            constexpr int W = kApplyBlock / 64;
+            constexpr int W = kApplyBlock / 64, P = kApplyBlock / CW;
             double sum = 0.0;
-            if (j < n) { // wave w adds partials w, w + W, ... (eight loads in flight)
-                int g = wid;
-                for (; g + 7 * W < G; g += 8 * W) {
+            const bool owner = threadIdx.x < CW && j < n;
+            float xo = 0.f, l = 0.f, u0 = 0.f;
+            if (owner && !cs.defer) { // the step's operands, fetched beside the partials
+                xo = x[j];
+                l = cs.lo[j];
+                u0 = cs.hi[j];
+            }
+            if (j < n) { // part p adds partials p, p + P, ... (eight loads in flight, then four)
+                int g = part0;
+                for (; g + 7 * P < G; g += 8 * P) {
                     double v[8];
 #pragma unroll
-                    for (int u = 0; u < 8; ++u) v[u] = (double)ypart[(long long)(g + u * W) * n + j];
+                    for (int u = 0; u < 8; ++u) v[u] = (double)ypart[(long long)(g + u * P) * n + j];
 #pragma unroll
                     for (int u = 0; u < 8; ++u) sum += v[u];
                 }
-                for (; g < G; g += W) sum += (double)ypart[(long long)g * n + j];
+                if (g + 3 * P < G) {
+                    double v[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) v[u] = (double)ypart[(long long)(g + u * P) * n + j];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sum += v[u];
+                    g += 4 * P;
+                }
+                for (; g < G; g += P) sum += (double)ypart[(long long)g * n + j];
             }
-            red[wid][wl] = sum;
+#pragma unroll
+            for (int off = CW; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+            if ((threadIdx.x & 63) < CW) red[wid][wl] = sum;
             __syncthreads();
-            if (wid == 0 && j < n) {
+            if (owner) {
                 double yv = 0.0;
 #pragma unroll
                 for (int w = 0; w < W; ++w) yv += red[w][wl];
@@ -1674,9 +1698,9 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
                     ysq += yv * yv;
                 } else {
                     if (cs.zcol) yv *= (double)cs.zcol[j];
-                    const float zj = zstep ? linear_step_point(x[j], lin_c[j], zs, zinv) : x[j];
+                    const float zj = zstep ? linear_step_point(xo, lin_c[j], zs, zinv) : xo;
                     const double z = fma((double)cs.lambda, yv, (double)zj);
-                    x[j] = (float)fmin(fmax(z, (double)cs.lo[j]), (double)cs.hi[j]);
+                    x[j] = (float)fmin(fmax(z, (double)l), (double)u0);
                 }
             }
             __syncthreads();
@@ -1684,7 +1708,7 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
     }
     // the next phase's direction partials from the x just written (each
     // lane rereads its own entries)
-    if (lin_part) lin_partials_block(x, lin_c, n, groups, lin_part, lds);
+    if (lin_part) lin_partials_block<CW>(x, lin_c, n, groups, lin_part, lds);
     end_columns<kApplyBlock>(cs, ysq, lds);
 }
 
@@ -4358,7 +4382,8 @@ size_t fused_zl_lds_bytes(int64_t n, int acc64)
     return size_t((n + 3) & ~int64_t(3)) * (sizeof(float) + (acc64 ? sizeof(double) : sizeof(float)));
 }
 
-int fused_apply_grid(int64_t n) { return (int)grid_for(n, 64, 4096); }
+static inline int fused_apply_cols(int64_t n) { return n <= 1024 ? 16 : 64; } // unknowns of a workgroup
+int fused_apply_grid(int64_t n) { return (int)grid_for(n, fused_apply_cols(n), 4096); }
 
 size_t fused_lds_limit()
 {
@@ -4494,20 +4519,27 @@ hipError_t launch_fused_apply(const FusedCfg &cfg, int64_t n, const void *ypart,
     if (cfg.grid < 1 || cfg.grid > kMaxPassGrid || n < 1 || nvec < cfg.grid || nvec > 2 * cfg.grid ||
         (wide && nvec != cfg.grid) || (lin_part && (!lin_c || cs.defer)) || (lin_z && (!lin_c || cs.defer)))
         return hipErrorInvalidValue;
-    const unsigned grid = column_grid(fused_apply_grid(n), cs);
-    if (wide)
-        hipLaunchKernelGGL(k_fused_apply<double>, dim3(grid), dim3(kApplyBlock), 0, s, static_cast<const double *>(ypart),
-                           nvec, (int)n, x, cs, st_in, st_out, part1, cfg.grid, h, lin_c, lin_part, lin_z);
-    else
-        hipLaunchKernelGGL(k_fused_apply<float>, dim3(grid), dim3(kApplyBlock), 0, s, static_cast<const float *>(ypart),
-                           nvec, (int)n, x, cs, st_in, st_out, part1, cfg.grid, h, lin_c, lin_part, lin_z);
+    const dim3 grid(column_grid(fused_apply_grid(n), cs)), block(kApplyBlock);
+    auto go = [&](auto kern, auto *vectors) {
+        hipLaunchKernelGGL(kern, grid, block, 0, s, vectors, nvec, (int)n, x, cs, st_in, st_out, part1, cfg.grid, h,
+                           lin_c, lin_part, lin_z);
+    };
+    const bool few = fused_apply_cols(n) == 16;
+    if (wide) {
+        const double *v = static_cast<const double *>(ypart);
+        few ? go(k_fused_apply<double, 16>, v) : go(k_fused_apply<double, 64>, v);
+    } else {
+        const float *v = static_cast<const float *>(ypart);
+        few ? go(k_fused_apply<float, 16>, v) : go(k_fused_apply<float, 64>, v);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, int groups, hipStream_t s)
 {
     if (n < 1 || groups < 1 || !x || !c || !part) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_lin_partials, dim3((unsigned)groups), dim3(kApplyBlock), 0, s, x, c, (int)n, part);
+    auto kern = fused_apply_cols(n) == 16 ? k_lin_partials<16> : k_lin_partials<64>;
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kApplyBlock), 0, s, x, c, (int)n, part);
     return hipGetLastError();
 }
 

@@ -84,7 +84,8 @@ def test_phase_on_the_line_ends_at_the_trial_cap(smx):
         assert st[0]["trials"] == 21 and st[0]["accepts"] == 0 and st[0]["cap_hits"] == 1
 
 
-@pytest.mark.parametrize("m,n", [(1, 2), (70, 63), (4097, 65), (16500, 324), (300, 2049), (200, 8192)])
+@pytest.mark.parametrize("m,n", [(1, 2), (64, 17), (70, 63), (4097, 65), (16500, 324), (500, 1024), (500, 1025),
+                                 (300, 2049), (200, 8192)])
 def test_linear_phase_in_the_apply_kernel(smx, m, n):
     """Linear objective below n = 8,192: the phase in closed form from the
     partials that the fused pass leaves, and grids at both ends of the rule on
