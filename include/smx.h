@@ -494,15 +494,16 @@ int smx_set_fused(smx_problem *p, int32_t mode);
  *     launch (f(x^k), ||c||), then one launch in which every workgroup takes
  *     each trial's value from f(x + t v) = f(x) - t ||c|| (v = -c/||c||), so
  *     no trial needs a pass over x, and adds the accepted step.  On the
- *     fused pass (not EL or EMR) the previous iteration's apply kernel
- *     leaves the direction's partial sums, so the direction launch goes;
+ *     fused pass the launch that moves x leaves the direction's partial
+ *     sums for the next iteration, so the direction launch goes;
  *     with z in LDS the pass itself opens the phase and stages
  *     z = x + s v, and the phase takes no launch of its own;
- *   SMX_PHASE_AUTO (the default): ONE_LAUNCH for those objectives up to
- *     n = 8,192 (there the chain of launches, not the arithmetic, sets the
- *     phase's time; one workgroup reads x at one compute unit's rate, so on
- *     longer vectors it is no faster than the chain), else CLOSED_FORM for
- *     the linear objective, else, for the squared norm and for L1 up to n =
+ *   SMX_PHASE_AUTO (the default): CLOSED_FORM for the linear objective on
+ *     the fused pass, else ONE_LAUNCH for those objectives up to n = 8,192
+ *     (there the chain of launches, not the arithmetic, sets the phase's
+ *     time; one workgroup reads x at one compute unit's rate, so on longer
+ *     vectors it is no faster than the chain), else CLOSED_FORM for the
+ *     linear objective, else, for the squared norm and for L1 up to n =
  *     131,072, a direction launch and one launch that takes each trial's
  *     value from f along the line x + t v (the squared norm in closed form;
  *     L1 in closed form while no entry changes sign, by summation beyond),
@@ -521,8 +522,8 @@ int smx_set_phase_form(smx_problem *p, int32_t form);
  * cap: 0 to read a row's entries again for the scatter, or 256/(lpr*vec) (16
  * or 32 lanes only) to keep 256 entries of each row in registers.  With
  * z_in_lds != 0 (problems whose n is at most about 20k): every workgroup
- * first copies the whole point z into LDS beside a float32 copy of y and
- * gathers from there instead of from memory; cap is then 0 or 16/vec (each
+ * first copies the whole point z into LDS beside its y (float64 where 12n
+ * bytes fit, else float32) and gathers from there instead of from memory; cap is then 0 or 16/vec (each
  * lane keeps 16 entries of its row in registers for the scatter).
  * Results do not depend on the shape beyond floating-point summation order.
  * Errors: SMX_ESTATE when the problem has no fused pass, SMX_EINVAL for

@@ -1333,7 +1333,9 @@ __device__ inline int first_row_at(const int *__restrict__ ptr, int rows, long l
 // lane whatever its addresses (192 a wave), a read and a compare-and-swap 15
 // a wave: so a float32 y is added to by one compare-and-swap round for all
 // VEC entries, a second one from the values the first found, and only the
-// entries another row changed both times by ds_add_f32.
+// entries another row changed both times by ds_add_f32 (2.06M rows of 19,881
+// columns, 400M entries, an iteration: float32 547 -> 475 us, bfloat16 503 ->
+// 347).
 template <int VEC>
 __device__ inline void lds_add_entries(double *y, const int (&c)[VEC], const float (&v)[VEC], double sc)
 {

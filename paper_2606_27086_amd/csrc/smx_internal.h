@@ -313,7 +313,7 @@ hipError_t launch_pass2_panels(const PassCfg &cfg, const SpView &At, const Panel
 // raises the dynamic-LDS limit of every LDS-staged pass kernel (once per
 // process; outside any stream capture, before the first such launch)
 hipError_t prepare_lds_passes();
-// pass 2: x = clip(x + lambda A^T c, lo, hi); workgroup 0 also ends the
+// pass 2: x = clip(x + lambda A^T c, lo, hi); one more workgroup ends the
 // iteration (proximity from pass 1's partials, history, k + 1) into st_out
 hipError_t launch_pass2(const PassCfg &cfg, const SpView &At, const RowBlocks &RB, int vk, const float *c, float *x,
                         ColStep cs, const SliceState *st_in, SliceState *st_out, int B, const double *part1,
