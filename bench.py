@@ -108,13 +108,13 @@ def kernel_name(pass_no, shape, B=1, shapes=None):
         acc = "double" if f["acc"] == "f64" else "float"
         if pass_no == 1:
             if f.get("zl", 0) and f.get("cap", 0):
-                return f"smx::k_fused_zlr<{f['lpr']}, {f['vec']}, {f['cap']}, {VALUE_TAG[f['format']]}>"
+                return f"smx::k_fused_zlr<{f['lpr']}, {f['vec']}, {f['cap']}, {VALUE_TAG[f['format']]}, {acc}>"
             if f.get("zl", 0):
-                return f"smx::k_fused_zl<{f['lpr']}, {f['vec']}, {VALUE_TAG[f['format']]}>"
+                return f"smx::k_fused_zl<{f['lpr']}, {f['vec']}, {VALUE_TAG[f['format']]}, {acc}>"
             if f.get("cap", 0):
                 return f"smx::k_fused_rc<{f['lpr']}, {f['vec']}, {f['cap']}, {VALUE_TAG[f['format']]}, {acc}>"
             return f"smx::k_fused<{f['lpr']}, {f['vec']}, {VALUE_TAG[f['format']]}, {acc}>"
-        return f"smx::k_fused_apply<{acc}>"
+        return f"smx::k_fused_apply<{acc}, 64>"  # 64 unknowns a workgroup (n > 1,024)
     vt = VALUE_TAG[shape["format"]]
     if shape["mode"] == "lds":
         return f"smx::k_pass{pass_no}_lds<{shape['lpr']}, {shape['vec']}, {vt}>"

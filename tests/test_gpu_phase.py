@@ -126,6 +126,25 @@ def test_linear_phase_with_extrapolated_steps(smx, m, n, basic, graph):
         assert abs(f[1] - c @ x) <= 2 * u * np.sum(np.abs(c * x)) + 1e-12
 
 
+@pytest.mark.parametrize("obj", [W.OBJ_NONE, W.OBJ_SQNORM, W.OBJ_L1])
+@pytest.mark.parametrize("B,m,n", [(1, 1, 1), (1, 5000, 3000), (8, 300, 4097), (32, 300, 200)])
+def test_query_of_every_slice(smx, obj, B, m, n):
+    """Both values of each slice in one launch, twice on the same problem.  The
+    weights D_i are rounded to float32 (2^-24 relative) and t_i^2 is summed in
+    float64; t_i = band - r_i is exact to float64 sums, so the proximity agrees
+    to 2^-23 and the objective to float64 summation."""
+    w = W.random_sparse(m, n, min(n, 8), seed=m + B, B=B, obj=obj, K=1)
+    p = smx.problem_from_workload(w)
+    for _ in range(2):
+        prox, f = p.query()
+        for s in range(B):
+            P, x = oracle.from_workload(w, s), w.x0[:, s].astype(np.float64)
+            assert abs(prox[s] - P.proximity(x)) <= 2.0 ** -23 * P.proximity(x) + 1e-18
+            want = 0.0 if obj == W.OBJ_NONE else P.objective(x)
+            assert abs(f[s] - want) <= 1e-12 * abs(want)
+    p.close()
+
+
 @pytest.mark.parametrize("B,gamma,alpha", [(1, 200.0, 0.93), (1, 3.0, 0.97), (2, 200.0, 0.93), (1, 1e6, 0.99)])
 def test_tv_phase_with_failing_batches(smx, B, gamma, alpha):
     """Four reduction steps in six trial launches: first batches of 8 that fail
