@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <type_traits>
 #include "smx_internal.h"
+#include "phase_rounds.h"
 
 #include <hip/hip_bf16.h>
 #include <hip/hip_fp16.h>
@@ -2979,6 +2980,23 @@ __device__ inline int line_trials(SliceState &sS, const PertParams &pp, const St
     return 0;
 }
 
+// The decision on ntr trials from each thread's share acc of their objectives
+// (every thread of the workgroup calls it; lds holds (BS/64) * T doubles).
+template <int T, int BS>
+__device__ inline void sum_and_record(SliceState &sS, const PertParams &pp, const StepWindow &win, double (&acc)[T],
+                                      int ntr, double *lds)
+{
+    block_sum<T, BS>(acc, lds);
+    if (threadIdx.x != 0) return;
+    int t = -1;
+    for (int w = 0; w < ntr; ++w)
+        if (acc[w] <= sS.f_cur) {
+            t = w;
+            break;
+        }
+    record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0, t >= 0 ? step_of(win, pp, sS, sS.ell + t) : 0.0);
+}
+
 // The phase of the linear objective f(x) = c^T x from its direction partials
 // (sum c_j^2 and sum c_j x_j per workgroup of the launch that left them).  On
 // v = -c/||c|| the objective at a trial point is known in closed form,
@@ -3050,14 +3068,9 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
     }
     derive_state<BS>(sS, st_in, pp, 1, part, s, nt, tot, win);
     const double gsq = tot[0], f0 = tot[1];
-    while (sS.phase) { // sS changes only in wave 0, between barriers
-        if (threadIdx.x < 64) {
-            const int ns = line_trials<OBJ>(sS, pp, win, f0, gsq, least, T);
-            if (threadIdx.x == 0) summed = ns;
-        }
-        __syncthreads();
-        const int ntr = summed;
-        if (ntr > 0) {
+    phase_rounds(
+        threadIdx.x < 64, summed, [&] { return line_trials<OBJ>(sS, pp, win, f0, gsq, least, T); },
+        [&](int ntr) {
             if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + step_of(win, pp, sS, sS.ell + threadIdx.x);
             __syncthreads();
             const double inv_gn = 1.0 / sS.gn;
@@ -3074,20 +3087,9 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
 #pragma unroll
                 for (int w = 0; w < T; ++w) acc[w] += fabs(xj + cw[w] * vj);
             }
-            block_sum<T, BS>(acc, lds);
-            if (threadIdx.x == 0) {
-                int t = -1;
-                for (int w = 0; w < ntr; ++w)
-                    if (acc[w] <= sS.f_cur) {
-                        t = w;
-                        break;
-                    }
-                record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0,
-                                t >= 0 ? step_of(win, pp, sS, sS.ell + t) : 0.0);
-            }
-        }
-        __syncthreads();
-    }
+            sum_and_record<T, BS>(sS, pp, win, acc, ntr, lds);
+        },
+        [] { __syncthreads(); });
     const bool apply = must_apply(sS);
     publish_state(sS, st_out, s, apply);
     if (apply) {
@@ -3232,14 +3234,9 @@ __global__ __launch_bounds__(kSmallPhaseBlock) void k_phase_small(float *__restr
         open[2] = least;
     }
     __syncthreads();
-    while (sS.phase) { // sS changes only in wave 0, between barriers
-        if (threadIdx.x < 64) {
-            const int ns = line_trials<OBJ>(sS, pp, win, open[1], open[0], open[2], T);
-            if (threadIdx.x == 0) summed = ns;
-        }
-        __syncthreads();
-        const int ntr = summed;
-        if (ntr > 0) { // L1 only
+    phase_rounds(
+        threadIdx.x < 64, summed, [&] { return line_trials<OBJ>(sS, pp, win, open[1], open[0], open[2], T); },
+        [&](int ntr) { // L1 only
             if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + step_of(win, pp, sS, sS.ell + threadIdx.x);
             __syncthreads();
             const double inv_gn = 1.0 / sS.gn;
@@ -3255,20 +3252,9 @@ __global__ __launch_bounds__(kSmallPhaseBlock) void k_phase_small(float *__restr
 #pragma unroll
                 for (int w = 0; w < T; ++w) acc[w] += fabs(xj + cw[w] * vj);
             }
-            block_sum<T, BS>(acc, lds);
-            if (threadIdx.x == 0) {
-                int t = -1;
-                for (int w = 0; w < ntr; ++w)
-                    if (acc[w] <= sS.f_cur) {
-                        t = w;
-                        break;
-                    }
-                record_decision(sS, pp, ntr, t, t >= 0 ? acc[t] : 0.0,
-                                t >= 0 ? step_of(win, pp, sS, sS.ell + t) : 0.0);
-            }
-        }
-        __syncthreads();
-    }
+            sum_and_record<T, BS>(sS, pp, win, acc, ntr, lds);
+        },
+        [] { __syncthreads(); });
     const bool apply = must_apply(sS);
     if (apply) {
         const double inv_gn = 1.0 / sS.gn;
