@@ -2198,7 +2198,7 @@ int phase_grid(const PertParams &pp)
     if (pp.obj == OBJ_TV2D)
         return ((pp.tv_rows + tv_tile_rows(pp) - 1) / tv_tile_rows(pp)) * ((pp.tv_cols + kTile - 1) / kTile);
     long long g = (pp.n + kBlock * 4 - 1) / (kBlock * 4);
-    return (int)(g < 1 ? 1 : (g > 512 ? 512 : g));
+    return (int)(g < 1 ? 1 : (g > kFlatPhaseGrid ? kFlatPhaseGrid : g));
 }
 
 // Totals over the `nt` tiles of slice s of rows v0 .. v0+nv-1 (rows of
@@ -4886,7 +4886,9 @@ hipError_t launch_phase(const PertParams &pp, const float *x, float *g, const fl
 
 bool phase_on_line(const PertParams &pp)
 {
-    return (pp.obj == OBJ_SQNORM || (pp.obj == OBJ_L1 && pp.n <= kLineMaxN)) && pp.n < (1LL << 31);
+    // k_trial_line steps an int by its grid's threads: longer vectors take the chain, which counts in 64 bits
+    constexpr long long walk = (1LL << 31) - (long long)kFlatPhaseGrid * kTrialBlock;
+    return (pp.obj == OBJ_SQNORM && pp.n <= walk) || (pp.obj == OBJ_L1 && pp.n <= kLineMaxN);
 }
 
 hipError_t launch_trial_line(const PertParams &pp, float *x, const float *xc, const SliceState *st_in,

@@ -20,6 +20,7 @@ constexpr int kSmallPhaseBlock = 1024; // threads of the one-launch perturbation
 constexpr int kSmallPhaseMaxN = 20000; // longest x it takes (x and the direction in LDS, 8 bytes an entry)
 constexpr int kSmallPhaseAutoN = 8192; // longest x it is the default for
 constexpr int kSmallTrials = 8;        // trials per batch there
+constexpr int kFlatPhaseGrid = 512;    // most workgroups (a slice) of the flat objectives' phase launches
 constexpr int kLineMaxN = 131072;      // longest x the L1 norm's phase sums in every workgroup alike
 constexpr int kApplyBlock = 1024;  // threads of the fused pass's apply kernel (16 waves share a column's partials)
 
