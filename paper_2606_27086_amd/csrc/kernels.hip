@@ -3004,6 +3004,12 @@ __device__ inline void sum_and_record(SliceState &sS, const PertParams &pp, cons
 // workgroup opens the phase from the partials (the same sums in the same
 // order) and runs the reduction steps' trials on those values; workgroup 0
 // publishes the state.  Returns whether the accepted step s v is to be added.
+constexpr int kPhaseSums = 2; // the totals a phase opens from
+// What the fused kernels hold beside z and y: block_sum's words, and the phase's
+// totals, state and steps.
+static_assert(sizeof(double) * (kFusedBlock / 64 + kPhaseSums) + sizeof(SliceState) + sizeof(StepWindow) <=
+                  kFusedStaticLds,
+              "the fused pass's limit on n leaves this much");
 template <int BS>
 __device__ inline bool linear_phase(SliceState &sS, const SliceState *__restrict__ st_in, const PertParams &pp,
                                    const double *__restrict__ part, int s, int nt, double *tot,
@@ -3025,7 +3031,7 @@ __global__ __launch_bounds__(kBlock) void k_trial_linear(float *__restrict__ x, 
                                                          SliceState *__restrict__ st_out, PertParams pp,
                                                          const double *__restrict__ part_phase)
 {
-    __shared__ double tot[kTrialChunk];
+    __shared__ double tot[kPhaseSums];
     __shared__ SliceState sS;
     const int s = blockIdx.y, B = pp.B, nt = gridDim.x;
     if (linear_phase<kBlock>(sS, st_in, pp, part_phase, s, nt, tot, st_out)) {
@@ -4142,7 +4148,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zl(SpView A, int n, const
     float *zl = reinterpret_cast<float *>(fused_lds);
     AccT *y = reinterpret_cast<AccT *>(zl + ((n + 3) & ~3));
     __shared__ double lds[kFusedBlock / 64];
-    __shared__ double tot[kTrialChunk];
+    __shared__ double tot[kPhaseSums];
     __shared__ SliceState sS;
     constexpr int RPB = kFusedBlock / LPR;
     constexpr int STEP = LPR * VEC;
@@ -4207,7 +4213,7 @@ __global__ __launch_bounds__(kFusedBlock) void k_fused_zlr(SpView A, int n, cons
     float *zl = reinterpret_cast<float *>(fused_lds);
     AccT *y = reinterpret_cast<AccT *>(zl + ((n + 3) & ~3));
     __shared__ double lds[kFusedBlock / 64];
-    __shared__ double tot[kTrialChunk];
+    __shared__ double tot[kPhaseSums];
     __shared__ SliceState sS;
     constexpr int RPB = kFusedBlock / LPR;
     constexpr int STEP = LPR * VEC;
@@ -4378,8 +4384,7 @@ size_t fused_lds_limit()
     int dev = 0, v = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess) return 0;
-    const size_t reserve = 1024; // the fused kernel's own static LDS
-    return size_t(v) > reserve ? size_t(v) - reserve : 0;
+    return size_t(v) > kFusedStaticLds ? size_t(v) - kFusedStaticLds : 0;
 }
 
 namespace {

@@ -22,6 +22,7 @@ constexpr int kSmallPhaseAutoN = 8192; // longest x it is the default for
 constexpr int kSmallTrials = 8;        // trials per batch there
 constexpr int kFlatPhaseGrid = 512;    // most workgroups (a slice) of the flat objectives' phase launches
 constexpr int kLineMaxN = 131072;      // longest x the L1 norm's phase sums in every workgroup alike
+constexpr size_t kFusedStaticLds = 1024; // bytes of LDS left to the fused kernels' own arrays
 constexpr int kApplyBlock = 1024;  // threads of the fused pass's apply kernel (16 waves share a column's partials)
 
 // Stored formats of A's entries.  The packed kinds hold one 32-bit word per
