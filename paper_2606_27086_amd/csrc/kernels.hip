@@ -1353,7 +1353,7 @@ __device__ inline void lds_add_entries(float *y, const int (&c)[VEC], const floa
     bool any = false;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        a[e] = (float)(sc * (double)v[e]);
+        a[e] = v[e] != 0.f ? (float)(sc * (double)v[e]) : 0.f; // sc may be infinite
         was[e] = __hip_atomic_load(&w[c[e]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 #pragma unroll

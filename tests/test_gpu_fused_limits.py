@@ -77,3 +77,39 @@ def test_dose_volume_rows_keep_the_pass(smx, n):
         xs.append(p.get_x().cpu().numpy().astype(np.float64))
         p.close()
     assert close_to(xs[0], xs[1])
+
+
+@pytest.mark.parametrize("n,shape", [(900, (8, 4, 0, 1)), (900, (8, 4, 0, 0)), (900, (16, 4, 4, 0)),
+                                     (14000, (8, 4, 0, 1)), (14000, (16, 8, 2, 1)), (21000, (8, 4, 0, 0)),
+                                     (21000, (16, 8, 0, 0)), (21000, (16, 4, 4, 0))])
+def test_infinite_row_reaches_its_columns_alone(smx, n, shape):
+    """A row whose value is -inf has c = +inf: its columns go to the box's upper
+    bound, the one at its end too, which the padding behind the row (value 0)
+    names again, and a stored zero adds nothing.  The other columns are those
+    of the same x0 without the infinity."""
+    rng = np.random.default_rng(n)
+    m, own = 70, np.array([5, 9, 11, 20])
+    cols = [np.sort(rng.choice(np.setdiff1d(np.arange(n), own), size=1 + i % 11, replace=False)) for i in range(m)]
+    cols[7] = np.array([5, 20, 9, 11])
+    ptr = np.concatenate([[0], np.cumsum([len(c) for c in cols])]).astype(np.int32)
+    col = np.concatenate(cols).astype(np.int32)
+    val = rng.uniform(0.5, 1.5, len(col)).astype(np.float32)
+    val[col == 20] = 0.0
+    x0 = rng.uniform(0.1, 1.0, (n, 1)).astype(np.float32)
+    w = W.Workload(name="inf", m=m, n=n, row_ptr=ptr, col_idx=col, val=val, lower=np.full((m, 1), -0.1, np.float32),
+                   upper=np.full((m, 1), 0.1, np.float32), x0=x0, box_lo=np.full(n, -1e30, np.float32),
+                   box_hi=np.full(n, 1e30, np.float32), lam=1.0, K=1)
+    ref = smx.problem_from_workload(w, fused=False)
+    ref.run(1, perturb=False)
+    want = ref.get_x().cpu().numpy().astype(np.float64)[:, 0]
+    ref.close()
+    p = smx.problem_from_workload(w)
+    p.set_fused_shape(*shape)
+    x0[5] = -np.inf
+    p.set_x(x0)
+    p.run(1, perturb=False)
+    got = p.get_x().cpu().numpy().astype(np.float64)[:, 0]
+    p.close()
+    rest = np.setdiff1d(np.arange(n), [5, 9, 11])
+    assert got[9] == got[11] == np.float32(1e30)
+    assert close_to(got[rest], want[rest])
