@@ -2595,8 +2595,9 @@ int smx_set_fused_shape(smx_problem *p, int32_t lpr, int32_t vec, int32_t cap, i
             if (!p->fused_ok[vk]) continue;
             for (const FusedCfg &c : fused_candidates(p->fcfg[vk], p->n, p->dvc.n > 0))
                 if (c.lpr == lpr && c.vec == vec && c.cap == cap && c.zl == z_in_lds) {
-                    p->fcfg[vk] = c;
+                    p->fcfg[vk] = c; // the first: of a shape tried at two grids, the larger
                     found = true;
+                    break;
                 }
         }
         if (!found)

@@ -113,3 +113,17 @@ def test_infinite_row_reaches_its_columns_alone(smx, n, shape):
     rest = np.setdiff1d(np.arange(n), [5, 9, 11])
     assert got[9] == got[11] == np.float32(1e30)
     assert close_to(got[rest], want[rest])
+
+
+def test_pinned_shape_takes_the_larger_grid(smx):
+    """Up to 2,048 columns the tuner tries a shape with z in LDS at two grids;
+    a shape that is asked for by name gets the one of the default shape, as many
+    workgroups as the rows use, again and again."""
+    w = W.random_sparse(20000, 300, 4, seed=5, obj=W.OBJ_NONE, K=1)
+    p = smx.problem_from_workload(w)
+    grid = p.describe()["f32"]["fused"]["grid"]
+    assert grid == 313  # ceil(20000 / 64), over one workgroup a CU
+    for shape in ((8, 8, 0, 1), (8, 4, 0, 0), (16, 4, 4, 1), (32, 8, 2, 1), (16, 8, 2, 1)):
+        p.set_fused_shape(*shape)
+        assert p.describe()["f32"]["fused"]["grid"] == grid, shape
+    p.close()
