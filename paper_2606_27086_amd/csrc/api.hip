@@ -911,12 +911,11 @@ bool lin_from_apply(const smx_problem *p, int vk)
     return phase_kind(p) == PHASE_LINEAR && p->fused[vk] && p->part_lin.p;
 }
 
+// Whether k_step_apply moves x (after the pass kept y).
+bool extrapolated(const smx_problem *p) { return p->basic == SMX_BASIC_EL || p->basic == SMX_BASIC_EMR; }
+
 // Slots of those partials: workgroups of the kernel that applies the step.
-int lin_slots(const smx_problem *p)
-{
-    const bool extrap = p->basic == SMX_BASIC_EL || p->basic == SMX_BASIC_EMR;
-    return extrap ? step_apply_grid(p->n, 1) : fused_apply_grid(p->n);
-}
+int lin_slots(const smx_problem *p) { return extrapolated(p) ? step_apply_grid(p->n, 1) : fused_apply_grid(p->n); }
 
 // Whether iterations of value kind vk take that phase inside the fused pass
 // (shapes with z in LDS): every workgroup of the pass opens the phase from the
@@ -1006,7 +1005,7 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
         p->ev_used += 4;
         hip_check(hipEventRecord(e[0], s), "event");
     }
-    const bool extrap = p->basic == SMX_BASIC_EL || p->basic == SMX_BASIC_EMR;
+    const bool extrap = extrapolated(p);
     if (p->fused[vk]) {
         const bool lin_pass = perturb && p->pp.obj != OBJ_NONE && pk == PHASE_LINEAR && lin_in_pass(p, vk);
         LinPhase lp{};
@@ -1141,7 +1140,7 @@ int run_impl(smx_problem *p, int32_t K, uint32_t flags)
         // the first phase of the run of iterations needs its direction partials of x
         if (perturb && lin_from_apply(p, vk))
             hip_check(launch_lin_partials(p->x.as<float>(), p->lin_c.as<float>(), p->n, p->part_lin.as<double>(),
-                                          lin_slots(p), p->stream),
+                                          lin_slots(p), extrapolated(p), p->stream),
                       "direction partials");
         if (graph) {
             while (left > 0) {

@@ -1589,12 +1589,13 @@ __global__ __launch_bounds__(kFusedRcBlock) void k_fused_rc(SpView A, int n, con
 
 // Direction partials of the linear objective f = c^T x for the next
 // perturbation phase: this workgroup's sums of c_j^2 and c_j x_j over the
-// unknowns j0 + l (l < CW, j0 = CW blockIdx.x, stepping CW groups),
-// added by the first wave's lanes in that order and then over the
-// workgroup, stored as the direction launch's partials would be (slot
+// unknowns j0 + l (l < CW, j0 = CW blockIdx.x, stepping CW groups), each of
+// its first CW threads adding its own in that order, then over the workgroup
+// (BS threads), stored as the direction launch's partials would be (slot
 // blockIdx.x of 2 x groups).  k_fused_apply calls it after writing x and
-// k_lin_partials alone, with the same sums in the same order.
-template <int CW>
+// k_lin_partials alone, with the same sums in the same order (CW = BS = kBlock:
+// those of k_step_apply), so a phase does not depend on where a run starts.
+template <int CW, int BS>
 __device__ inline void lin_partials_block(const float *__restrict__ x, const float *__restrict__ c, int n,
                                           int groups, double *__restrict__ part, double *lds)
 {
@@ -1605,20 +1606,19 @@ __device__ inline void lin_partials_block(const float *__restrict__ x, const flo
             v[0] += cj * cj;
             v[1] += cj * (double)x[j];
         }
-    block_sum<2, kApplyBlock>(v, lds);
+    block_sum<2, BS>(v, lds);
     if (threadIdx.x == 0) {
         part[blockIdx.x] = v[0];
         part[groups + blockIdx.x] = v[1];
     }
 }
 
-template <int CW>
-__global__ __launch_bounds__(kApplyBlock) void k_lin_partials(const float *__restrict__ x,
-                                                              const float *__restrict__ c, int n,
-                                                              double *__restrict__ part)
+template <int CW, int BS>
+__global__ __launch_bounds__(BS) void k_lin_partials(const float *__restrict__ x, const float *__restrict__ c, int n,
+                                                     double *__restrict__ part)
 {
-    __shared__ double lds[kApplyBlock / 64 * 2];
-    lin_partials_block<CW>(x, c, n, (int)gridDim.x, part, lds);
+    __shared__ double lds[BS / 64 * 2];
+    lin_partials_block<CW, BS>(x, c, n, (int)gridDim.x, part, lds);
 }
 
 // x = clip(z + lambda * Z_j * sum_g ypart[g], lo, hi) (Z_j = 1 unless DROP);
@@ -1711,7 +1711,7 @@ __global__ __launch_bounds__(kApplyBlock) void k_fused_apply(const AccT *__restr
     }
     // the next phase's direction partials from the x just written (each
     // lane rereads its own entries)
-    if (lin_part) lin_partials_block<CW>(x, lin_c, n, groups, lin_part, lds);
+    if (lin_part) lin_partials_block<CW, kApplyBlock>(x, lin_c, n, groups, lin_part, lds);
     end_columns<kApplyBlock>(cs, ysq, lds);
 }
 
@@ -4528,11 +4528,13 @@ hipError_t launch_fused_apply(const FusedCfg &cfg, int64_t n, const void *ypart,
     return hipGetLastError();
 }
 
-hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, int groups, hipStream_t s)
+hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, int groups, bool extrap,
+                               hipStream_t s)
 {
     if (n < 1 || groups < 1 || !x || !c || !part) return hipErrorInvalidValue;
-    auto kern = fused_apply_cols(n) == 16 ? k_lin_partials<16> : k_lin_partials<64>;
-    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(kApplyBlock), 0, s, x, c, (int)n, part);
+    auto kern = extrap ? k_lin_partials<kBlock, kBlock>
+                       : (fused_apply_cols(n) == 16 ? k_lin_partials<16, kApplyBlock> : k_lin_partials<64, kApplyBlock>);
+    hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(extrap ? kBlock : kApplyBlock), 0, s, x, c, (int)n, part);
     return hipGetLastError();
 }
 

@@ -370,8 +370,10 @@ hipError_t launch_fused_apply(const FusedCfg &cfg, int64_t n, const void *ypart,
                               const SliceState *st_in, SliceState *st_out, const double *part1, Hist h,
                               hipStream_t s, const float *lin_c = nullptr, double *lin_part = nullptr,
                               int lin_z = 0);
-// the same direction partials of x alone (one slice; `groups` slots)
-hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, int groups, hipStream_t s);
+// the same direction partials of x alone (one slice; `groups` slots; extrap:
+// summed as k_step_apply sums them, else as k_fused_apply does)
+hipError_t launch_lin_partials(const float *x, const float *c, int64_t n, double *part, int groups, bool extrap,
+                               hipStream_t s);
 // y partials of rows [r_lo, r_hi) whose c is set (the dose-volume rows of a
 // fused-pass problem, after their ranking): grid float32 vectors of n at ypart
 hipError_t prepare_scatter_rows(int vk, int64_t n);

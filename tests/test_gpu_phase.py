@@ -152,3 +152,23 @@ def test_tv_phase_with_failing_batches(smx, B, gamma, alpha):
     trial at once), batches that succeed, and a step that meets the cap."""
     w = W.random_sparse(900, 33 * 21, 6, seed=93, B=B, obj=W.OBJ_TV2D, K=1, tv_shape=(33, 21))
     check_iteration(smx, w.with_params(gamma=gamma, alpha=alpha, n_red=4), expect_launches=8)
+
+
+@pytest.mark.parametrize("basic", [W.BASIC_SIMULT, W.BASIC_EL, W.BASIC_EMR])
+@pytest.mark.parametrize("n", [700, 1500, 5000, 14000])
+def test_linear_phase_is_the_same_wherever_a_run_starts(smx, n, basic):
+    """The partials a run opens with are summed as those the launch that moves x
+    leaves: a phase's f(x^k) has the same bits as the first of a run and inside
+    one.  One row (one workgroup with entries, so that y has one order), weights
+    1: three iterations in one run and in three."""
+    w = W.random_sparse(1, n, n, seed=n, obj=W.OBJ_LINEAR, K=1, empty_frac=0.0, long_rows=1)
+    w = w.with_params(gamma=2.0, alpha=0.9, n_red=3, basic=basic)
+    got = []
+    for runs in ((3,), (1, 1, 1), (2, 1)):
+        p = smx.problem_from_workload(w, history_cap=4)
+        for k in runs:
+            p.run(k)
+        h = p.history()
+        got.append((h["f_start"][:, 0].tobytes(), h["f_end"][:, 0].tobytes(), p.get_x().cpu().numpy().tobytes()))
+        p.close()
+    assert got[0] == got[1] == got[2]
