@@ -172,3 +172,28 @@ def test_linear_phase_is_the_same_wherever_a_run_starts(smx, n, basic):
         got.append((h["f_start"][:, 0].tobytes(), h["f_end"][:, 0].tobytes(), p.get_x().cpu().numpy().tobytes()))
         p.close()
     assert got[0] == got[1] == got[2]
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("m,n", [(1, 2), (64, 17), (4097, 65), (16500, 324), (500, 1024), (500, 1025), (200, 8192)])
+def test_second_linear_phase_opens_from_the_apply_kernel(smx, m, n, graph):
+    """The partials that the fused pass's apply kernel leaves for the next phase
+    (16 unknowns a workgroup to n = 1,024, 64 beyond): the second phase opens at
+    c^T x of the first result, summed in float64 over float32 x, and tries as
+    many steps as the two passes' second phase does."""
+    w = W.random_sparse(m, n, min(n, 6), seed=m, obj=W.OBJ_LINEAR, K=1).with_params(gamma=3.0, alpha=0.9, n_red=2)
+    trials = []
+    for fused in (True, False):
+        p = smx.problem_from_workload(w, fused=fused, history_cap=4)
+        p.run(1, graph=graph)
+        x = p.get_x().cpu().numpy().astype(np.float64)[:, 0]
+        p.reset(w.x0)
+        p.run(2, graph=graph)
+        h = p.history()
+        p.close()
+        trials.append(tuple(h["trials"][:, 0]))
+        cx = np.asarray(w.linear_c, np.float64) * x
+        # the fused pass adds in no fixed order: its x may differ by a rounding from run to run
+        slack = 2 * 2.0 ** -24 if fused else 1e-13
+        assert abs(h["f_start"][1, 0] - cx.sum()) <= slack * np.sum(np.abs(cx)) + 1e-12
+    assert trials[0] == trials[1]
