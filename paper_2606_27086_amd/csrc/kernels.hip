@@ -2181,12 +2181,30 @@ __device__ inline int trial_width(const SliceState &S, const PertParams &pp, int
     return min(w, left);
 }
 
-// Rows of a TV tile: kTile for one slice; for several, halved (down to 2)
-// while the image has under 256 tiles.
+// Workgroups of 1,024 threads that the device holds at once (two a CU).
+constexpr long long kTvResident = 512;
+
+// Whether a workgroup of the TV phase takes a tile's pixels of every slice
+// (k_phase_tv_mm, k_trial_tv_mm) or of one (k_phase_tv, k_trial_tv).  While all
+// (16 x 16 tile, slice) pairs are resident at once their strided reads cost
+// little and a wave values a trial of its own; in whole lines the trials of a
+// pixel are a chain in one thread.  Four reduction steps with rejected trials,
+// an iteration, a slice a workgroup against whole lines: 64 x 64, 32 slices (512
+// pairs) 114 us against 293; 128 x 128, 4 slices 52 against 70, 8 (512) 83
+// against 88, 16 146 against 140, 32 274 against 178; 256 x 256, 2 (512) 91 each,
+// 4 145 against 113, 32 973 against 357.
+static inline bool tv_whole_lines(const PertParams &pp)
+{
+    const long long tiles = (long long)((pp.tv_rows + kTile - 1) / kTile) * ((pp.tv_cols + kTile - 1) / kTile);
+    return pp.obj == OBJ_TV2D && pp.B > 1 && tiles * pp.B > kTvResident;
+}
+
+// Rows of a TV tile: kTile for a workgroup of one slice; in whole lines halved
+// (down to 2) while the image has under 256 tiles.
 static inline int tv_tile_rows(const PertParams &pp)
 {
     int th = kTile;
-    if (pp.B > 1)
+    if (tv_whole_lines(pp))
         while (th > 2 && ((pp.tv_rows + th - 1) / th) * ((pp.tv_cols + kTile - 1) / kTile) < 256) th /= 2;
     return th;
 }
@@ -2662,12 +2680,10 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_tv(float *__restrict__ x,
 //    blockDim / B further on, ...  The layout is slice-interleaved, so a
 //    wave's loads are whole cache lines; with a workgroup per (tile, slice),
 //    as for one slice, each read 4 bytes of a line that B workgroups fetch
-//    (B = 32 at 256 x 256: 124 us a trial launch, 25 us the gradient).
-
+//    (B = 32 at 256 x 256: 124 us a trial launch, 25 us the gradient).  From
+//    512 such pairs on (tv_whole_lines).
 //    The tiles are kTile wide and tv_tile_rows(pp) high: 16 rows on large
-//    images, fewer while that leaves the device with under 256 workgroups (a
-//    128 x 128 image of 8 slices in 64 tiles of 16 rows: 6.5 us the gradient,
-//    10 us the trials).
+//    images, fewer while that leaves the device with under 256 workgroups.
 
 // Threads of such a workgroup: 256 for small tiles, whose barriers and
 // reductions over 16 waves would outweigh the pixels.
@@ -4865,7 +4881,7 @@ hipError_t launch_phase(const PertParams &pp, const float *x, float *g, const fl
                         int eval_only, double *partials, hipStream_t s, double *part_min)
 {
     const dim3 grid(phase_grid(pp), pp.B), block(kBlock);
-    if (pp.obj == OBJ_TV2D && pp.B > 1) {
+    if (tv_whole_lines(pp)) {
 #define SMX_PTV(NB)                                                                                                    \
     case NB:                                                                                                           \
         if (tv_small_block(pp))                                                                                        \
@@ -5094,7 +5110,7 @@ hipError_t launch_trial_close(const PertParams &pp, float *x, const float *g, co
                               SliceState *st_out, const double *part_prev, hipStream_t s)
 {
     if (pp.max_trials < 1 || pp.max_trials > 1024) return hipErrorInvalidValue;
-    if (pp.obj == OBJ_TV2D && pp.B > 1) return trial_tv_mm(pp, x, g, st_in, st_out, 0, -1, part_prev, nullptr, s);
+    if (tv_whole_lines(pp)) return trial_tv_mm(pp, x, g, st_in, st_out, 0, -1, part_prev, nullptr, s);
     const long long g_need = (pp.n + kTrialBlock - 1) / kTrialBlock; // one unknown a thread, at most 256 workgroups
     const unsigned grid = (unsigned)std::max(1LL, std::min(g_need, 256LL));
     hipLaunchKernelGGL(k_trial_close, dim3(grid, pp.B), dim3(kTrialBlock), 0, s, x, g, st_in, st_out, pp,
@@ -5106,7 +5122,7 @@ hipError_t launch_trial(const PertParams &pp, float *x, const float *g, const Sl
                         int first, int after, const double *part_prev, double *part_out, hipStream_t s)
 {
     if (pp.max_trials < 1 || pp.max_trials > 1024 || after < 0) return hipErrorInvalidValue;
-    if (pp.obj == OBJ_TV2D && pp.B > 1)
+    if (tv_whole_lines(pp))
         return trial_tv_mm(pp, x, g, st_in, st_out, first, after, part_prev, part_out, s);
     const dim3 grid(phase_grid(pp), pp.B), block(kBlock);
     if (pp.obj == OBJ_TV2D)

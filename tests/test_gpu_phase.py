@@ -197,3 +197,12 @@ def test_second_linear_phase_opens_from_the_apply_kernel(smx, m, n, graph):
         slack = 2 * 2.0 ** -24 if fused else 1e-13
         assert abs(h["f_start"][1, 0] - cx.sum()) <= slack * np.sum(np.abs(cx)) + 1e-12
     assert trials[0] == trials[1]
+
+
+@pytest.mark.parametrize("B,R,C", [(32, 64, 64), (2, 256, 256), (32, 80, 64), (16, 81, 90), (8, 130, 130),
+                                   (4, 180, 181), (2, 257, 250)])
+def test_tv_phase_of_several_slices(smx, B, R, C):
+    """Both sides of 512 (16 x 16 tile, slice) pairs: a workgroup a slice, and
+    whole lines in tiles of 2, 4, 8 and 16 rows; four steps with rejected trials."""
+    w = W.random_sparse(300, R * C, 6, seed=B + R, B=B, obj=W.OBJ_TV2D, K=1, tv_shape=(R, C))
+    check_iteration(smx, w.with_params(gamma=200.0, alpha=0.93, n_red=4), expect_launches=8)
