@@ -299,6 +299,7 @@ struct smx_problem {
     PertParams pp{};
     DBuf x, g, c, lower, upper, box_lo, box_hi, lin_c, w, D32, D16, st;
     HBuf qout; // query: proximity [B], objective [B]
+    DBuf line; // the L1 norm's sorted chunks (phase_sorted)
     DBuf part_pass, part_query, part_phase, part_trial[2]; // per-workgroup partial sums of each kernel kind
     int cur = 0; // which of the two state buffers (st holds 2*B states) is current
     bool tuned = false;
@@ -391,7 +392,7 @@ struct smx_problem {
     {
         size_t t = 0;
         for (const DBuf *b : {&x, &g, &c, &lower, &upper, &box_lo, &box_hi, &lin_c, &w, &D32, &D16, &st,
-                              &part_pass, &part_query, &part_phase, &part_trial[0], &part_trial[1], &h_prox, &h_fs,
+                              &line, &part_pass, &part_query, &part_phase, &part_trial[0], &part_trial[1], &h_prox, &h_fs,
                               &h_fe, &h_tr, &h_ac, &ypart, &part_lin, &S32, &S16, &ybuf, &ybuf32, &part_y, &part_q,
                               &ypanel,
                               &xprev, &part_var, &dvc_dose, &dvc_tie, &dvc_hist, &dvc_sel})
@@ -866,10 +867,9 @@ enum PhaseKind { PHASE_CHAIN, PHASE_SMALL, PHASE_LINEAR, PHASE_LINE };
 // launch chain takes ~22-25 us whatever n), the linear objective beyond that,
 // and wherever the fused pass's apply kernel leaves its partials (the phase
 // then takes one launch of ~4.5 us or none, the one-launch form 8 us at n =
-// 6,293), with its trials in closed form, the squared norm and L1 (up to kLineMaxN,
-// past which summing the trials in every workgroup would cost more than the
-// chain's launches) with theirs valued along the line in one launch, anything
-// else as the chain of launches.
+// 6,293), with its trials in closed form, the squared norm and L1 where
+// phase_on_line has them with theirs valued along the line in one launch,
+// anything else as the chain of launches.
 PhaseKind phase_kind(const smx_problem *p)
 {
     switch (p->phase_form) {
@@ -968,12 +968,22 @@ int enqueue_iteration_core(smx_problem *p, hipStream_t s, int vk, bool perturb, 
         cur ^= 1;
     } else if (perturb && p->pp.obj != OBJ_NONE && pk == PHASE_LINE) {
         double *least = p->part_trial[0].as<double>(); // free: this form has no trial launches
-        hip_check(launch_phase(p->pp, p->x.as<float>(), p->g.as<float>(), nullptr, p->state(cur), 0,
-                               p->part_phase.as<double>(), s, least),
-                  "phase");
-        hip_check(launch_trial_line(p->pp, p->x.as<float>(), p->g.as<float>(), p->state(cur), p->state(cur ^ 1),
-                                    p->part_phase.as<double>(), least, s),
-                  "phase on the line");
+        if (phase_sorted(p->pp)) {
+            const LineSorted L = line_sorted(p->line.p, p->pp);
+            hip_check(launch_phase_sorted(p->pp, p->x.as<float>(), p->state(cur), L, p->part_phase.as<double>(), least,
+                                          s),
+                      "phase");
+            hip_check(launch_trial_sorted(p->pp, p->x.as<float>(), p->state(cur), p->state(cur ^ 1), L,
+                                          p->part_phase.as<double>(), least, s),
+                      "phase on the line");
+        } else {
+            hip_check(launch_phase(p->pp, p->x.as<float>(), p->g.as<float>(), nullptr, p->state(cur), 0,
+                                   p->part_phase.as<double>(), s, least),
+                      "phase");
+            hip_check(launch_trial_line(p->pp, p->x.as<float>(), p->g.as<float>(), p->state(cur), p->state(cur ^ 1),
+                                        p->part_phase.as<double>(), least, s),
+                      "phase on the line");
+        }
         cur ^= 1;
     } else if (perturb && p->pp.obj != OBJ_NONE) {
         hip_check(launch_phase(p->pp, p->x.as<float>(), p->g.as<float>(), p->lin_c.as<float>(), p->state(cur), 0,
@@ -1384,6 +1394,7 @@ size_t problem_plan_bytes(int64_t m, int64_t n, int64_t nnz, bool has_f32, int l
     add(8 * pgrid * B * 2);
     add(8 * pgrid * B * trials);
     add(8 * pgrid * B * trials);
+    if (phase_sorted(pp)) add(line_sorted_bytes(pp));
     if (d->history_cap > 0) {
         const size_t hc = size_t(d->history_cap) * B;
         for (int k = 0; k < 3; ++k) add(8 * hc);
@@ -1687,6 +1698,7 @@ int create_problem(smx_operator *op, const smx_problem_desc *d, hipStream_t s, s
     p->part_phase.alloc(sizeof(double) * size_t(pgrid) * B * 2, "phase partials");
     p->part_trial[0].alloc(sizeof(double) * size_t(pgrid) * B * pp.max_trials, "trial partials");
     p->part_trial[1].alloc(sizeof(double) * size_t(pgrid) * B * pp.max_trials, "trial partials");
+    if (phase_sorted(pp)) p->line.alloc(line_sorted_bytes(pp), "sorted chunks");
     p->qout.alloc(sizeof(double) * 2 * B, "query output");
     p->hist_cap = d->history_cap;
     if (d->history_cap > 0) {

@@ -3124,6 +3124,239 @@ __global__ __launch_bounds__(kTrialBlock) void k_trial_line(float *__restrict__ 
     }
 }
 
+// Compare-exchange stage of a bitonic sort of 1,024 keys, four consecutive ones
+// a thread of a 256-thread workgroup (key i = 4 thread + e): partners `stride`
+// apart, runs of `size`.  ex (LDS, 1,024 words) for partners in other waves.
+template <int SIZE, int STRIDE>
+__device__ inline void sort_stage(unsigned (&k)[4], unsigned *ex)
+{
+    const int i0 = (int)threadIdx.x * 4;
+    const bool up = (i0 & SIZE) == 0; // SIZE >= 4: the same for a thread's keys
+    if constexpr (STRIDE < 4) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if ((e & STRIDE) == 0) {
+                const bool asc = SIZE < 4 ? (e & SIZE) == 0 : up;
+                const unsigned lo = min(k[e], k[e ^ STRIDE]), hi = max(k[e], k[e ^ STRIDE]);
+                k[e] = asc ? lo : hi;
+                k[e ^ STRIDE] = asc ? hi : lo;
+            }
+    } else {
+        const bool low = (i0 & STRIDE) == 0;
+        unsigned o[4];
+        if constexpr (STRIDE < 256) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = __shfl_xor(k[e], STRIDE / 4, 64);
+        } else {
+            __syncthreads(); // the previous stage's reads of ex are over
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ex[e * kBlock + threadIdx.x] = k[e];
+            __syncthreads();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = ex[e * kBlock + (threadIdx.x ^ (STRIDE / 4))];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) k[e] = low == up ? min(k[e], o[e]) : max(k[e], o[e]);
+    }
+}
+template <int SIZE, int STRIDE>
+__device__ inline void sort_merge(unsigned (&k)[4], unsigned *ex)
+{
+    sort_stage<SIZE, STRIDE>(k, ex);
+    if constexpr (STRIDE > 1) sort_merge<SIZE, STRIDE / 2>(k, ex);
+}
+template <int SIZE>
+__device__ inline void sort_chunk(unsigned (&k)[4], unsigned *ex)
+{
+    if constexpr (SIZE > 2) sort_chunk<SIZE / 2>(k, ex);
+    sort_merge<SIZE, SIZE / 2>(k, ex);
+}
+
+// Direction launch of the L1 norm for k_trial_sorted (one slice, a workgroup a
+// chunk of kLineChunk entries): k_phase_flat's partials of ||g||^2 (the nonzero
+// entries), f(x) and the least nonzero |x_j|, and the chunk's |x_j| sorted, as
+// bit patterns, which order as the nonnegative numbers do; zeros, NaN and what
+// lies past n become infinities, which no trial reaches.
+__global__ __launch_bounds__(kBlock) void k_phase_sorted(const float *__restrict__ x, int n,
+                                                         const SliceState *__restrict__ st, LineSorted L,
+                                                         double *__restrict__ partials, double *__restrict__ part_min)
+{
+    static_assert(kLineChunk == 4 * kBlock && kLineBucket % 4 == 0, "four keys a thread");
+    __shared__ unsigned ex[kLineChunk];
+    __shared__ double lds[4 * 2];
+    const int b = blockIdx.x, nt = gridDim.x, j0 = b * kLineChunk + (int)threadIdx.x * 4;
+    const bool live = st[0].live != 0; // the same in every thread
+    float xf[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) xf[e] = 0.f;
+    if (live) {
+        if (j0 + 4 <= n) {
+            const float4 v4 = *reinterpret_cast<const float4 *>(x + j0);
+            xf[0] = v4.x; xf[1] = v4.y; xf[2] = v4.z; xf[3] = v4.w;
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (j0 + e < n) xf[e] = x[j0 + e];
+        }
+    }
+    double v[2] = {0.0, 0.0}, least = INFINITY;
+    unsigned k[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const float a = fabsf(xf[e]);
+        const bool nz = a > 0.f; // not a NaN
+        v[0] += nz ? 1.0 : 0.0;
+        v[1] += (double)a;
+        if (nz) least = fmin(least, (double)a);
+        k[e] = __float_as_uint(nz ? a : INFINITY);
+    }
+    block_sum<2>(v, lds);
+    if (threadIdx.x == 0) {
+        partials[b] = v[0];
+        partials[nt + b] = v[1];
+    }
+    for (int off = 32; off > 0; off >>= 1) least = fmin(least, __shfl_xor(least, off, 64));
+    const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane == 0) lds[wid] = least;
+    __syncthreads();
+    if (threadIdx.x == 0) part_min[b] = fmin(fmin(lds[0], lds[1]), fmin(lds[2], lds[3]));
+    if (!live) return;
+    sort_chunk<kLineChunk>(k, ex);
+    double sum = 0.0; // of the thread's finite keys, then of all before them
+    float f[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        f[e] = __uint_as_float(k[e]);
+        if (isfinite(f[e])) sum += (double)f[e];
+    }
+    double incl = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const double o = __shfl_up(incl, off, 64);
+        if (lane >= off) incl += o;
+    }
+    double before = __shfl_up(incl, 1, 64);
+    if (lane == 0) before = 0.0;
+    if (lane == 63) lds[4 + wid] = incl;
+    __syncthreads();
+    for (int w = 0; w < wid; ++w) before += lds[4 + w];
+    *reinterpret_cast<float4 *>(L.key + j0) = make_float4(f[0], f[1], f[2], f[3]);
+    if (threadIdx.x % (kLineBucket / 4) == 0) {
+        const int q = j0 / kLineBucket;
+        L.pivot[q] = f[0];
+        L.below[q] = before;
+    }
+}
+
+// The L1 norm's phase in one launch after k_phase_sorted, as k_trial_line; past
+// a change of sign
+//   ||x + t v||_1 = f0 - t gsq/||g|| + 2 sum over 0 < |x_j| < tau of (tau - |x_j|),
+// tau = t/||g||, and thread (trial, chunk) finds its chunk's count and sum of
+// keys below tau: a search of the pivots (in LDS from the phase's first such
+// batch on) and one bucket of keys, loaded at once.  Every workgroup takes the
+// same decisions from the same sums, and adds the step to its part of x, which
+// no other workgroup reads.  A batch is a chain of two loads out of L2 and two
+// barriers, ~5 us whatever n; summed over x by every workgroup it was 15 us at n
+// = 32,761 and 45 at 131,044 (an iteration of four steps there 207 us, now 69).
+__global__ __launch_bounds__(kTrialBlock) void k_trial_sorted(float *__restrict__ x,
+                                                              const SliceState *__restrict__ st_in,
+                                                              SliceState *__restrict__ st_out, PertParams pp,
+                                                              const double *__restrict__ part,
+                                                              const double *__restrict__ part_min, LineSorted L,
+                                                              int nt)
+{
+    constexpr int BS = kTrialBlock, T = kSmallTrials, Q = kLineMaxN / kLineChunk, P = kLineChunk / kLineBucket;
+    static_assert(Q * T == BS && Q % 64 == 0, "a thread a trial and chunk, a wave of one trial");
+    __shared__ float pivot[Q * P];
+    __shared__ double below[Q * P];
+    __shared__ double tot[kPhaseSums];
+    __shared__ double wsum[BS / 64];
+    __shared__ double coef[T];
+    __shared__ SliceState sS;
+    __shared__ StepWindow win;
+    __shared__ int summed; // trials the next batch sums (0: the phase is over)
+    double least = INFINITY; // wave 0: least nonzero |x_j|
+    if (threadIdx.x < 64) {
+        for (int b = threadIdx.x; b < nt; b += 64) least = fmin(least, part_min[b]);
+        for (int off = 32; off > 0; off >>= 1) least = fmin(least, __shfl_xor(least, off, 64));
+    }
+    derive_state<BS>(sS, st_in, pp, 1, part, 0, nt, tot, win);
+    const double gsq = tot[0], f0 = tot[1];
+    const int w = threadIdx.x / Q, q = threadIdx.x % Q;
+    bool staged = false;
+    phase_rounds(
+        threadIdx.x < 64, summed, [&] { return line_trials<OBJ_L1>(sS, pp, win, f0, gsq, least, T); },
+        [&](int ntr) {
+            if (!staged) { // the same in every thread
+                for (int i = threadIdx.x; i < nt * P; i += BS) {
+                    pivot[i] = L.pivot[i];
+                    below[i] = L.below[i];
+                }
+                staged = true;
+            }
+            if (threadIdx.x < ntr) coef[threadIdx.x] = sS.s_acc + step_of(win, pp, sS, sS.ell + threadIdx.x);
+            __syncthreads();
+            double ex[1] = {0.0};
+            if (w < ntr && q < nt) {
+                const double tau = coef[w] / sS.gn;
+                const float *pv = pivot + q * P;
+                int c = 0; // pivots below tau
+#pragma unroll
+                for (int h = P / 2; h > 0; h >>= 1)
+                    if ((double)pv[c + h - 1] < tau) c += h;
+                if ((double)pv[c] < tau) ++c;
+                if (c > 0) { // the keys before bucket c - 1 are below tau, and some of its own
+                    const int bk = q * P + c - 1;
+                    const float4 *key = reinterpret_cast<const float4 *>(L.key + (size_t)bk * kLineBucket);
+                    float4 a[kLineBucket / 4];
+#pragma unroll
+                    for (int h = 0; h < kLineBucket / 4; ++h) a[h] = key[h];
+                    double cnt = (double)((c - 1) * kLineBucket), sum = below[bk];
+#pragma unroll
+                    for (int h = 0; h < kLineBucket / 4; ++h) {
+                        const float f[4] = {a[h].x, a[h].y, a[h].z, a[h].w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if ((double)f[e] < tau) {
+                                cnt += 1.0;
+                                sum += (double)f[e];
+                            }
+                    }
+                    ex[0] = cnt * tau - sum;
+                }
+            }
+            wave_sum<1>(ex);
+            if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = ex[0];
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                int acc = -1;
+                double fa = 0.0;
+                for (int t = 0; t < ntr && acc < 0; ++t) {
+                    double e2 = 0.0;
+                    for (int h = 0; h < Q / 64; ++h) e2 += wsum[t * (Q / 64) + h];
+                    const double ft = f0 - coef[t] * (gsq / sS.gn) + 2.0 * e2;
+                    if (ft <= sS.f_cur) {
+                        acc = t;
+                        fa = ft;
+                    }
+                }
+                record_decision(sS, pp, ntr, acc, fa, acc >= 0 ? step_of(win, pp, sS, sS.ell + acc) : 0.0);
+            }
+        },
+        [] { __syncthreads(); });
+    const bool apply = must_apply(sS);
+    publish_state(sS, st_out, 0, apply);
+    if (apply) {
+        const double inv_gn = 1.0 / sS.gn, s_acc = sS.s_acc;
+        const int n = (int)pp.n;
+        for (int j = blockIdx.x * BS + threadIdx.x; j < n; j += gridDim.x * BS) {
+            const float xf = x[j];
+            const double gj = xf > 0.f ? 1.0 : (xf < 0.f ? -1.0 : 0.0);
+            x[j] = (float)((double)xf + s_acc * (-gj * inv_gn));
+        }
+    }
+}
+
 // Trial launch for the squared norm and the linear objective (flat vectors).
 __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, const float *__restrict__ g,
                                                        const SliceState *__restrict__ st_in,
@@ -4911,7 +5144,50 @@ bool phase_on_line(const PertParams &pp)
 {
     // k_trial_line steps an int by its grid's threads: longer vectors take the chain, which counts in 64 bits
     constexpr long long walk = (1LL << 31) - (long long)kFlatPhaseGrid * kTrialBlock;
-    return (pp.obj == OBJ_SQNORM && pp.n <= walk) || (pp.obj == OBJ_L1 && pp.n <= kLineMaxN);
+    if (pp.obj == OBJ_SQNORM) return pp.n <= walk;
+    return pp.obj == OBJ_L1 && pp.n <= (pp.B == 1 ? kLineMaxN : kLineSumN);
+}
+
+bool phase_sorted(const PertParams &pp)
+{
+    return pp.obj == OBJ_L1 && pp.B == 1 && pp.n > kLineSumN && pp.n <= kLineMaxN;
+}
+
+static size_t line_chunks(const PertParams &pp) { return size_t((pp.n + kLineChunk - 1) / kLineChunk); }
+
+size_t line_sorted_bytes(const PertParams &pp)
+{
+    return phase_sorted(pp) ? line_chunks(pp) * (sizeof(float) * kLineChunk +
+                                                 (sizeof(double) + sizeof(float)) * (kLineChunk / kLineBucket))
+                            : 0;
+}
+
+LineSorted line_sorted(void *buf, const PertParams &pp)
+{
+    const size_t chunks = line_chunks(pp), pivots = chunks * (kLineChunk / kLineBucket);
+    LineSorted L;
+    L.key = static_cast<float *>(buf);
+    L.below = reinterpret_cast<double *>(L.key + chunks * kLineChunk);
+    L.pivot = reinterpret_cast<float *>(L.below + pivots);
+    return L;
+}
+
+hipError_t launch_phase_sorted(const PertParams &pp, const float *x, const SliceState *st, const LineSorted &L,
+                               double *partials, double *part_min, hipStream_t s)
+{
+    if (!phase_sorted(pp) || size_t(phase_grid(pp)) != line_chunks(pp)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_phase_sorted, dim3(phase_grid(pp)), dim3(kBlock), 0, s, x, (int)pp.n, st, L, partials,
+                       part_min);
+    return hipGetLastError();
+}
+
+hipError_t launch_trial_sorted(const PertParams &pp, float *x, const SliceState *st_in, SliceState *st_out,
+                               const LineSorted &L, const double *part_phase, const double *part_min, hipStream_t s)
+{
+    if (!phase_sorted(pp) || pp.max_trials < 1 || pp.max_trials > 1024) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_trial_sorted, dim3(phase_grid(pp)), dim3(kTrialBlock), 0, s, x, st_in, st_out, pp,
+                       part_phase, part_min, L, phase_grid(pp));
+    return hipGetLastError();
 }
 
 hipError_t launch_trial_line(const PertParams &pp, float *x, const float *xc, const SliceState *st_in,

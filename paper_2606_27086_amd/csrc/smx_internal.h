@@ -21,7 +21,20 @@ constexpr int kSmallPhaseMaxN = 20000; // longest x it takes (x and the directio
 constexpr int kSmallPhaseAutoN = 8192; // longest x it is the default for
 constexpr int kSmallTrials = 8;        // trials per batch there
 constexpr int kFlatPhaseGrid = 512;    // most workgroups (a slice) of the flat objectives' phase launches
-constexpr int kLineMaxN = 131072;      // longest x the L1 norm's phase sums in every workgroup alike
+// The L1 norm's phase on the line (phase_on_line).  Past a change of sign every
+// workgroup sums the trials over all of x up to kLineSumN; beyond, one slice
+// has x sorted in chunks by the direction launch (phase_sorted), up to
+// kLineMaxN, and several slices take the chain of launches.  An iteration, 16 x
+// 32 Fresnel rows, four steps with changes of sign, summed / sorted / chain: n =
+// 8,464 72 / 75 / 116 us, 16,384 74 / 69 / 113, 24,336 99 / 75 / -, 32,761 124 /
+// 89 / 132, 65,536 118 / 51 / 91, 131,044 207 / 69 / 102; one step 56 / 57 / 69,
+// 52 / 51 / 66, 69 / 62 / -, 87 / 76 / 85, 55 / 36 / 44, 88 / 48 / 54.  Without a
+// change of sign at 16,384 43.1 / 44.5 / 64.5.  Several slices summed / chain:
+// 16,384 of 8 169 / 185 us, 32,761 of 8 290 / 272, of 32 1,023 / 766.
+constexpr int kLineSumN = 16384;
+constexpr int kLineMaxN = 131072; // the chunks that k_trial_sorted has threads for
+constexpr int kLineChunk = 1024; // entries sorted by a workgroup of the direction launch
+constexpr int kLineBucket = 32;  // keys of a chunk between two of its pivots
 constexpr size_t kFusedStaticLds = 1024; // bytes of LDS left to the fused kernels' own arrays
 constexpr int kApplyBlock = 1024;  // threads of the fused pass's apply kernel (16 waves share a column's partials)
 
@@ -398,12 +411,28 @@ int phase_grid(const PertParams &pp);
 // (part_min, squared norm and L1: g gets a copy of x, part_min B*tiles minima of the nonzero |x_j|)
 hipError_t launch_phase(const PertParams &pp, const float *x, float *g, const float *lin_c, const SliceState *st,
                         int eval_only, double *partials, hipStream_t s, double *part_min = nullptr);
-// Whether the phase's trials can be valued along the line (squared norm, L1 up
-// to kLineMaxN), and that phase after launch_phase with part_min (xc: its copy
-// of x): decisions and the accepted step in one launch.
+// Whether the phase's trials can be valued along the line, and that phase after
+// launch_phase with part_min (xc: its copy of x): decisions and the accepted
+// step in one launch.
 bool phase_on_line(const PertParams &pp);
 hipError_t launch_trial_line(const PertParams &pp, float *x, const float *xc, const SliceState *st_in,
                              SliceState *st_out, const double *part_phase, const double *part_min, hipStream_t s);
+// The same for L1 beyond kLineSumN (phase_sorted): the direction launch leaves
+// |x_j| sorted in chunks of kLineChunk, the first key of every bucket and the
+// sum of the chunk's keys before it, from which a trial's value takes one
+// search a chunk.
+struct LineSorted {
+    float *key;    // [chunks * kLineChunk], entries that are 0 or past n last, as infinities
+    float *pivot;  // [chunks * kLineChunk / kLineBucket]
+    double *below; // likewise
+};
+bool phase_sorted(const PertParams &pp);
+size_t line_sorted_bytes(const PertParams &pp); // 0 unless phase_sorted
+LineSorted line_sorted(void *buf, const PertParams &pp);
+hipError_t launch_phase_sorted(const PertParams &pp, const float *x, const SliceState *st, const LineSorted &L,
+                               double *partials, double *part_min, hipStream_t s);
+hipError_t launch_trial_sorted(const PertParams &pp, float *x, const SliceState *st_in, SliceState *st_out,
+                               const LineSorted &L, const double *part_phase, const double *part_min, hipStream_t s);
 // query: per slice the proximity from pass 1's partials into out[B], and f(x)
 // from eval_only phase partials (part_obj, may be null) into out[B .. 2B - 1]
 hipError_t launch_query_out(SliceState *st, const PertParams &pp, const double *part_prox, int nparts,

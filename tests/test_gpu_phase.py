@@ -206,3 +206,54 @@ def test_tv_phase_of_several_slices(smx, B, R, C):
     whole lines in tiles of 2, 4, 8 and 16 rows; four steps with rejected trials."""
     w = W.random_sparse(300, R * C, 6, seed=B + R, B=B, obj=W.OBJ_TV2D, K=1, tv_shape=(R, C))
     check_iteration(smx, w.with_params(gamma=200.0, alpha=0.93, n_red=4), expect_launches=8)
+
+
+@pytest.mark.parametrize("n,gamma,n_red,kind", [
+    (16385, 30.0, 4, "spread"),   # the shortest sorted x: 17 chunks, one entry in the last
+    (25600, 1e-4, 2, "spread"),   # no entry changes sign: closed form
+    (32761, 300.0, 3, "ties"),    # three magnitudes: whole runs of equal keys
+    (65536, 60.0, 1, "sparse"),   # most entries zero, the rest small
+    (100003, 2e3, 4, "spread"),   # steps past the largest entry, rejected
+    (131071, 100.0, 4, "spread"),
+    (131072, 400.0, 2, "ties"),
+])
+def test_l1_phase_from_sorted_chunks(smx, n, gamma, n_red, kind):
+    """L1 beyond n = 16,384: the direction launch sorts |x_j| in chunks, and a
+    trial past a change of sign takes a search a chunk."""
+    w = W.random_sparse(300, n, 10, seed=n % 91, obj=W.OBJ_L1, K=1)
+    rng = np.random.default_rng(n)
+    x0 = rng.uniform(-0.2, 1.0, (n, 1))
+    if kind == "ties":
+        x0 = np.array([0.0, 0.25, -0.5, 0.75])[rng.integers(0, 4, (n, 1))]
+    elif kind == "sparse":
+        x0 = np.where(rng.random((n, 1)) < 0.9, 0.0, 0.3 * x0 * rng.random((n, 1)))
+    w = w.with_params(gamma=gamma, alpha=0.9, n_red=n_red, x0=x0.astype(np.float32))
+    check_iteration(smx, w, expect_launches=2)
+
+
+def test_sorted_phase_ends_at_the_trial_cap(smx):
+    """Every trial rejected, in batches of eight and a rest of five."""
+    w = W.random_sparse(300, 30000, 10, seed=97, obj=W.OBJ_L1, K=1).with_params(gamma=1e6, alpha=0.99, n_red=2,
+                                                                               max_trials=21)
+    st = check_iteration(smx, w, expect_launches=2)
+    assert st[0]["trials"] == 21 and st[0]["accepts"] == 0 and st[0]["cap_hits"] == 1
+
+
+@pytest.mark.parametrize("B,n,launches", [(2, 16384, 2), (2, 16385, 6), (8, 16385, 6)])
+def test_l1_phase_of_several_slices(smx, B, n, launches):
+    """Several slices sum past a change of sign up to n = 16,384, then take the
+    chain."""
+    w = W.random_sparse(200, n, 8, seed=B, B=B, obj=W.OBJ_L1, K=1)
+    check_iteration(smx, w.with_params(gamma=40.0, alpha=0.9, n_red=2), expect_launches=launches)
+
+
+def test_footprint_counts_the_sorted_chunks(smx):
+    """16,385 unknowns allocate what the plan says, with the chunks' buffer."""
+    w = W.random_sparse(100, 16385, 5, seed=4, obj=W.OBJ_L1, K=1)
+    p = smx.problem_from_workload(w)
+    got = p.describe()["device_bytes"]
+    p.close()
+    _, plan = smx.problem_footprint(w.m, w.n, len(w.val), "f32", obj=W.OBJ_L1)
+    assert got == plan
+    _, short = smx.problem_footprint(w.m, 16384, len(w.val), "f32", obj=W.OBJ_L1)
+    assert plan - short >= 17 * (1024 * 4 + 32 * 12)
