@@ -417,7 +417,7 @@ PassCfg pick_cfg(const DevLayout &L, int vk, int B = 1)
     c.vec = (vk == VK_F32) ? 4 : 8;
     if (B > 1) {
         c.mode = 0;
-        c.lpr = mm_lanes(B, 1);
+        c.lpr = mm_default(B, L.rows > 0 ? double(L.slots) / double(L.rows) : 0.0);
         const int64_t rpb = kBlock / c.lpr;
         c.grid = (int)std::max<int64_t>(1, std::min<int64_t>((L.rows + rpb - 1) / rpb, kMaxPassGrid));
         return c;
@@ -1647,7 +1647,7 @@ int create_problem(smx_operator *op, const smx_problem_desc *d, hipStream_t s, s
         }
         if (start_tiles) {
             p->cfg2[vk].mode = 2;
-            p->cfg2[vk].lpr = B == 1 ? 4 : mm_lanes(B, 1);
+            p->cfg2[vk].lpr = B == 1 ? 4 : mm_default(B, 0.0); // a tile's share of a column is short
             p->cfg2[vk].vec = 4;
             p->cfg2[vk].grid = std::max(1, std::min(op->t_ntiles, kMaxPassGrid));
         }

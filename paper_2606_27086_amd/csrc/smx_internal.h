@@ -295,10 +295,17 @@ hipError_t launch_disable_slot(SliceState *st, int slot, hipStream_t s);
 
 // lanes per row of the multi-slice passes for B slices, choice i of 3: the
 // lanes over the slices (four slices a lane) times 1, 2 or 4 lanes over the
-// entries (B = 32), 2, 4 or 8 (B = 8, 16), 4, 8 or 16 (B = 2, 4)
+// entries (B = 32), 2, 4 or 8 (B = 16), 4, 8 or 16 (B = 2 to 8)
 // (256 x 256 CT, B = 32, bf16: pass 1 112 us with 16 lanes, 119 / 125 with 8
-// / 32 at 1,024 workgroups; pass 2 101 / 116 / 103)
-constexpr int mm_lanes(int B, int i) { return (B >= 16 ? 8 : 4) << i; }
+// / 32 at 1,024 workgroups; pass 2 101 / 116 / 103).  B = 8 had 2, 4 or 8
+// lanes over the entries, too few where rows are few and long: 512 rows of 6,008
+// entries, an iteration 197 us tuned, now 104 (180 before the lanes were split).
+constexpr int mm_lanes(int B, int i) { return (B >= 8 ? 8 : 4) << i; }
+// the choice of an untuned pass over rows of `mean` entries: the middle one,
+// but for 8 slices the first while a row takes its lanes 16 loads or fewer (CT
+// 256 x 256, 226 entries a row: an iteration 45 us against 48 with the middle
+// one; rows of 2,172 entries 110 against 74)
+constexpr int mm_default(int B, double mean) { return mm_lanes(B, B == 8 && mean <= 256.0 ? 0 : 1); }
 
 constexpr int kMaxPassGrid = 4096; // workgroups of a pass kernel (one proximity partial each)
 

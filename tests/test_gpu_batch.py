@@ -234,3 +234,26 @@ def test_slot_load_rejects_bad_input(smx):
     with pytest.raises(smx.SmxError):
         p.slot_load(0, w.lower[:, 0], w.upper[:, 0], w.x0[:, 0], -1)
     p.close()
+
+
+@pytest.mark.parametrize("m,n,mean,lanes", [(40, 5000, 2000, 16), (500, 3000, 40, 8)])
+def test_lanes_of_eight_slices(smx, m, n, mean, lanes):
+    """Eight slices: 16 lanes a row where rows are long, 8 where they are short,
+    and whatever of 8, 16 and 32 the tuner takes.  c and x are float32 values of
+    float64 sums, so another order moves x by a rounding or two."""
+    w = W.random_sparse(m, n, mean, seed=m, B=8, obj=W.OBJ_NONE, K=1)
+    p = smx.problem_from_workload(w)
+    assert p.describe()["f32"]["pass1"]["lpr"] == lanes
+    p.run(1, perturb=False)
+    x = p.get_x().cpu().numpy().astype(np.float64)
+    for s in range(8):
+        P = oracle.from_workload(w, s)
+        xo, _ = P.step(w.x0[:, s].astype(np.float64))
+        assert np.max(np.abs(x[:, s] - xo)) <= 4 * 2.0 ** -24 * max(1.0, np.max(np.abs(xo)))
+    p.set_x(w.x0)
+    p.autotune(reps=2)
+    assert p.describe()["f32"]["pass1"]["lpr"] in (8, 16, 32)
+    p.run(1, perturb=False)
+    y = p.get_x().cpu().numpy().astype(np.float64)
+    p.close()
+    assert np.max(np.abs(x - y)) <= 4 * 2.0 ** -24 * max(1.0, np.max(np.abs(x)))
