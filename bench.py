@@ -88,9 +88,8 @@ def alg_bytes(m, n, nnz, shapes, B=1, tiles=None):
     if fused_in_use(shapes):
         f = shapes["fused"]
         e1 = ENTRY_BYTES[f["format"]]
-        acc = 8 if f["acc"] == "f64" else 4
         p1 = nnz * e1 + 4 * (m + 1) + 12 * m + 4 * n + 8 * n
-        p2 = acc * n * f["grid"] + 16 * n
+        p2 = (8 if f["partials"]["type"] == "f64" else 4) * n * f["partials"]["vectors"] + 16 * n
         return p1, p2
     e2 = ENTRY_BYTES[shapes["pass2"]["format"]]
     p1 = nnz * e1 + 4 * (m + 1) + 4 * m + B * (8 * m + 4 * m + 4 * n)
@@ -114,7 +113,8 @@ def kernel_name(pass_no, shape, B=1, shapes=None):
             if f.get("cap", 0):
                 return f"smx::k_fused_rc<{f['lpr']}, {f['vec']}, {f['cap']}, {VALUE_TAG[f['format']]}, {acc}>"
             return f"smx::k_fused<{f['lpr']}, {f['vec']}, {VALUE_TAG[f['format']]}, {acc}>"
-        return f"smx::k_fused_apply<{acc}, 64>"  # 64 unknowns a workgroup (n > 1,024)
+        y = f["partials"]  # what the pass (and the dose-volume rows' kernel) left, columns a workgroup
+        return f"smx::k_fused_apply<{'double' if y['type'] == 'f64' else 'float'}, {y['columns']}>"
     vt = VALUE_TAG[shape["format"]]
     if shape["mode"] == "lds":
         return f"smx::k_pass{pass_no}_lds<{shape['lpr']}, {shape['vec']}, {vt}>"

@@ -2004,9 +2004,11 @@ int describe_impl(const smx_problem *p, char *buf, size_t cap, size_t *need)
             const FusedCfg &f = p->fcfg[vk];
             snprintf(fz, sizeof fz,
                      "{\"in_use\": %s, \"lpr\": %d, \"vec\": %d, \"cap\": %d, \"zl\": %d, \"grid\": %d, "
-                     "\"acc\": \"%s\", \"format\": \"%s\"}",
+                     "\"acc\": \"%s\", \"format\": \"%s\", \"partials\": {\"type\": \"%s\", \"vectors\": %d, "
+                     "\"columns\": %d}}",
                      p->fused[vk] ? "true" : "false", f.lpr, f.vec, f.cap, f.zl, f.grid, f.acc64 ? "f64" : "f32",
-                     fmt_name(fused_fmt(p, vk)));
+                     fmt_name(fused_fmt(p, vk)), f.acc64 && !f.out32 ? "f64" : "f32",
+                     f.grid + (p->dvc.n > 0 ? scatter_rows_grid(p->dvc.span, f.grid) : 0), fused_apply_cols(p->n));
         } else {
             snprintf(fz, sizeof fz, "null");
         }

@@ -4625,7 +4625,7 @@ size_t fused_zl_lds_bytes(int64_t n, int acc64)
     return size_t((n + 3) & ~int64_t(3)) * (sizeof(float) + (acc64 ? sizeof(double) : sizeof(float)));
 }
 
-static inline int fused_apply_cols(int64_t n) { return n <= 1024 ? 16 : 64; } // unknowns of a workgroup
+int fused_apply_cols(int64_t n) { return n <= 1024 ? 16 : 64; }
 int fused_apply_grid(int64_t n) { return (int)grid_for(n, fused_apply_cols(n), 4096); }
 
 size_t fused_lds_limit()

@@ -377,6 +377,7 @@ hipError_t launch_fused(const FusedCfg &cfg, const SpView &A, int vk, int64_t n,
                         hipStream_t s, const LinPhase *lp = nullptr);
 // workgroups of the fused pass's apply kernel (its ||y||^2 partials in deferred mode)
 int fused_apply_grid(int64_t n);
+int fused_apply_cols(int64_t n); // unknowns of each
 // x = clip(z + lambda * sum of the partial vectors, lo, hi), closing the
 // iteration; in deferred mode (cs.defer) y itself into cs.ybuf (and ybuf32)
 // with fused_apply_grid(n) partials of ||y||^2 in cs.ypart (the extrapolated

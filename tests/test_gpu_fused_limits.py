@@ -127,3 +127,26 @@ def test_pinned_shape_takes_the_larger_grid(smx):
         p.set_fused_shape(*shape)
         assert p.describe()["f32"]["fused"]["grid"] == grid, shape
     p.close()
+
+
+@pytest.mark.parametrize("n,dvc,kind,vectors,columns", [
+    (900, False, "f64", 64, 16), (1025, False, "f64", 64, 64), (900, True, "f32", 65, 16),
+    (13569, True, "f32", 65, 64), (21000, False, "f32", 64, 64),
+])
+def test_describe_names_the_partial_vectors(smx, n, dvc, kind, vectors, columns):
+    """What the launch after the fused pass sums: float64 vectors from a float64
+    y, float32 ones from a float32 y and wherever dose-volume rows add theirs
+    (here one more), 16 or 64 columns a workgroup; the benchmark's byte count
+    and kernel name go by it."""
+    import bench
+
+    w = W.random_sparse(300, n, 8, seed=n % 89, obj=W.OBJ_NONE, K=1)
+    if dvc:
+        w = w.with_params(dvc=[dict(row_begin=180, row_end=300, sense=W.DVC_MAX, fraction=0.3, dose=0.1)])
+    p = smx.problem_from_workload(w)
+    shapes = p.describe()["f32"]
+    p.close()
+    assert shapes["fused"]["partials"] == dict(type=kind, vectors=vectors, columns=columns)
+    size, name = (8, "double") if kind == "f64" else (4, "float")
+    assert bench.alg_bytes(w.m, n, w.nnz, shapes)[1] == size * n * vectors + 16 * n
+    assert bench.kernel_name(2, shapes["pass2"], 1, shapes) == f"smx::k_fused_apply<{name}, {columns}>"
