@@ -1280,10 +1280,9 @@ int build_dvc_table(const smx_problem_desc *d, int64_t m, DvcTable &dt)
 }
 
 // Launch shape of the fused single pass for a problem of n unknowns and B
-// slices on the current device, or false where it has none: one slice, no
-// dose-volume rows (their ranking precedes c), an LDS copy of y that fits
-// (float64 if it can, else float32), one or two workgroups per CU as the LDS
-// allows.
+// slices on the current device, or false where it has none: one slice, an LDS
+// copy of y that fits (float64 if it can, else float32; with dose-volume rows z
+// beside it), one or two workgroups per CU as the LDS allows.
 bool fused_plan(int64_t m, int64_t n, int64_t nnz, int B, int n_dvc, FusedCfg &c, size_t &lds_bytes)
 {
     if (B != 1) return false;

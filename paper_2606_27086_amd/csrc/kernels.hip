@@ -4356,6 +4356,20 @@ __device__ inline double fused_epilogue(const RowW &w, long long row, double r, 
     return (double)sw * t;
 }
 
+// A workgroup's y as its partial vector, float64 or (out32, or a float32 y)
+// float32.
+template <typename AccT>
+__device__ inline void write_partial(void *ypart, int out32, int n, const AccT *y)
+{
+    if (out32 || sizeof(AccT) == sizeof(float)) {
+        float *out = static_cast<float *>(ypart) + (long long)blockIdx.x * n;
+        for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = (float)y[j];
+    } else {
+        double *out = static_cast<double *>(ypart) + (long long)blockIdx.x * n;
+        for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = (double)y[j];
+    }
+}
+
 // Fused pass with the gathered vector in LDS.  The plain fused pass gathers
 // z_j through the vector memory path once per stored entry, about one
 // address per CU per clock, which bounds it on long operators.  Here each
@@ -4371,20 +4385,6 @@ __device__ inline double fused_epilogue(const RowW &w, long long row, double r, 
 // workgroup; k_fused_apply adds them in float64.  A float64 y costs half
 // the adds' time or less: ds_add_f32 takes 192 clocks a wave whatever its
 // addresses (3 a lane), ds_add_f64 8 to 16 where they spread over the banks.
-// A workgroup's y as its partial vector, float64 or (out32, or a float32 y)
-// float32.
-template <typename AccT>
-__device__ inline void write_partial(void *ypart, int out32, int n, const AccT *y)
-{
-    if (out32 || sizeof(AccT) == sizeof(float)) {
-        float *out = static_cast<float *>(ypart) + (long long)blockIdx.x * n;
-        for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = (float)y[j];
-    } else {
-        double *out = static_cast<double *>(ypart) + (long long)blockIdx.x * n;
-        for (int j = threadIdx.x; j < n; j += kFusedBlock) out[j] = (double)y[j];
-    }
-}
-
 template <int LPR, int VEC, typename VT, typename AccT>
 __global__ __launch_bounds__(kFusedBlock) void k_fused_zl(SpView A, int n, const float *__restrict__ x,
                                                           const float *__restrict__ lower,

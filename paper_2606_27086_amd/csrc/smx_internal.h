@@ -445,13 +445,6 @@ hipError_t launch_trial_sorted(const PertParams &pp, float *x, const SliceState 
 // from eval_only phase partials (part_obj, may be null) into out[B .. 2B - 1]
 hipError_t launch_query_out(SliceState *st, const PertParams &pp, const double *part_prox, int nparts,
                             const double *part_obj, double *out, hipStream_t s);
-// One trial launch: derives the state (first: the phase opening from the
-// gradient partials; otherwise the previous launch's decision from its trial
-// partials), then the next batch of trial steps (partials
-// [max_trials][B*tiles] into part_out), or adds the accepted step to x once
-// the phase is over.  The derived state goes to st_out.  after: trial launches
-// behind this one in the phase.
-// the closing launch of a phase (one workgroup per slice)
 // Whether the perturbation phase runs as one launch (flat objectives, short
 // vectors), and that launch: state st_in in, st_out out.
 bool phase_in_one_launch(const PertParams &pp);
@@ -464,8 +457,15 @@ hipError_t launch_phase_small(const PertParams &pp, float *x, const float *lin_c
 // part_phase): trials in closed form, the accepted step added to x.
 hipError_t launch_trial_linear(const PertParams &pp, float *x, const float *c, const SliceState *st_in,
                                SliceState *st_out, const double *part_phase, hipStream_t s, int nt = 0);
+// the closing launch of a phase
 hipError_t launch_trial_close(const PertParams &pp, float *x, const float *g, const SliceState *st_in,
                               SliceState *st_out, const double *part_prev, hipStream_t s);
+// One trial launch: derives the state (first: the phase opening from the
+// gradient partials; otherwise the previous launch's decision from its trial
+// partials), then the next batch of trial steps (partials
+// [max_trials][B*tiles] into part_out), or adds the accepted step to x once
+// the phase is over.  The derived state goes to st_out.  after: trial launches
+// behind this one in the phase.
 hipError_t launch_trial(const PertParams &pp, float *x, const float *g, const SliceState *st_in, SliceState *st_out,
                         int first, int after, const double *part_prev, double *part_out, hipStream_t s);
 
