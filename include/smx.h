@@ -524,8 +524,10 @@ int smx_set_phase_form(smx_problem *p, int32_t form);
  * or 32 lanes only) to keep 256 entries of each row in registers.  With
  * z_in_lds != 0 (problems whose n is at most about 20k): every workgroup
  * first copies the whole point z into LDS beside its y (float64 where 12n
- * bytes fit, else float32) and gathers from there instead of from memory; cap is then 0 or 16/vec (each
- * lane keeps 16 entries of its row in registers for the scatter).
+ * bytes fit, else float32) and gathers from there instead of from memory;
+ * cap is then 0 or 16/vec (each lane keeps 16 entries of its row in registers
+ * for the scatter).  Where the tuner tries a shape at two grids (z in LDS, up
+ * to 2,048 columns) the larger is pinned.
  * Results do not depend on the shape beyond floating-point summation order.
  * Errors: SMX_ESTATE when the problem has no fused pass, SMX_EINVAL for
  * another shape. */
