@@ -504,11 +504,11 @@ int smx_set_fused(smx_problem *p, int32_t mode);
  *     time; one workgroup reads x at one compute unit's rate, so on longer
  *     vectors it is no faster than the chain), else CLOSED_FORM for the
  *     linear objective, else, for the squared norm and for L1 up to n =
- *     131,072 (several slices: 16,384), a direction launch and one launch that
- *     takes each trial's value from f along the line x + t v (the squared norm
- *     in closed form; L1 in closed form while no entry changes sign, beyond
- *     by summation up to 16,384 and from |x| sorted in chunks on longer
- *     vectors), else BATCHES.
+ *     131,072 (several slices: 16,384; not 32 of them), a direction launch
+ *     and one launch that takes each trial's value from f along the line
+ *     x + t v (the squared norm in closed form; L1 in closed form while no
+ *     entry changes sign, beyond by summation up to 16,384 and from |x| sorted
+ *     in chunks on longer vectors), else BATCHES.
  * Every form accepts the same trial (the first acceptable one in order) and
  * keeps the same state; they differ in the order of the float64 sums of f
  * (and those in closed form in taking a trial's value from the identity), so a

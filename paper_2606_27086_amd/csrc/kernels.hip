@@ -5145,7 +5145,8 @@ bool phase_on_line(const PertParams &pp)
     // k_trial_line steps an int by its grid's threads: longer vectors take the chain, which counts in 64 bits
     constexpr long long walk = (1LL << 31) - (long long)kFlatPhaseGrid * kTrialBlock;
     if (pp.obj == OBJ_SQNORM) return pp.n <= walk;
-    return pp.obj == OBJ_L1 && pp.n <= (pp.B == 1 ? kLineMaxN : kLineSumN);
+    if (pp.obj != OBJ_L1) return false;
+    return pp.B == 1 ? pp.n <= kLineMaxN : pp.n <= kLineSumN && phase_grid(pp) * pp.B <= kLineSumGroups;
 }
 
 bool phase_sorted(const PertParams &pp)

@@ -30,8 +30,13 @@ constexpr int kFlatPhaseGrid = 512;    // most workgroups (a slice) of the flat 
 // 89 / 132, 65,536 118 / 51 / 91, 131,044 207 / 69 / 102; one step 56 / 57 / 69,
 // 52 / 51 / 66, 69 / 62 / -, 87 / 76 / 85, 55 / 36 / 44, 88 / 48 / 54.  Without a
 // change of sign at 16,384 43.1 / 44.5 / 64.5.  Several slices summed / chain:
-// 16,384 of 8 169 / 185 us, 32,761 of 8 290 / 272, of 32 1,023 / 766.
+// 16,384 of 8 169 / 185 us, 32,761 of 8 290 / 272, of 32 1,023 / 766; the sums
+// are a workgroup's for each slice and 1,024 entries, of which a CU holds one,
+// so beyond 256 of them a second round waits: with rejected trials 16 slices of
+// 16,384 (256 workgroups) 85 / 93, 32 of 8,464 (288) 136 / 122, of 12,000 (384)
+// 168 / 120.
 constexpr int kLineSumN = 16384;
+constexpr int kLineSumGroups = 256;
 constexpr int kLineMaxN = 131072; // the chunks that k_trial_sorted has threads for
 constexpr int kLineChunk = 1024; // entries sorted by a workgroup of the direction launch
 constexpr int kLineBucket = 32;  // keys of a chunk between two of its pivots

@@ -239,10 +239,11 @@ def test_sorted_phase_ends_at_the_trial_cap(smx):
     assert st[0]["trials"] == 21 and st[0]["accepts"] == 0 and st[0]["cap_hits"] == 1
 
 
-@pytest.mark.parametrize("B,n,launches", [(2, 16384, 2), (2, 16385, 6), (8, 16385, 6)])
+@pytest.mark.parametrize("B,n,launches", [(2, 16384, 2), (2, 16385, 6), (8, 16385, 6), (16, 16384, 2),
+                                          (32, 8193, 6)])
 def test_l1_phase_of_several_slices(smx, B, n, launches):
-    """Several slices sum past a change of sign up to n = 16,384, then take the
-    chain."""
+    """Several slices sum past a change of sign up to n = 16,384 and 256
+    workgroups, then take the chain."""
     w = W.random_sparse(200, n, 8, seed=B, B=B, obj=W.OBJ_L1, K=1)
     check_iteration(smx, w.with_params(gamma=40.0, alpha=0.9, n_red=2), expect_launches=launches)
 
