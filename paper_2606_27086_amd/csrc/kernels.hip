@@ -3383,7 +3383,9 @@ __global__ __launch_bounds__(kBlock) void k_trial_flat(float *__restrict__ x, co
         return;
     }
     publish_state(S, st_out, s, false);
-    const int ntr = trial_width(S, pp, after);
+    // the same in every lane: in a scalar register the trials' conditions are branches, not masks (L1, 20M
+    // unknowns, the first batch 201 us without)
+    const int ntr = __builtin_amdgcn_readfirstlane(trial_width(S, pp, after));
     if (ntr == 0) return;
     const long long nslots = (long long)B * nt, slot = (long long)s * nt + blockIdx.x;
     const double inv_gn = 1.0 / S.gn;
