@@ -21,7 +21,7 @@ COPY_BYTES = 512 * 1024 * 1024
 
 def kernel_source_hash() -> str:
     h = hashlib.sha256()
-    for f in ("kernels.hip", "smx_internal.h"):
+    for f in ("kernels.hip", "smx_internal.h", "phase_rounds.h"):
         h.update(open(os.path.join(HERE, "csrc", f), "rb").read())
     return h.hexdigest()
 

@@ -258,3 +258,30 @@ def test_footprint_counts_the_sorted_chunks(smx):
     assert got == plan
     _, short = smx.problem_footprint(w.m, 16384, len(w.val), "f32", obj=W.OBJ_L1)
     assert plan - short >= 17 * (1024 * 4 + 32 * 12)
+
+
+@pytest.mark.parametrize("obj,n", [(W.OBJ_SQNORM, 9000), (W.OBJ_L1, 9000), (W.OBJ_L1, 20000)])
+def test_adaptive_step_on_the_line(smx, obj, n):
+    """The adaptive step has one trial a phase, whose step no window holds: four
+    iterations on the line and by the chain take the same ones.  x0 is near 0, so
+    that the steps T raise f and every later phase has its trial.  The passes
+    of both are the bitwise ones and f agrees to float64 summation, so an
+    iteration moves an entry by a float32 rounding of z and of x, which T passes
+    on as they are: 8 u of the largest entry after four, u = 2^-24, and twice
+    that of f relative to the sum of |x_j| or x_j^2."""
+    w = W.random_sparse(500, n, 12, seed=n % 83, obj=obj, K=1)
+    rng = np.random.default_rng(n)
+    w = w.with_params(x0=(0.02 * rng.uniform(-1.0, 1.0, (n, 1))).astype(np.float32))
+    got = []
+    for form in (smx.PHASE_AUTO, smx.PHASE_BATCHES):
+        p = smx.problem_from_workload(w, fused=False, history_cap=8, step_rule=1)
+        p.set_phase_form(form)
+        p.run(4)
+        h = p.history()
+        got.append((tuple(h["trials"][:, 0]), tuple(h["accepts"][:, 0]), h["f_start"][:, 0].copy(),
+                    p.get_x().cpu().numpy().astype(np.float64)))
+        p.close()
+    assert got[0][:2] == got[1][:2] and sum(got[0][0]) >= 2
+    u = 2.0 ** -24
+    assert np.all(np.abs(got[0][2] - got[1][2]) <= 32 * u * np.abs(got[1][2]))
+    assert np.max(np.abs(got[0][3] - got[1][3])) <= 8 * u * max(1.0, np.max(np.abs(got[1][3])))
