@@ -1350,20 +1350,21 @@ __device__ inline void lds_add_entries(float *y, const int (&c)[VEC], const floa
     unsigned *const w = reinterpret_cast<unsigned *>(y);
     float a[VEC];
     unsigned was[VEC], now[VEC];
-    bool any = false;
+    bool nz[VEC], any = false;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        a[e] = v[e] != 0.f ? (float)(sc * (double)v[e]) : 0.f; // sc may be infinite
+        nz[e] = v[e] != 0.f;
+        a[e] = nz[e] ? (float)(sc * (double)v[e]) : 0.f; // sc may be infinite
         was[e] = __hip_atomic_load(&w[c[e]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
 #pragma unroll
     for (int e = 0; e < VEC; ++e) now[e] = atomicCAS(&w[c[e]], was[e], __float_as_uint(__uint_as_float(was[e]) + a[e]));
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) any = any || (now[e] != was[e] && a[e] != 0.f);
+    for (int e = 0; e < VEC; ++e) any = any || (now[e] != was[e] && nz[e]);
     if (!any) return;
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-        if (now[e] != was[e] && a[e] != 0.f) {
+        if (now[e] != was[e] && nz[e]) {
             was[e] = atomicCAS(&w[c[e]], now[e], __float_as_uint(__uint_as_float(now[e]) + a[e]));
             if (was[e] != now[e]) atomicAdd(&y[c[e]], a[e]);
         }
