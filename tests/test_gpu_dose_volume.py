@@ -75,3 +75,42 @@ def test_ties_rank_by_row(smx, B, fused, fractions):
         for got in (x[:, s], again[:, s]):
             assert np.all(np.abs(got - xo) <= 1.01 * (2 * u * terms + u * np.abs(xo)) + 1e-13)
         assert np.all(np.isfinite(y[:, s]))
+
+
+@pytest.mark.parametrize("fused", [True, False])
+def test_more_chunks_of_rows_than_workgroups(smx, fused):
+    """1.1 million rows in two constraints: 538 chunks of 2,048 rows, more than
+    the fused pass's workgroups (512 here), whose partials the band kernel's add
+    to, so that some take two chunks, of both constraints.  Bounds as above."""
+    rng = np.random.default_rng(7)
+    n, n0, n1, n2 = 13, 500, 700_001, 400_000
+    m = n0 + n1 + n2
+    w = W.Workload(
+        name="chunks", m=m, n=n, row_ptr=np.arange(m + 1, dtype=np.int32), col_idx=rng.integers(0, n, m).astype(np.int32),
+        val=rng.uniform(0.5, 1.5, m).astype(np.float32), lower=np.full((m, 1), 0.6, np.float32),
+        upper=np.full((m, 1), 0.7, np.float32), x0=rng.uniform(0.2, 1.0, (n, 1)).astype(np.float32),
+        box_lo=np.full(n, -np.inf, np.float32), box_hi=np.full(n, np.inf, np.float32), lam=1.0, K=1,
+        weights=rng.uniform(0.5, 2.0, m))
+    w = w.with_params(dvc=[dict(row_begin=n0, row_end=n0 + n1, sense=W.DVC_MAX, fraction=0.37, dose=0.4),
+                           dict(row_begin=n0 + n1, row_end=m, sense=W.DVC_MIN, fraction=0.41, dose=1.1)])
+    p = smx.problem_from_workload(w, fused=fused)
+    if fused:
+        assert p.describe()["f32"]["fused"]["grid"] < 538
+    prox, _ = p.query()
+    got = []
+    for _ in range(2):
+        p.set_x(w.x0)
+        p.run(1, perturb=False)
+        got.append(p.get_x().cpu().numpy().astype(np.float64)[:, 0])
+    p.close()
+    u = 2.0 ** -24
+    P, x0 = oracle.from_workload(w, 0), w.x0[:, 0].astype(np.float64)
+    xo, po = P.step(x0)
+    assert abs(prox[0] - po) <= 4 * u * po
+    lo, up = P.bands_at(x0)
+    r = P.matvec(x0)
+    c = P.w / P.row_sqnorms() * (np.clip(r, lo, up) - r)
+    terms = np.zeros(n)
+    np.add.at(terms, w.col_idx, np.abs(c * P.val))
+    for x in got:
+        assert np.all(np.abs(x - xo) <= 1.01 * (2 * u * terms + u * np.abs(xo)) + 1e-13)
